@@ -543,8 +543,9 @@ typedef struct {
     int32_t steps_per_round; /* K: steps between admission/retirement points */
     int32_t direct;          /* 0: replay captured graphs; 1: launch every kernel directly (same
                                 results; for comparison) */
-    uint64_t max_items;      /* most tiles (workgroups) one batched launch may hold: admission keeps
-                                every launch within it; a request that alone needs more is rejected */
+    uint64_t max_items;      /* most tiles one batched launch may hold (64 x 32 cells of a plain solve):
+                                admission keeps every launch within it; a request that alone needs more
+                                is rejected */
     const fv_model *model;   /* network of the learned requests (NULL: none accepted); its
                                 packed weights must be ready (its stream synchronised) */
     int32_t learned_split;   /* network tiles (8 x 8 cells) in a round's first step from which the

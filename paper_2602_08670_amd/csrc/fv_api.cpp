@@ -178,9 +178,11 @@ fv_status enqueue_step(fv_solver *s)
     if (s->batched) {
         // the server's stage arithmetic on the solve's descriptor, passed by
         // value (the copy in the workspace serves the learned kernels' list form)
-        const int tiles = ((s->cfg.nx + fvk::TILE_X - 1) / fvk::TILE_X) * ((s->cfg.ny + fvk::TILE_Y - 1) / fvk::TILE_Y);
-        e = fvk::launch_batch_stage_one(s->d.eqn, s->d.bathy, 1, s->bd, s->bi[n], tiles, s->stream);
-        if (e == hipSuccess) e = fvk::launch_batch_stage_one(s->d.eqn, s->d.bathy, 2, s->bd, s->bi[n], tiles, s->stream);
+        const int shape = fvk::stage_shape((int64_t)s->cfg.nx * s->cfg.ny);
+        const int tiles = (int)fvk::stage_tiles(s->cfg.nx, s->cfg.ny, shape);
+        e = fvk::launch_batch_stage_one(s->d.eqn, s->d.bathy, 1, shape, s->bd, s->bi[n], tiles, s->stream);
+        if (e == hipSuccess)
+            e = fvk::launch_batch_stage_one(s->d.eqn, s->d.bathy, 2, shape, s->bd, s->bi[n], tiles, s->stream);
         if (e != hipSuccess) return hip_fail(e, "stage launch");
         s->enq++;
         return FV_OK;

@@ -37,6 +37,10 @@ __device__ __forceinline__ double tmax(double a, double b) { return __builtin_fm
 __device__ __forceinline__ float tabs(float a) { return __builtin_fabsf(a); }
 __device__ __forceinline__ double tabs(double a) { return __builtin_fabs(a); }
 
+// a b + c, rounded once
+__device__ __forceinline__ float tfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double tfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // MINMOD(a, b): 0 unless a and b share a sign, else the one of smaller
 // magnitude -- which is the median of (a, b, 0).
 __device__ __forceinline__ float minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
@@ -203,141 +207,273 @@ template <typename T> __device__ __forceinline__ bool eul_admissible(T r, T m, T
 // or infinite, so one comparison of the rate covers finiteness; the
 // comparison is false for NaN.  (A positive depth so small that the rate
 // overflows is reported inadmissible too: it would stall Delta t at 0.)
+// Fused multiply-adds are written out, so that every kernel computes the
+// same bits.
 template <typename T, int EQN>
 __device__ __forceinline__ bool cell_rate_ok(const T *s, const Phys<T> &ph, T rdx, T rdy, T &rate)
 {
+#pragma clang fp contract(off)
     const T ir = rcp(s[0]);
     const T u = s[1] * ir, v = s[2] * ir;
-    T c;
-    bool pos = true;
     if (EQN == SWE) {
-        c = ph.sqg * fsqrt(s[0]);
-    } else {
-        const T p = (ph.gamma - T(1)) * (s[3] - T(0.5) * (s[1] * u + s[2] * v));
-        c = fsqrt(ph.gamma * p * ir);
-        pos = s[0] > T(0) && p > T(0);
+        const T w = fsqrt(s[0]);
+        rate = tfma(tfma(ph.sqg, w, tabs(v)), rdy, tfma(ph.sqg, w, tabs(u)) * rdx);
+        return rate < T(__builtin_inf());
     }
-    rate = (tabs(u) + c) * rdx + (tabs(v) + c) * rdy;
-    return pos && rate < T(__builtin_inf());
+    const T p = (ph.gamma - T(1)) * tfma(T(-0.5), tfma(s[2], v, s[1] * u), s[3]);
+    const T c = fsqrt(ph.gamma * p * ir);
+    rate = tfma(tabs(v) + c, rdy, (tabs(u) + c) * rdx);
+    return s[0] > T(0) && p > T(0) && rate < T(__builtin_inf());
 }
 
-// Full face computation.  Inputs: the four cells along the normal for each
-// variable, in Cartesian order (v = 0..NV-1, plus the free surface eta = h + b
-// as the last entry when BATHY).  Output: flux seen by the cell on the left
-// (FlC, NV values, Cartesian order) and the normal-momentum flux seen by the
-// cell on the right (frn) -- they differ only by the hydrostatic correction.
-// With a bed, `sd` receives the two face states the centred bed source needs:
-// {h, z} of the left state and {h, z} of the right state (z = eta - h), after
-// the positivity fallback.
+// Full face computation of a flat bottom, for the exported fluxes.  Inputs:
+// the four cells along the normal for each variable, in Cartesian order.
+// Output: the flux (NV values, Cartesian order).
 // AXIS 0: x face (normal momentum is variable 1), AXIS 1: y face (variable 2).
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int AXIS>
-__device__ __forceinline__ void face_flux(const T (*st)[4], const Phys<T> &ph, T *FlC, T &frn, T *sd)
+template <typename T, int EQN, int FLUX, int RECON, int AXIS>
+__device__ __forceinline__ void face_flux(const T (*st)[4], const Phys<T> &ph, T *F)
 {
     constexpr int NV = EQN == SWE ? 3 : 4;
-    constexpr int NR = NV + (BATHY ? 1 : 0);
     constexpr int NM = AXIS == 0 ? 1 : 2, TM = AXIS == 0 ? 2 : 1;
-    T QL[NR], QR[NR];
+    T QL[NV], QR[NV];
 #pragma unroll
-    for (int v = 0; v < NR; v++) recon_pair<T, RECON>(st[v][0], st[v][1], st[v][2], st[v][3], QL[v], QR[v]);
-    // Face states that are not admissible fall back to the cell average.  A
-    // MINMOD (or first-order) face depth of positive cell averages is at
-    // least half the cell's own depth, so for shallow water the fallback can
-    // only act where a cell average is already non-positive, which the step
-    // reports as a failure anyway: the check is kept for Euler only, where a
-    // reconstructed pressure can turn negative.
+    for (int v = 0; v < NV; v++) recon_pair<T, RECON>(st[v][0], st[v][1], st[v][2], st[v][3], QL[v], QR[v]);
     if (EQN == EULER) {
+        // face states that are not admissible fall back to the cell average
         const bool okl = eul_admissible(QL[0], QL[1], QL[2], QL[3], ph.gamma);
         const bool okr = eul_admissible(QR[0], QR[1], QR[2], QR[3], ph.gamma);
 #pragma unroll
-        for (int v = 0; v < NR; v++) {
+        for (int v = 0; v < NV; v++) {
             QL[v] = okl ? QL[v] : st[v][1];
             QR[v] = okr ? QR[v] : st[v][2];
         }
-    }
-    if (EQN == EULER) {
         EulS<T> L{QL[0], QL[NM], QL[TM], QL[3]}, R{QR[0], QR[NM], QR[TM], QR[3]};
-        T F[4];
-        eul_numflux<T, FLUX>(L, R, ph.gamma, F);
-        FlC[0] = F[0];
-        FlC[NM] = F[1];
-        FlC[TM] = F[2];
-        FlC[3] = F[3];
-        frn = F[1];
+        T G[4];
+        eul_numflux<T, FLUX>(L, R, ph.gamma, G);
+        F[0] = G[0];
+        F[NM] = G[1];
+        F[TM] = G[2];
+        F[3] = G[3];
         return;
     }
     T il = rcp(QL[0]), ir = rcp(QR[0]);  // face depths are positive here
-    if (!BATHY) {
-        SweV<T> L{QL[0], QL[NM] * il, QL[TM] * il}, R{QR[0], QR[NM] * ir, QR[TM] * ir};
-        T F[3];
-        swe_numflux<T, FLUX>(L, R, ph, F);
-        FlC[0] = F[0];
-        FlC[NM] = F[1];
-        FlC[TM] = F[2];
-        frn = F[1];
+    SweV<T> L{QL[0], QL[NM] * il, QL[TM] * il}, R{QR[0], QR[NM] * ir, QR[TM] * ir};
+    T G[3];
+    swe_numflux<T, FLUX>(L, R, ph, G);
+    F[0] = G[0];
+    F[NM] = G[1];
+    F[TM] = G[2];
+}
+
+// ------------------------------------------------ faces of the stage kernels
+// The stage kernels are bound by vector-ALU issue, so their faces use fewer
+// operations than the formulas above, and write every fused multiply-add out
+// (contraction off), so that a face has the same bits wherever it is
+// evaluated: in any tile shape, at a tile's edge or inside.
+//
+// HLLE is F_L + t (s_R dQ - (F_R - F_L)), t = s_L / (s_R - s_L).  With the mass
+// flux F_0 and b = t (s_R rho_R - m_R), every transported quantity a (a normal
+// or tangential velocity, the enthalpy) has the flux a_L F_0 + (a_R - a_L) b,
+// which is the same value rearranged.  Roe averages are a_L + k (a_R - a_L),
+// k = sqrt(rho_R) / (sqrt(rho_L) + sqrt(rho_R)).
+//
+// Shallow water carries the normal momentum flux relative to the pressure
+// g h^2 / 2 of each side's own face state, since a cell's two face states
+// along an axis are h -+ s/2: the pressures (and with a bed the hydrostatic
+// terms and the centred source) of the two faces sum to -g h s_eta, s_eta the
+// limited slope of the free surface, which the cell adds by itself.  No large
+// pressure is then formed and subtracted, and a face hands over three values.
+
+// MINMOD values of a cell at its low and high face, and its slope, from the
+// differences to its two neighbours along the axis.
+template <typename T, int RECON>
+__device__ __forceinline__ void cell_ends(T c, T dl, T dh, T &lo, T &hi, T &slope)
+{
+#pragma clang fp contract(off)
+    if (RECON == FIRST) {
+        lo = hi = c;
+        slope = T(0);
         return;
     }
-    // hydrostatic reconstruction: bed at the face = max of the two sides,
-    // depths re-evaluated against it, velocities kept
+    slope = minmod(dl, dh);
+    lo = tfma(T(-0.5), slope, c);
+    hi = tfma(T(0.5), slope, c);
+}
+
+// Difference of the two face values between cells whose averages differ by d
+// and whose slopes are sl and sr.
+template <typename T, int RECON> __device__ __forceinline__ T face_jump(T d, T sl, T sr)
+{
+    if (RECON == FIRST) return d;
+    return tfma(T(-0.5), sl + sr, d);
+}
+
+template <typename T> __device__ __forceinline__ T clamp0(T x, T hi) { return tmax(tmin(x, hi), T(0)); }
+template <> __device__ __forceinline__ float clamp0(float x, float hi) { return __builtin_amdgcn_fmed3f(x, 0.0f, hi); }
+
+// Shallow water: face values QL, QR (Cartesian order, the free surface last
+// with a bed) and the jump of the free surface across the face -> F (the flux
+// as the low cell sees it, normal momentum relative to its own pressure) and
+// nr (the normal momentum flux as the high cell sees it).  The jump is formed
+// from the cells' differences and slopes, which are exact or nearly so, and
+// carries none of the face values' rounding into the pressure.  With a bed
+// the depths are limited against the higher bed side (velocities kept):
+// h_L* = h_R - jump within [0, h_L], h_R* = h_L + jump within [0, h_R], and
+// h_R* - h_L* is the jump within [-h_L, h_R].
+template <typename T, bool BATHY, int FLUX, int AXIS>
+__device__ __forceinline__ void swe_face(const T *QL, const T *QR, T jump, const Phys<T> &ph, T *F, T &nr)
+{
+#pragma clang fp contract(off)
+    constexpr int NM = AXIS == 0 ? 1 : 2, TM = AXIS == 0 ? 2 : 1;
     T hl = QL[0], hr = QR[0];
-    T el = QL[NV], er = QR[NV];
-    T zf = tmax(el - hl, er - hr);
-    T hls = tmax(T(0), el - zf), hrs = tmax(T(0), er - zf);
-    SweV<T> L{hls, QL[NM] * il, QL[TM] * il}, R{hrs, QR[NM] * ir, QR[TM] * ir};
-    T F[3];
-    swe_numflux<T, FLUX>(L, R, ph, F);
-    const T hg = T(0.5) * ph.g;
-    FlC[0] = F[0];
-    FlC[NM] = F[1] + hg * (hl - hls) * (hl + hls);
-    FlC[TM] = F[2];
-    frn = F[1] + hg * (hr - hrs) * (hr + hrs);
-    sd[0] = hl;
-    sd[1] = el - hl;
-    sd[2] = hr;
-    sd[3] = er - hr;
+    const T il = rcp(hl), ir = rcp(hr);  // face depths are positive here
+    const T ul = QL[NM] * il, vl = QL[TM] * il, ur = QR[NM] * ir, vr = QR[TM] * ir;
+    T ml = QL[NM], mr = QR[NM];
+    T dh = jump;
+    if constexpr (BATHY) {
+        dh = tmax(tmin(jump, hr), -hl);
+        const T a = clamp0(hr - jump, hl), b = clamp0(hl + jump, hr);
+        hl = a;
+        hr = b;
+        ml = hl * ul;
+        mr = hr * ur;
+    }
+    const T du = ur - ul, dv = vr - vl, dm = BATHY ? tfma(hr, ur, -ml) : mr - ml;
+    const T gs = (T(0.5) * ph.g) * (hl + hr);
+    const T hp = gs * dh;  // pressure difference
+    const T wl = fsqrt(hl), wr = fsqrt(hr);
+    if constexpr (FLUX == RUSANOV) {
+        const T a = T(0.5) * tmax(tfma(ph.sqg, wl, tabs(ul)), tfma(ph.sqg, wr, tabs(ur)));
+        F[0] = tfma(-a, dh, T(0.5) * (ml + mr));
+        F[NM] = tfma(-a, dm, T(0.5) * (tfma(mr, ur, ml * ul) + hp));
+        F[TM] = tfma(-a, tfma(hr, vr, -(hl * vl)), T(0.5) * tfma(mr, vr, ml * vl));
+        nr = F[NM] - hp;
+        return;
+    }
+    const T ws = wl + wr;
+    const T k = wr * rcp(BATHY ? tmax(ws, tiny<T>()) : ws);
+    const T ua = tfma(k, du, ul), ca = fsqrt(gs);
+    if constexpr (FLUX == HLLE) {
+        // s_R is floored at a tiny power of two instead of 0: where both
+        // sides are dry the formula then returns F_L = 0
+        const T sL = tmin(tmin(tfma(-ph.sqg, wl, ul), ua - ca), T(0));
+        const T sR = tmax(tmax(tfma(ph.sqg, wr, ur), ua + ca), tiny<T>());
+        const T t = sL * rcp(sR - sL);
+        const T f0 = tfma(t, tfma(sR, dh, -dm), ml);
+        const T b = t * tfma(sR, hr, -mr);
+        F[0] = f0;
+        F[NM] = tfma(du, b, tfma(ul, f0, -(t * hp)));
+        F[TM] = tfma(dv, b, vl * f0);
+        nr = F[NM] - hp;
+        return;
+    }
+    // Roe: three waves u-c, u (shear), u+c
+    const T va = tfma(k, dv, vl);
+    const T i2c = rcp_pos(T(2) * ca);
+    const T a1 = tabs(ua - ca) * (tfma(ua + ca, dh, -dm) * i2c);
+    const T a3 = tabs(ua + ca) * (tfma(-(ua - ca), dh, dm) * i2c);
+    const T a2 = tabs(ua) * (tfma(hr, vr, -(hl * vl)) - va * dh);
+    F[0] = T(0.5) * ((ml + mr) - (a1 + a3));
+    F[NM] = T(0.5) * (tfma(mr, ur, ml * ul) + hp - tfma(a3, ua + ca, a1 * (ua - ca)));
+    F[TM] = T(0.5) * (tfma(mr, vr, ml * vl) - tfma(a1 + a3, va, a2));
+    nr = F[NM] - hp;
 }
 
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int AXIS>
-__device__ __forceinline__ void face_flux(const T (*st)[4], const Phys<T> &ph, T *FlC, T &frn)
+// Euler: face values QL, QR and the cell averages CL, CR that replace them
+// where they are not admissible -> F (Cartesian order).  The replacement is
+// rare: it runs only in waves that need it.
+template <typename T> __device__ __forceinline__ T eul_prim(const T *Q, int nm, int tm, T gm1, T &ir, T &u, T &v)
 {
-    T sd[4];
-    face_flux<T, EQN, BATHY, FLUX, RECON, AXIS>(st, ph, FlC, frn, sd);
+#pragma clang fp contract(off)
+    ir = rcp(Q[0]);
+    u = Q[nm] * ir;
+    v = Q[tm] * ir;
+    return gm1 * tfma(T(-0.5), tfma(Q[tm], v, Q[nm] * u), Q[3]);
 }
 
-// What one face hands to its two cells, for kernels that pass face results
-// between lanes: TL to the cell on the left (below), TR to the cell on the
-// right (above).  Entries 0..NV-1: the flux that cell sees (the two differ
-// only in the normal momentum, by the hydrostatic correction); with a bed,
-// entries NV and NV+1: depth and bed height of the face state on that side.
-template <typename T, int EQN, bool BATHY> struct FaceSide {
-    static constexpr int NV = EQN == SWE ? 3 : 4;
-    static constexpr int N = NV + (BATHY ? 2 : 0);
-};
-
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int AXIS>
-__device__ __forceinline__ void face_eval(const T (*st)[4], const Phys<T> &ph, T *TL, T *TR)
+template <typename T, int FLUX, int AXIS>
+__device__ __forceinline__ void eul_face(T *QL, T *QR, const T *CL, const T *CR, const Phys<T> &ph, T *F)
 {
-    constexpr int NV = FaceSide<T, EQN, BATHY>::NV;
-    constexpr int NM = AXIS == 0 ? 1 : 2;
-    T F[NV], frn, sd[4];
-    face_flux<T, EQN, BATHY, FLUX, RECON, AXIS>(st, ph, F, frn, sd);
+#pragma clang fp contract(off)
+    constexpr int NM = AXIS == 0 ? 1 : 2, TM = AXIS == 0 ? 2 : 1;
+    const T gm1 = ph.gamma - T(1);
+    T irl, ul, vl, irr, ur, vr;
+    T pl = eul_prim(QL, NM, TM, gm1, irl, ul, vl), pr = eul_prim(QR, NM, TM, gm1, irr, ur, vr);
+    const bool okl = QL[0] > T(0) && pl > T(0), okr = QR[0] > T(0) && pr > T(0);
+    if (__any(!(okl && okr))) {
 #pragma unroll
-    for (int v = 0; v < NV; v++) TL[v] = TR[v] = F[v];
-    TR[NM] = frn;
-    if (BATHY) {
-        TL[NV] = sd[0];
-        TL[NV + 1] = sd[1];
-        TR[NV] = sd[2];
-        TR[NV + 1] = sd[3];
+        for (int v = 0; v < 4; v++) {
+            QL[v] = okl ? QL[v] : CL[v];
+            QR[v] = okr ? QR[v] : CR[v];
+        }
+        pl = eul_prim(QL, NM, TM, gm1, irl, ul, vl);
+        pr = eul_prim(QR, NM, TM, gm1, irr, ur, vr);
+    }
+    if constexpr (FLUX != HLLE) {
+        const EulS<T> L{QL[0], QL[NM], QL[TM], QL[3]}, R{QR[0], QR[NM], QR[TM], QR[3]};
+        T G[4];
+        eul_numflux<T, FLUX>(L, R, ph.gamma, G);
+        F[0] = G[0];
+        F[NM] = G[1];
+        F[TM] = G[2];
+        F[3] = G[3];
+        return;
+    }
+    const T cl = fsqrt((ph.gamma * pl) * irl), cr = fsqrt((ph.gamma * pr) * irr);
+    const T Hl = (QL[3] + pl) * irl, Hr = (QR[3] + pr) * irr;
+    const T dr = QR[0] - QL[0], dm = QR[NM] - QL[NM], du = ur - ul, dv = vr - vl, dH = Hr - Hl, dp = pr - pl;
+    const T wl = fsqrt(QL[0]), wr = fsqrt(QR[0]);
+    const T k = wr * rcp(wl + wr);
+    const T ua = tfma(k, du, ul), va = tfma(k, dv, vl), Ha = tfma(k, dH, Hl);
+    const T ca = fsqrt(tmax(gm1 * tfma(T(-0.5), tfma(va, va, ua * ua), Ha), T(0)));
+    const T sL = tmin(tmin(ul - cl, ua - ca), T(0));
+    const T sR = tmax(tmax(ur + cr, ua + ca), T(0));
+    const T t = sL * rcp(sR - sL);  // sR - sL >= c~ > 0 for admissible states
+    const T f0 = tfma(t, tfma(sR, dr, -dm), QL[NM]);
+    const T b = t * tfma(sR, QR[0], -QR[NM]);
+    F[0] = f0;
+    F[NM] = tfma(du, b, tfma(ul, f0, tfma(-t, dp, pl)));
+    F[TM] = tfma(dv, b, vl * f0);
+    F[3] = tfma(-(t * sR), dp, tfma(dH, b, Hl * f0));
+}
+
+// The face between two cells from its two face values, for either system;
+// nr is the normal momentum flux as the high cell sees it (Euler: F's), jump
+// the free surface's (shallow water).
+template <typename T, int EQN, bool BATHY, int FLUX, int AXIS>
+__device__ __forceinline__ void stage_face(T *QL, T *QR, const T *CL, const T *CR, T jump, const Phys<T> &ph,
+                                           T *F, T &nr)
+{
+    if constexpr (EQN == EULER) {
+        eul_face<T, FLUX, AXIS>(QL, QR, CL, CR, ph, F);
+        nr = F[AXIS == 0 ? 1 : 2];
+    } else {
+        swe_face<T, BATHY, FLUX, AXIS>(QL, QR, jump, ph, F, nr);
     }
 }
 
-// Centred bed source of one cell along one axis (hydrostatic reconstruction),
-// times the cell width: -g (h_{i-1/2+} + h_{i+1/2-})/2 (z_{i+1/2-} - z_{i-1/2+}),
-// from the face state at the cell's low face (hL, zL) and at its high face
-// (hR, zR); it is added to the cell's flux difference along that axis.
-template <typename T> __device__ __forceinline__ T bed_term(T hL, T zL, T hR, T zR, T g)
+// The same from the four cells c[v][0..3] around it (the free surface as the
+// last variable with a bed); slope: the free surface's slope in cell 2.
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int AXIS>
+__device__ __forceinline__ void line_face(const T (*c)[4], const Phys<T> &ph, T *F, T &nr, T &slope)
 {
-    return -g * T(0.5) * (hL + hR) * (zR - zL);
+#pragma clang fp contract(off)
+    constexpr int NL = (EQN == SWE ? 3 : 4) + (BATHY ? 1 : 0);
+    T ql[NL], qr[NL], cl[NL], cr[NL], jump = T(0);
+#pragma unroll
+    for (int v = 0; v < NL; v++) {
+        const T d = c[v][2] - c[v][1];
+        T x, sl, sr;
+        cell_ends<T, RECON>(c[v][1], c[v][1] - c[v][0], d, x, ql[v], sl);
+        cell_ends<T, RECON>(c[v][2], d, c[v][3] - c[v][2], qr[v], x, sr);
+        cl[v] = c[v][1];
+        cr[v] = c[v][2];
+        if (v == (BATHY ? NL - 1 : 0)) {
+            slope = sr;
+            jump = face_jump<T, RECON>(d, sl, sr);
+        }
+    }
+    stage_face<T, EQN, BATHY, FLUX, AXIS>(ql, qr, cl, cr, jump, ph, F, nr);
 }
 
 }  // namespace fvk

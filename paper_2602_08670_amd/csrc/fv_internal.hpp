@@ -67,23 +67,48 @@ struct WorkItem {
     int tiles_x;     // tiles per row of the solve; tile = workgroup - tile_begin, row-major
     unsigned char ri, ro, rc, pad;
 };
-#ifndef FV_TILE_Y
-#define FV_TILE_Y 32
-#endif
-constexpr int TILE_X = 64, TILE_Y = FV_TILE_Y;  // FP32 tile of the stage kernels
-// One workgroup per tile: grid = the list's tiles.  one != 0 declares that
-// the list holds exactly one solve, solves[0].
-hipError_t launch_batch_stage(int eqn, int bathy, int stage, const BatchSolve *solves, const WorkItem *items,
-                              const int *nitems, int grid, hipStream_t st, int one = 0);
+// Tile shapes of the stage kernels: 64 columns (one wave64 per row) by
+// shape_rows rows, shape_rpw rows per wave.  A cell's arithmetic is the same
+// in each, to the bit.  A small grid is bound by each wave's serial chain (load,
+// barrier, faces, store) with most of the chip idle, so it takes the shape
+// with the most and shortest waves; a large one is bound by vector-ALU issue,
+// so it takes the one that shares the most work between a wave's rows (each
+// row's face values formed once, one exchange per wave) while small
+// workgroups keep loads and arithmetic of different tiles overlapping.
+// Microseconds per shallow-water-over-a-bed step, shapes 4 x 1 / 8 x 1 /
+// 16 x 2 / 16 x 4 (rows x rows per wave), and the 32 x 2 used before:
+//   64^2   8.0 /  8.5 / 10.0 / 11.6, 12.4     256^2  8.2 /  8.5 / 10.4 / 11.8, 13.0
+//   512^2 11.3 / 10.7 / 11.0 / 12.3, 13.5     768^2 16.8 / 16.5 / 17.0 / 17.8, 19.5
+//   1000 x 700 18.0 (8 x 1) / 17.3 / 18.2, 19.9   1024^2 23.1 / 22.2 / 20.4 / 21.4, 20.1
+//   2048^2 78.1 / 76.2 / 64.8 / 63.6, 69.5    4096^2  306 (8 x 1) / 269 / 265, 304
+// Euler's order is the same.  Double precision (4 x 1 / 16 x 2, and the 8 x 2
+// used before): 256^2 10.1 / 15.6, 12.3; 512^2 17.9 / 16.5, 17.1; 1024^2
+// 49.8 / 43.8, 45.4.
+constexpr int TILE_X = 64, NSHAPES = 4;
+constexpr int shape_rows(int shape) { return shape == 0 ? 4 : shape == 1 ? 8 : 16; }
+constexpr int shape_rpw(int shape) { return shape < 2 ? 1 : shape == 2 ? 2 : 4; }
+// The shape for a launch over `cells` cells in all.
+inline int stage_shape(int64_t cells, int prec = 0)
+{
+    if (prec == 1) return cells <= 150000 ? 0 : 2;
+    return cells <= 160000 ? 0 : cells <= 640000 ? 1 : cells <= 3000000 ? 2 : 3;
+}
+inline int64_t stage_tiles(int nx, int ny, int shape)
+{
+    return (int64_t)((nx + TILE_X - 1) / TILE_X) * ((ny + shape_rows(shape) - 1) / shape_rows(shape));
+}
+// One workgroup per tile: grid = the list's tiles of the given shape.
+hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
+                              const WorkItem *items, const int *nitems, int grid, hipStream_t st);
 // One solve, descriptor and list entry by value (it.tile_begin == 0): the
 // launches of a single solve.
-hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, const BatchSolve &d, const WorkItem &it, int grid,
-                                  hipStream_t st);
+hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
+                                  int grid, hipStream_t st);
 // The form recorded in graphs: wgs workgroups (a multiple of 8, set to
 // xcd_grid(tiles) before each replay), the tile count read from the list
 // header list = {items, tiles}.
-hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, const BatchSolve *solves, const WorkItem *items,
-                                   const int *list, int wgs, hipStream_t st);
+hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
+                                   const WorkItem *items, const int *list, int wgs, hipStream_t st);
 // Grid of a tiled launch: the tiles padded to a multiple of the 8 XCDs.
 __host__ __device__ inline int xcd_grid(int ntiles) { return (ntiles + 7) & ~7; }
 

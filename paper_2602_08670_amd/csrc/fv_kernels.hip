@@ -1,10 +1,12 @@
 // Finite-volume stage kernels for gfx950 (MI355X).
 //
-// One workgroup of TY/2 wave64 (two tile rows per wave) owns a TX x TY tile of cells.
+// One workgroup owns a tile of 64 columns (a wave64 per row) and 4, 8 or 16
+// rows, one to four rows per wave; the launch's size picks the shape.
 //  1. The tile plus a two-cell halo of every variable (and eta = h + b with a
-//     bed) is staged into LDS with coalesced row loads; ghost cells are
-//     synthesised during the load (periodic wrap or wall mirror with the
-//     normal momentum negated).
+//     bed) is staged into LDS, a wave loading whole rows, every load issued
+//     before the first store; ghost cells are synthesised during the load
+//     (periodic wrap or wall mirror with the normal momentum negated), the row
+//     mapped in scalar registers and the column once per lane.
 //  2. Every x face and y face of the tile is evaluated exactly once
 //     (reconstruction, hydrostatic step, numerical flux), by the lane of its
 //     high-side cell, and stays in registers: a cell's high x face comes from
@@ -29,11 +31,6 @@ __device__ __forceinline__ int map_index(int i, int n, int bc, bool &flip)
     int m = i < 0 ? -1 - i : 2 * n - 1 - i;
     return m < 0 ? 0 : (m >= n ? n - 1 : m);  // cells past the ghost layer are never used
 }
-
-template <typename T> struct Tile;
-template <> struct Tile<float> { static constexpr int X = TILE_X, Y = TILE_Y; };
-static_assert(TILE_X == 64, "a tile row is one wave64");
-template <> struct Tile<double> { static constexpr int X = 64, Y = 8; };
 
 template <typename T> struct StageArgs {
     const T *qs;
@@ -171,31 +168,22 @@ __device__ __forceinline__ double from_right(double v, double edge)
 
 // LDS of one stage tile: the halo tile of every variable (and eta), the
 // faces handed between waves, and the step's Delta t.
-template <typename T, int EQN, bool BATHY, int TX, int TY> struct StageLds {
-    static constexpr int RPW = 2;             // tile rows per wave
+template <typename T, int EQN, bool BATHY, int TX, int TY, int RPW_> struct StageLds {
+    static constexpr int RPW = RPW_;          // tile rows per wave
     static constexpr int NW = TY / RPW;       // waves per workgroup
     static constexpr int NTH = 64 * NW;       // threads per workgroup
-    static_assert(TY % RPW == 0 && NW >= 2 && NW <= 16, "whole rows per wave, 2..16 waves");
+    static_assert(TX == 64 && TY % RPW == 0 && NW >= 2 && NW <= 16, "a tile row is one wave64; whole rows, 2..16 waves");
     static constexpr int NV = EQN == SWE ? 3 : 4;
     static constexpr int NL = NV + (BATHY ? 1 : 0);  // LDS planes: variables (+ eta)
-    static constexpr int NT = FaceSide<T, EQN, BATHY>::N;
     static constexpr int HX = TX + 4, HY = TY + 4;
-    static constexpr int NIT = (HY * HX + NTH - 1) / NTH;  // halo elements per thread
-    // rows past HY pad each plane to NIT * NTH elements: the last pass of the
-    // halo staging then stores unconditionally (its extra lanes write padding),
-    // so every halo load is issued before the first store
-    static constexpr int HYP = (NIT * NTH + HX - 1) / HX;
-    T q[NL][HYP][HX];
-    T edge[NT][TY];         // right face of column TX-1, handed to that cell
-    T low[NW - 1][NT][TX];  // low y face of wave w+1's first row, handed to wave w
+    static constexpr int NIT = (HY + NW - 1) / NW;   // halo rows per wave
+    // the waves that stage the last four columns: those without a last row if they are enough
+    static constexpr int XT0 = 64 * (HY % NW) + 4 * HY <= NTH ? 64 * (HY % NW) : 0;
+    static_assert(4 * HY <= NTH, "one pass stages the last four columns");
+    T q[NL][HY][HX];
+    T edge[NV][TY];         // right face of column TX-1, handed to that cell
+    T low[NW - 1][NV][TX];  // low y face of wave w+1's first row, handed to wave w
     double dt;
-};
-
-// Halo values of one inner tile held in registers between the issue of their
-// loads and their store to LDS.
-template <typename T, int EQN, bool BATHY, int TX, int TY> struct HaloRegs {
-    using L = StageLds<T, EQN, BATHY, TX, TY>;
-    T val[L::NIT][L::NL];
 };
 
 // A tile whose two-cell halo lies inside the grid (all but the border tiles)
@@ -205,72 +193,102 @@ template <int TX, int TY> __device__ __forceinline__ bool inner_tile(int x0, int
     return x0 >= 2 && y0 >= 2 && x0 + TX + 2 <= nx && y0 + TY + 2 <= ny;
 }
 
-// Issue every halo load of an inner tile (no LDS access, no wait).  The last
-// pass re-reads the tile's first halo element on lanes past the end.
-template <typename T, int EQN, bool BATHY, int TX, int TY>
+// The grid index of ghost or inner index i (i >= -2), and whether it is a
+// wall's mirror image.  Indices past the ghost layer, in the last tile's
+// overhang, give some index of the grid; their cells are never used.
+__device__ __forceinline__ int ghost_index(int i, int n, int bc, bool &flip)
+{
+    flip = bc != 0 && (i < 0 || i >= n);
+    const int lo = bc == 0 ? i + n : -1 - i;
+    const int hi = bc == 0 ? min(i - n, n - 1) : max(2 * n - 1 - i, 0);
+    return i < 0 ? lo : (i >= n ? hi : i);
+}
+
+// The halo tile's values held in registers between the issue of their loads
+// and their store to LDS.
+template <typename T, int EQN, bool BATHY, int TX, int TY, int RPW> struct HaloRegs {
+    using L = StageLds<T, EQN, BATHY, TX, TY, RPW>;
+    T row[L::NIT][L::NL];  // halo row wave + it * NW, column lane
+    T tail[L::NL];         // one element of the last four columns
+};
+
+// Issue every load of the halo tile (no LDS access, no wait).  A wave loads
+// whole rows, so a row's address is scalar and its column offset is the same
+// in every pass; border tiles map the row (scalar) and the column (once per
+// lane) to the wrapped or mirrored cell, and cost no further pass.
+template <typename T, int EQN, bool BATHY, int TX, int TY, int RPW, bool BORDER>
 __device__ __forceinline__ void halo_issue(const StageArgs<T> &a, const int x0, const int y0, const int tid,
-                                           HaloRegs<T, EQN, BATHY, TX, TY> &r)
+                                           HaloRegs<T, EQN, BATHY, TX, TY, RPW> &r)
 {
-    using L = StageLds<T, EQN, BATHY, TX, TY>;
-    const int nx = a.nx;
-    const size_t plane = (size_t)nx * a.ny;
-    const size_t hb = (size_t)y0 * nx + x0 - 2 * (size_t)nx - 2;
-#pragma unroll
-    for (int it = 0; it < L::NIT; it++) {
-        const int e = tid + it * L::NTH;
-        const int ec = e < L::HY * L::HX ? e : 0;
-        const int ly = ec / L::HX, lx = ec - ly * L::HX;
-        const unsigned off = (unsigned)(ly * nx + lx);
-#pragma unroll
-        for (int v = 0; v < L::NV; v++) r.val[it][v] = ld_off(a.qs + v * plane + hb, off);
-        if constexpr (BATHY) r.val[it][L::NV] = ld_off(a.bed + hb, off);
-    }
-}
-
-template <typename T, int EQN, bool BATHY, int TX, int TY>
-__device__ __forceinline__ void halo_commit(const HaloRegs<T, EQN, BATHY, TX, TY> &r,
-                                            StageLds<T, EQN, BATHY, TX, TY> &sh, const int tid)
-{
-    using L = StageLds<T, EQN, BATHY, TX, TY>;
-#pragma unroll
-    for (int it = 0; it < L::NIT; it++) {
-        const int e = tid + it * L::NTH;
-        const int ly = e / L::HX, lx = e - ly * L::HX;
-#pragma unroll
-        for (int v = 0; v < L::NV; v++) sh.q[v][ly][lx] = r.val[it][v];
-        if constexpr (BATHY) sh.q[L::NV][ly][lx] = r.val[it][0] + r.val[it][L::NV];
-    }
-}
-
-// Border tiles: ghost cells synthesised during the load (periodic wrap or
-// wall mirror with the normal momentum negated).
-template <typename T, int EQN, bool BATHY, int TX, int TY>
-__device__ __forceinline__ void halo_border(const StageArgs<T> &a, const int x0, const int y0, const int tid,
-                                            StageLds<T, EQN, BATHY, TX, TY> &sh)
-{
-    using L = StageLds<T, EQN, BATHY, TX, TY>;
+    using L = StageLds<T, EQN, BATHY, TX, TY, RPW>;
     const int nx = a.nx, ny = a.ny;
     const size_t plane = (size_t)nx * ny;
-    for (int k = tid; k < L::HY * L::HX; k += L::NTH) {
-        int ly = k / L::HX, lx = k - ly * L::HX;
-        bool fx = false, fy = false;
-        int ix = map_index(x0 - 2 + lx, nx, a.bc_x, fx);
-        int iy = map_index(y0 - 2 + ly, ny, a.bc_y, fy);
-        size_t idx = (size_t)iy * nx + ix;
-        T val[L::NV];
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    bool fx = false, fy = false;
+    const unsigned col = BORDER ? (unsigned)ghost_index(x0 - 2 + lane, nx, a.bc_x, fx) : (unsigned)lane;
 #pragma unroll
-        for (int v = 0; v < L::NV; v++) val[v] = gload(a.qs)[v * plane + idx];
-        const T b = BATHY ? gload(a.bed)[idx] : T(0);
+    for (int it = 0; it < L::NIT; it++) {
+        const int ly = wave + it * L::NW;
+        if (L::HY % L::NW != 0 && it == L::NIT - 1 && ly >= L::HY) break;
+        const int gy = y0 - 2 + ly;
+        const size_t base = BORDER ? (size_t)ghost_index(gy, ny, a.bc_y, fy) * nx : (size_t)gy * nx + (x0 - 2);
 #pragma unroll
-        for (int v = 0; v < L::NV; v++) sh.q[v][ly][lx] = ((v == 1 && fx) || (v == 2 && fy)) ? -val[v] : val[v];
-        if constexpr (BATHY) sh.q[L::NV][ly][lx] = val[0] + b;
+        for (int v = 0; v < L::NV; v++) r.row[it][v] = ld_off(a.qs + v * plane + base, col);
+        if constexpr (BATHY) r.row[it][L::NV] = ld_off(a.bed + base, col);
+        if (BORDER) {
+            r.row[it][1] = fx ? -r.row[it][1] : r.row[it][1];
+            r.row[it][2] = fy ? -r.row[it][2] : r.row[it][2];
+        }
+    }
+    const int te = tid - L::XT0;
+    if (te >= 0 && te < 4 * L::HY) {
+        const int ly = te >> 2, gx = x0 + TX - 2 + (te & 3);
+        if (BORDER) {
+            const size_t idx = (size_t)ghost_index(y0 - 2 + ly, ny, a.bc_y, fy) * nx + ghost_index(gx, nx, a.bc_x, fx);
+#pragma unroll
+            for (int v = 0; v < L::NV; v++) r.tail[v] = gload(a.qs)[v * plane + idx];
+            if constexpr (BATHY) r.tail[L::NV] = gload(a.bed)[idx];
+        } else {
+            const size_t base = (size_t)(y0 - 2) * nx;
+            const unsigned off = (unsigned)(ly * nx + gx);
+#pragma unroll
+            for (int v = 0; v < L::NV; v++) r.tail[v] = ld_off(a.qs + v * plane + base, off);
+            if constexpr (BATHY) r.tail[L::NV] = ld_off(a.bed + base, off);
+        }
+        if (BORDER) {
+            r.tail[1] = fx ? -r.tail[1] : r.tail[1];
+            r.tail[2] = fy ? -r.tail[2] : r.tail[2];
+        }
+    }
+}
+
+template <typename T, int EQN, bool BATHY, int TX, int TY, int RPW>
+__device__ __forceinline__ void halo_commit(const HaloRegs<T, EQN, BATHY, TX, TY, RPW> &r,
+                                            StageLds<T, EQN, BATHY, TX, TY, RPW> &sh, const int tid)
+{
+    using L = StageLds<T, EQN, BATHY, TX, TY, RPW>;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+    for (int it = 0; it < L::NIT; it++) {
+        const int ly = wave + it * L::NW;
+        if (L::HY % L::NW != 0 && it == L::NIT - 1 && ly >= L::HY) break;
+#pragma unroll
+        for (int v = 0; v < L::NV; v++) sh.q[v][ly][lane] = r.row[it][v];
+        if constexpr (BATHY) sh.q[L::NV][ly][lane] = r.row[it][0] + r.row[it][L::NV];
+    }
+    const int te = tid - L::XT0;
+    if (te >= 0 && te < 4 * L::HY) {
+#pragma unroll
+        for (int v = 0; v < L::NV; v++) sh.q[v][te >> 2][TX + (te & 3)] = r.tail[v];
+        if constexpr (BATHY) sh.q[L::NV][te >> 2][TX + (te & 3)] = r.tail[0] + r.tail[L::NV];
     }
 }
 
 // Delta t of the step = CFL / (max over the previous step's rate sub-slots),
 // read by wave 1 into LDS.
-template <typename T, int EQN, bool BATHY, int TX, int TY>
-__device__ __forceinline__ void stage_dt(const StageArgs<T> &a, const int tid, StageLds<T, EQN, BATHY, TX, TY> &sh)
+template <typename T, int EQN, bool BATHY, int TX, int TY, int RPW>
+__device__ __forceinline__ void stage_dt(const StageArgs<T> &a, const int tid,
+                                         StageLds<T, EQN, BATHY, TX, TY, RPW> &sh)
 {
     if ((tid >> 6) == 1) {
         const int lane = tid & 63;
@@ -285,25 +303,28 @@ __device__ __forceinline__ void stage_dt(const StageArgs<T> &a, const int tid, S
 // the solve.  Shared by every stage kernel, so a solve computes bit-identical
 // results in all of them.
 //
-// Work split: lane = column, wave w owns tile rows [2w, 2w+1].  Each
-// lane evaluates the low x face and the low y face of each of its cells, so
+// Work split: lane = column, wave w owns tile rows RPW w .. RPW w + RPW - 1.
+// Each lane evaluates the low x face and the low y face of each of its cells, so
 // face results stay in registers: the high x face arrives from lane + 1 by a
 // DPP shift, the high y face from the same lane's next row.  Faces with no
 // owner inside the wave are the tile's right column (one lane per row, wave
 // 0, through LDS), the tile's top row (last wave) and the low face of each
 // wave's first row, which the wave below reads through LDS.
-// tid: threadIdx.x (a workgroup looping over tiles passes it opaquely, so
-// that per-lane index arithmetic is redone per tile instead of being held in
-// registers across the loop).
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY>
+// Bound by vector-ALU issue where the chip is full: 228 lane instructions per
+// cell and stage of shallow water over a bed (270 before the faces shared
+// their reconstruction and the flux was rearranged), 1024^2 21.3 -> 20.4 us a
+// step, 2048^2 76.2 -> 63.6, Euler 1000 x 700 26.6 -> 19.9; by latency on
+// small grids (64^2 13.0 -> 8.0).
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY, int RPW>
 __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x0, const int y0,
                                               const int tile_linear, const int tid,
-                                              StageLds<T, EQN, BATHY, TX, TY> &sh)
+                                              StageLds<T, EQN, BATHY, TX, TY, RPW> &sh)
 {
-    static_assert(TX == 64, "a tile row is one wave64");
-    using LD = StageLds<T, EQN, BATHY, TX, TY>;
-    constexpr int NW = LD::NW, RPW = LD::RPW;
-    constexpr int NV = LD::NV, NL = LD::NL, NT = LD::NT;
+#pragma clang fp contract(off)
+    using LD = StageLds<T, EQN, BATHY, TX, TY, RPW>;
+    constexpr int NW = LD::NW;
+    constexpr int NV = LD::NV, NL = LD::NL;
+    constexpr int ES = BATHY ? NL - 1 : 0;  // plane of the free surface (flat bottom: the depth)
     auto &s_q = sh.q;
     auto &s_edge = sh.edge;
     auto &s_low = sh.low;
@@ -320,86 +341,82 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
     // stage weight times Delta t over the cell width, per axis
     const T cxs = a.a1 * dt * a.rdx, cys = a.a1 * dt * a.rdy;
 
-    // 2. faces with no owner lane: the tile's right column and top row
+    // 2. faces with no owner lane: the tile's right column
     if (wave == 0 && lane < TY) {
-        T st[NL][4];
+        T c[NL][4], F[NV], nr, slope;
 #pragma unroll
         for (int v = 0; v < NL; v++)
 #pragma unroll
-            for (int k = 0; k < 4; k++) st[v][k] = s_q[v][lane + 2][TX + k];
-        T tl[NT], tr[NT];
-        face_eval<T, EQN, BATHY, FLUX, RECON, 0>(st, a.ph, tl, tr);
+            for (int k = 0; k < 4; k++) c[v][k] = s_q[v][lane + 2][TX + k];
+        line_face<T, EQN, BATHY, FLUX, RECON, 0>(c, a.ph, F, nr, slope);
 #pragma unroll
-        for (int k = 0; k < NT; k++) s_edge[k][lane] = tl[k];
-    }
-    T top[NT];  // low-side values of the y face above this wave's last row
-    if (wave == NW - 1) {
-        T st[NL][4];
-#pragma unroll
-        for (int v = 0; v < NL; v++)
-#pragma unroll
-            for (int k = 0; k < 4; k++) st[v][k] = s_q[v][TY + k][lane + 2];
-        T tr[NT];
-        face_eval<T, EQN, BATHY, FLUX, RECON, 1>(st, a.ph, top, tr);
+        for (int k = 0; k < NV; k++) s_edge[k][lane] = F[k];
     }
 
-    // 3. y faces: the low face of every own row, evaluated from the last row
-    //    down so that each row's y divergence can be formed at once
-    T Ly[RPW][NV];
-    T lowR[NT];  // high-side values of the low face of the wave's first row
+    // 3. y faces, from the wave's last row down: a cell's two face values are
+    //    formed once, its low value kept for the face below it.  The last
+    //    wave starts with the face above the tile.
+    T Ly[RPW][NV];  // y flux difference; without the face above in the last row until the exchange
+    {
+        T qa[NL], qi[NL], d[NL];  // the row above, row i and their difference
+        T lo[NL], sa[NL];         // low value and slope of the row above
+        T top[NV];                // the face above the row above, seen from below
 #pragma unroll
-    for (int j = RPW - 1; j >= 0; j--) {
-        const int cy = r0 + j;
-        T st[NL][4];
+        for (int v = 0; v < NL; v++) {
+            qa[v] = s_q[v][r0 + RPW + 2][lane + 2];
+            qi[v] = s_q[v][r0 + RPW + 1][lane + 2];
+            d[v] = qa[v] - qi[v];
+        }
+        if (wave == NW - 1) {
 #pragma unroll
-        for (int v = 0; v < NL; v++)
-#pragma unroll
-            for (int k = 0; k < 4; k++) st[v][k] = s_q[v][cy + k][lane + 2];
-        T tl[NT], tr[NT];
-        face_eval<T, EQN, BATHY, FLUX, RECON, 1>(st, a.ph, tl, tr);
-        if (j == RPW - 1) {
-            if (wave == NW - 1) {
-#pragma unroll
-                for (int v = 0; v < NV; v++) Ly[j][v] = tr[v] - top[v];
-                if constexpr (BATHY) Ly[j][2] += bed_term(tr[NV], tr[NV + 1], top[NV], top[NV + 1], a.ph.g);
-            } else {
-#pragma unroll
-                for (int k = 0; k < NT; k++) lowR[k] = tr[k];  // finished after the exchange
+            for (int v = 0; v < NL; v++) {
+                T x;
+                cell_ends<T, RECON>(qa[v], d[v], s_q[v][TY + 3][lane + 2] - qa[v], lo[v], x, sa[v]);
             }
-        } else {
-#pragma unroll
-            for (int v = 0; v < NV; v++) Ly[j][v] = tr[v] - top[v];
-            if constexpr (BATHY) Ly[j][2] += bed_term(tr[NV], tr[NV + 1], top[NV], top[NV + 1], a.ph.g);
-        }
-        if (j == 0 && wave > 0) {
-#pragma unroll
-            for (int k = 0; k < NT; k++) s_low[wave - 1][k][lane] = tl[k];
         }
 #pragma unroll
-        for (int k = 0; k < NT; k++) top[k] = tl[k];
+        for (int i = RPW - 1; i >= -1; i--) {
+            T qb[NL], db[NL], nlo[NL], hi[NL], s[NL];
+#pragma unroll
+            for (int v = 0; v < NL; v++) {
+                qb[v] = s_q[v][r0 + i + 1][lane + 2];
+                db[v] = qi[v] - qb[v];
+                cell_ends<T, RECON>(qi[v], db[v], d[v], nlo[v], hi[v], s[v]);
+            }
+            if (i < RPW - 1 || wave == NW - 1) {
+                T F[NV], nr;
+                stage_face<T, EQN, BATHY, FLUX, 1>(hi, lo, qi, qa, face_jump<T, RECON>(d[ES], s[ES], sa[ES]), a.ph, F, nr);
+                if (i < RPW - 1) {
+                    // the face is the low face of row i + 1
+                    T hs[NV];
+#pragma unroll
+                    for (int v = 0; v < NV; v++) hs[v] = v == 2 ? nr : F[v];
+                    if constexpr (EQN == SWE) hs[2] = tfma(-(a.ph.g * qa[0]), sa[ES], hs[2]);
+#pragma unroll
+                    for (int v = 0; v < NV; v++)
+                        Ly[i + 1][v] = i + 1 < RPW - 1 || wave == NW - 1 ? hs[v] - top[v] : hs[v];
+                    if (i == -1 && wave > 0) {
+#pragma unroll
+                        for (int k = 0; k < NV; k++) s_low[wave - 1][k][lane] = F[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < NV; k++) top[k] = F[k];
+            }
+#pragma unroll
+            for (int v = 0; v < NL; v++) {
+                qa[v] = qi[v];
+                qi[v] = qb[v];
+                d[v] = db[v];
+                lo[v] = nlo[v];
+                sa[v] = s[v];
+            }
+        }
     }
     __syncthreads();
     if (wave < NW - 1) {
-        T up[NT];
 #pragma unroll
-        for (int k = 0; k < NT; k++) up[k] = s_low[wave][k][lane];
-#pragma unroll
-        for (int v = 0; v < NV; v++) Ly[RPW - 1][v] = lowR[v] - up[v];
-        if constexpr (BATHY) Ly[RPW - 1][2] += bed_term(lowR[NV], lowR[NV + 1], up[NV], up[NV + 1], a.ph.g);
-    }
-
-    // q0 is needed only in the final combine: issued here, its latency hides
-    // behind the x faces, and it holds no registers during the y faces
-    T q0r[RPW][NV];
-    if (a.a0 != T(0)) {
-#pragma unroll
-        for (int j = 0; j < RPW; j++) {
-            const int cy = r0 + j;
-            const bool in = x0 + lane < nx && y0 + cy < ny;
-            const unsigned off = in ? (unsigned)(cy * nx + lane) : 0u;
-#pragma unroll
-            for (int v = 0; v < NV; v++) q0r[j][v] = ld_off(a.q0 + v * plane + tbase, off);
-        }
+        for (int v = 0; v < NV; v++) Ly[RPW - 1][v] -= s_low[wave][v][lane];
     }
 
     // 4. x faces, divergence, bed source, RK combine
@@ -408,19 +425,27 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
 #pragma unroll
     for (int j = 0; j < RPW; j++) {
         const int cy = r0 + j;
-        T st[NL][4];
+        T c[NL][4], F[NV], nr, slope, Lv[NV];
+        // q0 is needed only in the combine: its latency hides behind the x face
+        T q0r[NV];
+        if (a.a0 != T(0)) {
+            const bool in = x0 + lane < nx && y0 + cy < ny;
+            const unsigned off = in ? (unsigned)(cy * nx + lane) : 0u;
+#pragma unroll
+            for (int v = 0; v < NV; v++) q0r[v] = ld_off(a.q0 + v * plane + tbase, off);
+        }
 #pragma unroll
         for (int v = 0; v < NL; v++)
 #pragma unroll
-            for (int k = 0; k < 4; k++) st[v][k] = s_q[v][cy + 2][lane + k];
-        T tl[NT], tr[NT], rt[NT];
-        face_eval<T, EQN, BATHY, FLUX, RECON, 0>(st, a.ph, tl, tr);
+            for (int k = 0; k < 4; k++) c[v][k] = s_q[v][cy + 2][lane + k];
+        line_face<T, EQN, BATHY, FLUX, RECON, 0>(c, a.ph, F, nr, slope);
 #pragma unroll
-        for (int k = 0; k < NT; k++) rt[k] = from_right(tl[k], s_edge[k][cy]);
-        T Lv[NV];
-#pragma unroll
-        for (int v = 0; v < NV; v++) Lv[v] = tr[v] - rt[v];
-        if constexpr (BATHY) Lv[1] += bed_term(tr[NV], tr[NV + 1], rt[NV], rt[NV + 1], a.ph.g);
+        for (int v = 0; v < NV; v++) {
+            const T rt = from_right(F[v], s_edge[v][cy]);
+            T tr = v == 1 ? nr : F[v];
+            if (EQN == SWE && v == 1) tr = tfma(-(a.ph.g * c[0][2]), slope, tr);
+            Lv[v] = tr - rt;
+        }
         const bool in = x0 + lane < nx && y0 + cy < ny && !frozen;
         if (in) {
             const unsigned off = (unsigned)(cy * nx + lane);
@@ -430,9 +455,9 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
                 // out = a0 q0 + a1 (q + dt L), L = (x flux difference) / dx + (y flux difference) / dy;
                 // the increment is summed first, so the result is rounded
                 // twice at its own magnitude (once per added state)
-                const T inc = cxs * Lv[v] + cys * Ly[j][v];
-                T o = a.a1 * st[v][2] + inc;
-                if (a.a0 != T(0)) o = a.a0 * q0r[j][v] + o;
+                const T inc = tfma(cys, Ly[j][v], cxs * Lv[v]);
+                T o = tfma(a.a1, c[v][2], inc);
+                if (a.a0 != T(0)) o = tfma(a.a0, q0r[v], o);
                 __builtin_nontemporal_store(o, st_off(a.out + v * plane + tbase, off));
                 qn[v] = o;
             }
@@ -460,24 +485,22 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
 }
 
 // One RK stage on one tile, loaded and computed by the calling workgroup.
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY>
+// Every halo load is issued before the first LDS store and before the Delta t
+// read, whose reduction would otherwise hold them back.
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY, int RPW>
 __device__ __forceinline__ void stage_tile(const StageArgs<T> &a, const int x0, const int y0, const int tile_linear,
                                            const int tid)
 {
-    __shared__ StageLds<T, EQN, BATHY, TX, TY> sh;
-    if (inner_tile<TX, TY>(x0, y0, a.nx, a.ny)) {
-        // every halo load is issued before the first LDS store and before
-        // the Delta t read, whose reduction would otherwise hold them back
-        HaloRegs<T, EQN, BATHY, TX, TY> r;
-        halo_issue(a, x0, y0, tid, r);
+    __shared__ StageLds<T, EQN, BATHY, TX, TY, RPW> sh;
+    {
+        HaloRegs<T, EQN, BATHY, TX, TY, RPW> r;
+        if (inner_tile<TX, TY>(x0, y0, a.nx, a.ny)) halo_issue<T, EQN, BATHY, TX, TY, RPW, false>(a, x0, y0, tid, r);
+        else halo_issue<T, EQN, BATHY, TX, TY, RPW, true>(a, x0, y0, tid, r);
         stage_dt(a, tid, sh);
         halo_commit(r, sh, tid);
-    } else {
-        stage_dt(a, tid, sh);
-        halo_border(a, x0, y0, tid, sh);
     }
     __syncthreads();
-    stage_compute<T, EQN, BATHY, FLUX, RECON, TX, TY>(a, x0, y0, tile_linear, tid, sh);
+    stage_compute<T, EQN, BATHY, FLUX, RECON, TX, TY, RPW>(a, x0, y0, tile_linear, tid, sh);
 }
 
 // Workgroups are handed to the eight XCDs in turn (workgroup w runs on XCD
@@ -489,14 +512,19 @@ __device__ __forceinline__ int xcd_tile(int w, int grid)
     return (grid & 7) ? w : (w & 7) * (grid >> 3) + (w >> 3);
 }
 
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY>
-__global__ __launch_bounds__((StageLds<T, EQN, BATHY, TX, TY>::NTH)) void stage_kernel(StageArgs<T> a, int tiles_x,
-                                                                                   int ntiles)
+// LDS of a tile of the given shape.
+template <typename T, int EQN, bool BATHY, int SHAPE>
+using ShapeLds = StageLds<T, EQN, BATHY, TILE_X, shape_rows(SHAPE), shape_rpw(SHAPE)>;
+
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int SHAPE>
+__global__ __launch_bounds__((ShapeLds<T, EQN, BATHY, SHAPE>::NTH)) void stage_kernel(StageArgs<T> a, int tiles_x,
+                                                                                 int ntiles)
 {
+    constexpr int TX = TILE_X, TY = shape_rows(SHAPE);
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
     const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    stage_tile<T, EQN, BATHY, FLUX, RECON, TX, TY>(a, tx * TX, ty * TY, tile, threadIdx.x);
+    stage_tile<T, EQN, BATHY, FLUX, RECON, TX, TY, shape_rpw(SHAPE)>(a, tx * TX, ty * TY, tile, threadIdx.x);
 }
 
 // Batched stage over many solves: the step's list holds one item per solve
@@ -507,41 +535,29 @@ struct TileRef {
     int x0, y0, tile;
 };
 
-template <typename T, int STAGE>
+template <typename T, int STAGE, int SHAPE>
 __device__ __forceinline__ TileRef batch_fill(const BatchSolve &d, const WorkItem &it, const int w, StageArgs<T> &a);
 
-template <typename T, int STAGE>
+template <typename T, int STAGE, int SHAPE>
 __device__ __forceinline__ TileRef batch_resolve(const BatchSolve *__restrict__ solves,
                                                  const WorkItem *__restrict__ items, const int *__restrict__ nitems,
-                                                 const int w, const int one, StageArgs<T> &a)
+                                                 const int w, StageArgs<T> &a)
 {
-    // one != 0: the list is known to hold one solve, solves[0] (a single
-    // solve stepping through this kernel); its descriptor and list entry are
-    // then fetched together instead of one after the other
-    WorkItem it;
-    const BatchSolve *dp;
-    if (one) {
-        it = items[0];
-        dp = solves;
-    } else {
-        const int n = *nitems;
-        int lo = 0, hi = n - 1;
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (items[mid].tile_begin <= w) lo = mid;
-            else hi = mid - 1;
-        }
-        it = items[lo];
-        dp = solves + it.solve;
+    int lo = 0, hi = *nitems - 1;
+    while (lo < hi) {
+        int mid = (lo + hi + 1) >> 1;
+        if (items[mid].tile_begin <= w) lo = mid;
+        else hi = mid - 1;
     }
-    return batch_fill<T, STAGE>(*dp, it, w, a);
+    const WorkItem it = items[lo];
+    return batch_fill<T, STAGE, SHAPE>(solves[it.solve], it, w, a);
 }
 
 // The stage arguments of workgroup w, whose solve is d with list entry it.
-template <typename T, int STAGE>
+template <typename T, int STAGE, int SHAPE>
 __device__ __forceinline__ TileRef batch_fill(const BatchSolve &d, const WorkItem &it, const int w, StageArgs<T> &a)
 {
-    constexpr int TX = Tile<T>::X, TY = Tile<T>::Y;
+    constexpr int TX = TILE_X, TY = shape_rows(SHAPE);
     const int tile = w - it.tile_begin;
     a.qs = (const T *)(STAGE == 1 ? d.q : d.s1);
     a.q0 = (const T *)d.q;
@@ -575,34 +591,37 @@ __device__ __forceinline__ TileRef batch_fill(const BatchSolve &d, const WorkIte
 // ntiles == 0: the tile count is read from the list header (nitems[1]), so
 // that a launch recorded in a graph serves whatever list is uploaded before
 // each replay.  The grid is xcd_grid(tiles).  Eight waves per SIMD (at most
-// 64 VGPRs): every tile of a 1024^2 grid is then resident at once.
-template <typename T, int EQN, bool BATHY, int STAGE>
-__global__ __launch_bounds__((StageLds<T, EQN, BATHY, Tile<T>::X, Tile<T>::Y>::NTH), 8) void batch_stage_kernel(
+// 64 VGPRs); the shape with four rows per wave holds more values per lane and
+// runs five.
+constexpr int shape_waves(int shape) { return shape == 3 ? 5 : 8; }
+
+template <typename T, int EQN, bool BATHY, int STAGE, int SHAPE>
+__global__ __launch_bounds__((ShapeLds<T, EQN, BATHY, SHAPE>::NTH), shape_waves(SHAPE)) void batch_stage_kernel(
     const BatchSolve *__restrict__ solves, const WorkItem *__restrict__ items, const int *__restrict__ nitems,
-    int ntiles, int one)
+    int ntiles)
 {
-    constexpr int TX = Tile<T>::X, TY = Tile<T>::Y;
     const int total = ntiles > 0 ? ntiles : nitems[1];
     const int w = xcd_tile(blockIdx.x, gridDim.x);
     if (w >= total) return;
     StageArgs<T> a;
-    const TileRef t = batch_resolve<T, STAGE>(solves, items, nitems, w, one, a);
-    stage_tile<T, EQN, BATHY, HLLE, MINMOD, TX, TY>(a, t.x0, t.y0, t.tile, threadIdx.x);
+    const TileRef t = batch_resolve<T, STAGE, SHAPE>(solves, items, nitems, w, a);
+    stage_tile<T, EQN, BATHY, HLLE, MINMOD, TILE_X, shape_rows(SHAPE), shape_rpw(SHAPE)>(a, t.x0, t.y0, t.tile,
+                                                                                        threadIdx.x);
 }
 
 // One solve, its descriptor and list entry passed by value: the halo loads
 // wait for nothing but the arguments.  The same stage arguments, hence the
 // same results, as the list form.
-template <typename T, int EQN, bool BATHY, int STAGE>
-__global__ __launch_bounds__((StageLds<T, EQN, BATHY, Tile<T>::X, Tile<T>::Y>::NTH), 8) void batch_stage_one_kernel(
+template <typename T, int EQN, bool BATHY, int STAGE, int SHAPE>
+__global__ __launch_bounds__((ShapeLds<T, EQN, BATHY, SHAPE>::NTH), shape_waves(SHAPE)) void batch_stage_one_kernel(
     BatchSolve d, WorkItem it, int ntiles)
 {
-    constexpr int TX = Tile<T>::X, TY = Tile<T>::Y;
     const int w = xcd_tile(blockIdx.x, gridDim.x);
     if (w >= ntiles) return;
     StageArgs<T> a;
-    const TileRef t = batch_fill<T, STAGE>(d, it, w, a);
-    stage_tile<T, EQN, BATHY, HLLE, MINMOD, TX, TY>(a, t.x0, t.y0, t.tile, threadIdx.x);
+    const TileRef t = batch_fill<T, STAGE, SHAPE>(d, it, w, a);
+    stage_tile<T, EQN, BATHY, HLLE, MINMOD, TILE_X, shape_rows(SHAPE), shape_rpw(SHAPE)>(a, t.x0, t.y0, t.tile,
+                                                                                        threadIdx.x);
 }
 
 // ------------------------------------------------------------ CFL rate of q
@@ -745,12 +764,12 @@ __global__ void face_kernel(const T *q, int nx, int ny, int bc_x, int bc_y, Phys
             st[v][k] = val;
         }
     }
-    T Fl[NV], frn;
+    T Fl[NV];
     if (axis == 0) {
-        face_flux<T, EQN, false, FLUX, RECON, 0>(st, ph, Fl, frn);
+        face_flux<T, EQN, FLUX, RECON, 0>(st, ph, Fl);
         for (int v = 0; v < NV; v++) fx[(size_t)v * nfx + (size_t)j * (nx + 1) + i + 1] = Fl[v];
     } else {
-        face_flux<T, EQN, false, FLUX, RECON, 1>(st, ph, Fl, frn);
+        face_flux<T, EQN, FLUX, RECON, 1>(st, ph, Fl);
         for (int v = 0; v < NV; v++) fy[(size_t)v * nfy + (size_t)(j + 1) * nx + i] = Fl[v];
     }
 }
@@ -787,11 +806,23 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
     a.rate_out = ro;
     a.rate_clear = rc;
     a.last = last;
-    constexpr int TX = Tile<T>::X, TY = Tile<T>::Y;
-    const int tiles_x = (d.nx + TX - 1) / TX, ntiles = tiles_x * ((d.ny + TY - 1) / TY);
-    constexpr int NTH = StageLds<T, EQN, BATHY, TX, TY>::NTH;
-    hipLaunchKernelGGL((stage_kernel<T, EQN, BATHY, FLUX, RECON, TX, TY>), dim3(xcd_grid(ntiles)), dim3(NTH), 0, st, a,
-                       tiles_x, ntiles);
+    // the shapes with one and with two rows per wave serve every scheme, the
+    // other two FP32 HLLE with MINMOD (the scheme of long runs)
+    constexpr bool ALL = sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD;
+    int shape = stage_shape((int64_t)d.nx * d.ny, d.prec);
+    if (!ALL) shape = shape < 2 ? 0 : 2;
+    const int tiles_x = (d.nx + TILE_X - 1) / TILE_X, ntiles = (int)stage_tiles(d.nx, d.ny, shape);
+    const dim3 grid(xcd_grid(ntiles));
+#define FV_GO(S)                                                                                       \
+    hipLaunchKernelGGL((stage_kernel<T, EQN, BATHY, FLUX, RECON, S>), grid,                            \
+                       dim3(ShapeLds<T, EQN, BATHY, S>::NTH), 0, st, a, tiles_x, ntiles)
+    if (shape == 0) FV_GO(0);
+    else if (shape == 2) FV_GO(2);
+    if constexpr (ALL) {
+        if (shape == 1) FV_GO(1);
+        else if (shape == 3) FV_GO(3);
+    }
+#undef FV_GO
     return hipGetLastError();
 }
 
@@ -853,66 +884,73 @@ static hipError_t rate_t(const StageDesc &d, const void *q, Ctl *ctl, unsigned l
     return hipGetLastError();
 }
 
-template <int STAGE>
-static void batch_stage_go(int eqn, int bathy, dim3 g, const BatchSolve *solves, const WorkItem *items,
-                           const int *nitems, int ntiles, int one, hipStream_t st)
+// The kernel of a batched launch: form 0 the list's, 1 a single solve's.
+template <int EQN, bool BATHY, int STAGE, int SHAPE>
+static void batch_kernel_s(const void *fn[2], int *threads)
 {
-    constexpr int TX = Tile<float>::X, TY = Tile<float>::Y;
-    if (eqn == EULER)
-        hipLaunchKernelGGL((batch_stage_kernel<float, EULER, false, STAGE>), g,
-                           dim3(StageLds<float, EULER, false, TX, TY>::NTH), 0, st, solves, items, nitems, ntiles, one);
-    else if (bathy)
-        hipLaunchKernelGGL((batch_stage_kernel<float, SWE, true, STAGE>), g,
-                           dim3(StageLds<float, SWE, true, TX, TY>::NTH), 0, st, solves, items, nitems, ntiles, one);
-    else
-        hipLaunchKernelGGL((batch_stage_kernel<float, SWE, false, STAGE>), g,
-                           dim3(StageLds<float, SWE, false, TX, TY>::NTH), 0, st, solves, items, nitems, ntiles, one);
+    fn[0] = (const void *)batch_stage_kernel<float, EQN, BATHY, STAGE, SHAPE>;
+    fn[1] = (const void *)batch_stage_one_kernel<float, EQN, BATHY, STAGE, SHAPE>;
+    *threads = ShapeLds<float, EQN, BATHY, SHAPE>::NTH;
+}
+template <int EQN, bool BATHY, int STAGE>
+static void batch_kernel_e(int shape, const void *fn[2], int *threads)
+{
+    switch (shape) {
+    case 0: return batch_kernel_s<EQN, BATHY, STAGE, 0>(fn, threads);
+    case 1: return batch_kernel_s<EQN, BATHY, STAGE, 1>(fn, threads);
+    case 2: return batch_kernel_s<EQN, BATHY, STAGE, 2>(fn, threads);
+    default: return batch_kernel_s<EQN, BATHY, STAGE, 3>(fn, threads);
+    }
+}
+static void batch_kernel(int eqn, int bathy, int stage, int shape, const void *fn[2], int *threads)
+{
+    if (eqn == EULER) {
+        if (stage == 1) batch_kernel_e<EULER, false, 1>(shape, fn, threads);
+        else batch_kernel_e<EULER, false, 2>(shape, fn, threads);
+    } else if (bathy) {
+        if (stage == 1) batch_kernel_e<SWE, true, 1>(shape, fn, threads);
+        else batch_kernel_e<SWE, true, 2>(shape, fn, threads);
+    } else {
+        if (stage == 1) batch_kernel_e<SWE, false, 1>(shape, fn, threads);
+        else batch_kernel_e<SWE, false, 2>(shape, fn, threads);
+    }
 }
 
-hipError_t launch_batch_stage(int eqn, int bathy, int stage, const BatchSolve *solves, const WorkItem *items,
-                              const int *nitems, int grid, hipStream_t st, int one)
+static hipError_t go_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves, const WorkItem *items,
+                          const int *nitems, int ntiles, int wgs, hipStream_t st)
+{
+    const void *fn[2];
+    int threads;
+    batch_kernel(eqn, bathy, stage, shape, fn, &threads);
+    void *args[] = {(void *)&solves, (void *)&items, (void *)&nitems, (void *)&ntiles};
+    return hipLaunchKernel(fn[0], dim3(wgs), dim3(threads), args, 0, st);
+}
+
+hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
+                              const WorkItem *items, const int *nitems, int grid, hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
-    const dim3 g(xcd_grid(grid));
-    if (stage == 1) batch_stage_go<1>(eqn, bathy, g, solves, items, nitems, grid, one, st);
-    else batch_stage_go<2>(eqn, bathy, g, solves, items, nitems, grid, one, st);
-    return hipGetLastError();
+    if (shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
+    return go_list(eqn, bathy, stage, shape, solves, items, nitems, grid, xcd_grid(grid), st);
 }
 
-template <int STAGE>
-static void batch_stage_one_go(int eqn, int bathy, dim3 g, const BatchSolve &d, const WorkItem &it, int ntiles,
-                               hipStream_t st)
-{
-    constexpr int TX = Tile<float>::X, TY = Tile<float>::Y;
-    if (eqn == EULER)
-        hipLaunchKernelGGL((batch_stage_one_kernel<float, EULER, false, STAGE>), g,
-                           dim3(StageLds<float, EULER, false, TX, TY>::NTH), 0, st, d, it, ntiles);
-    else if (bathy)
-        hipLaunchKernelGGL((batch_stage_one_kernel<float, SWE, true, STAGE>), g,
-                           dim3(StageLds<float, SWE, true, TX, TY>::NTH), 0, st, d, it, ntiles);
-    else
-        hipLaunchKernelGGL((batch_stage_one_kernel<float, SWE, false, STAGE>), g,
-                           dim3(StageLds<float, SWE, false, TX, TY>::NTH), 0, st, d, it, ntiles);
-}
-
-hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, const BatchSolve &d, const WorkItem &it, int grid,
-                                  hipStream_t st)
+hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
+                                  int grid, hipStream_t st)
 {
     if (grid <= 0) return hipSuccess;
-    if (it.tile_begin != 0) return hipErrorInvalidValue;
-    const dim3 g(xcd_grid(grid));
-    if (stage == 1) batch_stage_one_go<1>(eqn, bathy, g, d, it, grid, st);
-    else batch_stage_one_go<2>(eqn, bathy, g, d, it, grid, st);
-    return hipGetLastError();
+    if (it.tile_begin != 0 || shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
+    const void *fn[2];
+    int threads;
+    batch_kernel(eqn, bathy, stage, shape, fn, &threads);
+    void *args[] = {(void *)&d, (void *)&it, (void *)&grid};
+    return hipLaunchKernel(fn[1], dim3(xcd_grid(grid)), dim3(threads), args, 0, st);
 }
 
-hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, const BatchSolve *solves, const WorkItem *items,
-                                   const int *list, int wgs, hipStream_t st)
+hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
+                                   const WorkItem *items, const int *list, int wgs, hipStream_t st)
 {
-    if (wgs <= 0 || (wgs & 7)) return hipErrorInvalidValue;
-    if (stage == 1) batch_stage_go<1>(eqn, bathy, dim3(wgs), solves, items, list, 0, 0, st);
-    else batch_stage_go<2>(eqn, bathy, dim3(wgs), solves, items, list, 0, 0, st);
-    return hipGetLastError();
+    if (wgs <= 0 || (wgs & 7) || shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
+    return go_list(eqn, bathy, stage, shape, solves, items, list, 0, wgs, st);
 }
 
 hipError_t launch_rate(const StageDesc &d, const void *q, Ctl *ctl, unsigned long long *rates, int slot,

@@ -44,7 +44,6 @@ struct Req {
     size_t off = 0, bytes = 0;
     int slot = -1;
     int64_t done_steps = 0;
-    int tiles_x = 0, tiles = 0;
     double sim_time = 0;
     size_t q_off, s1_off, bed_off, ctl_off, rates_off;
     size_t s2_off, z_off, small_off;  // learned requests
@@ -54,6 +53,16 @@ struct Req {
     int nvar() const { return r.eqn == FV_EULER ? 4 : 3; }
     bool learned() const { return r.learned != 0; }
 };
+
+// Tile shape of the plain solves' batched launches: one for all rounds, since
+// a captured launch keeps its kernel and a graph per shape would be captured
+// for each.  Of the four this one is within 3 % of the best from half a
+// million cells in a launch on, which a loaded server's rounds hold.
+constexpr int PLAIN_SHAPE = 2;
+
+// max_items counts a plain solve's tiles of 64 x 32 cells, whatever the shape
+// of the launches.
+uint64_t plain_items(int n) { return (uint64_t)((n + 63) / 64) * ((n + 31) / 32); }
 
 double side(const fv_request &r) { return r.lx > 0 ? r.lx : 1.0; }
 
@@ -333,8 +342,6 @@ fv_status admit(fv_server *s, Req *q, std::vector<Req *> &need_h0)
                          s->stream);
     if (e != hipSuccess) return hip_fail(e, "admission rate kernel");
     if (r.eqn == FV_SWE && !(r.h_ref > 0)) need_h0.push_back(q);
-    q->tiles_x = (r.n + fvk::TILE_X - 1) / fvk::TILE_X;
-    q->tiles = q->tiles_x * ((r.n + fvk::TILE_Y - 1) / fvk::TILE_Y);
     return FV_OK;
 }
 
@@ -378,9 +385,11 @@ hipError_t enqueue_steps(fv_server *s, int mask, int nsteps, const int *grids, c
                 const fvk::WorkItem *it = d_items + li * ncap;
                 const int *hdr = d_nitems + li * HDR;
                 if (!rec) {
-                    e = fvk::launch_batch_stage(eqn, type == 0, stage, tab, it, hdr, grids[li], s->stream);
+                    e = fvk::launch_batch_stage(eqn, type == 0, stage, PLAIN_SHAPE, tab, it, hdr, grids[li],
+                                                s->stream);
                 } else {
-                    e = fvk::launch_batch_stage_list(eqn, type == 0, stage, tab, it, hdr, 8, s->stream);
+                    e = fvk::launch_batch_stage_list(eqn, type == 0, stage, PLAIN_SHAPE, tab, it, hdr, 8,
+                                                     s->stream);
                     if (e == hipSuccess) e = record(0, (int)li);
                 }
             }
@@ -456,7 +465,8 @@ fv_status round_graph(fv_server *s, int mask, int nsteps, RoundGraph **out)
 }
 
 // Before a replay: every node's grid from its list's tile count (at least
-// one workgroup: an empty list's launch reads 0 tiles and does nothing).
+// one workgroup: an empty list's launch reads 0 tiles and does nothing).  The
+// kernel and its workgroup size stay the recorded ones.
 hipError_t set_grids(fv_server *s, RoundGraph *rg, const int *grids, const int *lgrid_cnn, const int *lgrid_st,
                      const int *lgrid_h)
 {
@@ -545,9 +555,7 @@ fv_status fv_server_submit(fv_server *s, const fv_request *r, int64_t *id)
     if (rc != FV_OK) return rc;
     if (r->learned && !s->cfg.model) return fail(FV_E_INVALID, "a learned request needs a server model");
     {
-        const uint64_t n = (uint64_t)r->n;
-        const uint64_t own = r->learned ? (uint64_t)cnn::ltiles_st(r->n, r->n)
-                                        : ((n + fvk::TILE_X - 1) / fvk::TILE_X) * ((n + fvk::TILE_Y - 1) / fvk::TILE_Y);
+        const uint64_t own = r->learned ? (uint64_t)cnn::ltiles_st(r->n, r->n) : plain_items(r->n);
         const uint64_t own_cnn = r->learned ? (uint64_t)cnn::ltiles_cnn(r->n, r->n) : 0;
         if (own > s->cfg.max_items || own_cnn > s->cfg.max_items)
             return fail(FV_E_NOMEM, "request needs more than max_items = %llu tiles in one launch",
@@ -593,8 +601,7 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
             t[2] += (uint64_t)cnn::ltiles_cnn(n, n);
             t[3] += (uint64_t)cnn::ltiles_st(n, n);
         } else {
-            t[q->r.eqn == FV_EULER ? 1 : 0] +=
-                (uint64_t)((n + fvk::TILE_X - 1) / fvk::TILE_X) * ((n + fvk::TILE_Y - 1) / fvk::TILE_Y);
+            t[q->r.eqn == FV_EULER ? 1 : 0] += plain_items(n);
         }
     };
     for (Req *q : s->active) kind_tiles(q, tiles);
@@ -669,7 +676,7 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
     s->admit_s += s->now() - ta0;
     // ---- work-lists of the round: one list per [step][type] (type 0 = SWE,
     // 1 = Euler) of the solves still running at that step, packed back to
-    // back; tiles per launch are capped by max_items
+    // back; tiles per launch are capped by max_items at admission
     const size_t ncap = (size_t)s->cfg.max_solves;
     std::vector<int> counts((size_t)K * 2, 0), grids((size_t)K * 2, 0);
     std::vector<int> lcounts((size_t)K, 0), lgrid_cnn((size_t)K, 0), lgrid_st((size_t)K, 0), lgrid_h((size_t)K, 0);
@@ -697,20 +704,17 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
             }
             int type = q->r.eqn == FV_EULER ? 1 : 0;
             size_t li = (size_t)k * 2 + type;
-            if ((uint64_t)grids[li] + q->tiles > s->cfg.max_items)
-                return fail(FV_E_NOMEM, "more than max_items = %llu tiles in one launch",
-                            (unsigned long long)s->cfg.max_items);
             fvk::WorkItem &w = s->h_items[li * ncap + counts[li]];
             int64_t st = q->done_steps + k;
             w.solve = q->slot;
             w.tile_begin = grids[li];
-            w.tiles_x = q->tiles_x;
+            w.tiles_x = (q->r.n + fvk::TILE_X - 1) / fvk::TILE_X;
             w.ri = (unsigned char)(st % 3);
             w.ro = (unsigned char)((st + 1) % 3);
             w.rc = (unsigned char)((st + 2) % 3);
             w.pad = 0;
             counts[li]++;
-            grids[li] += q->tiles;
+            grids[li] += (int)fvk::stage_tiles(q->r.n, q->r.n, PLAIN_SHAPE);
         }
     int mask = 0, nsteps = 0;  // kinds of work present (1 SWE, 2 Euler, 4 learned), last non-empty step + 1
     for (int k = 0; k < K; k++) {

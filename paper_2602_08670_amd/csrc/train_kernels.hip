@@ -108,29 +108,50 @@ hipError_t launch_flags_or(const int *flags, int B, int *any, hipStream_t st)
 namespace cnn {
 
 // Exact cell-average coarsening: coarse(I, J) = mean of the f x f fine block,
-// accumulated in double precision in a fixed order.
-__global__ void coarsen_kernel(const float *fine, int nvar, int nx, int ny, int f, float *coarse)
+// accumulated in double precision in a fixed order.  Bound by reading the
+// fine array once.  A workgroup takes
+// 256 / f coarse cells of a row (one where f > 256): thread t sums column t of
+// their fine cells down the f rows, so that a wave reads whole lines and has
+// its rows' loads in flight together, then one thread per coarse cell adds its
+// f column sums.  (One thread per coarse cell read f x f values in a strided
+// serial chain: 157 us for 3 x 2048^2 at f = 32; now 14 us, 3.6 TB/s.)
+constexpr int CO_TH = 256;
+__global__ __launch_bounds__(CO_TH) void coarsen_kernel(const float *__restrict__ fine, int nvar, int nx, int ny, int f,
+                                                        float *__restrict__ coarse)
 {
+    __shared__ double s[CO_TH];
     const int cx = nx / f, cy = ny / f;
-    const size_t n = (size_t)nvar * cx * cy;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        int v = (int)(i / ((size_t)cx * cy));
-        int r = (int)(i - (size_t)v * cx * cy);
-        int J = r / cx, I = r - J * cx;
-        const float *src = fine + (size_t)v * nx * ny + (size_t)J * f * nx + (size_t)I * f;
+    const int cb = f <= CO_TH ? CO_TH / f : 1, nb = (cx + cb - 1) / cb;
+    const long total = (long)nvar * cy * nb;
+    for (long w = blockIdx.x; w < total; w += gridDim.x) {
+        const long row = w / nb;  // v * cy + J
+        const int I0 = (int)(w - row * nb) * cb, nc = min(cb, cx - I0);
+        const int J = (int)(row % cy);
+        const float *src = fine + ((size_t)(row / cy) * ny + (size_t)J * f) * nx + (size_t)I0 * f;
         double acc = 0.0;
-        for (int a = 0; a < f; a++)
-            for (int b = 0; b < f; b++) acc += (double)src[(size_t)a * nx + b];
-        coarse[i] = (float)(acc / ((double)f * f));
+        for (int c = threadIdx.x; c < nc * f; c += CO_TH) {
+            const float *p = src + c;
+#pragma unroll 8
+            for (int a = 0; a < f; a++) acc += (double)p[(size_t)a * nx];
+        }
+        s[threadIdx.x] = acc;
+        __syncthreads();
+        if ((int)threadIdx.x < nc) {
+            const int n = f <= CO_TH ? f : CO_TH;
+            double sum = 0.0;
+            for (int b = 0; b < n; b++) sum += s[threadIdx.x * n + b];
+            coarse[row * cx + I0 + threadIdx.x] = (float)(sum / ((double)f * f));
+        }
+        __syncthreads();
     }
 }
 
 hipError_t launch_coarsen(const float *fine, int nvar, int nx, int ny, int f, float *coarse, hipStream_t st)
 {
-    size_t n = (size_t)nvar * (nx / f) * (ny / f);
-    unsigned blocks = (unsigned)((n + 255) / 256);
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(coarsen_kernel, dim3(blocks), dim3(256), 0, st, fine, nvar, nx, ny, f, coarse);
+    const int cb = f <= CO_TH ? CO_TH / f : 1;
+    const long total = (long)nvar * (ny / f) * ((nx / f + cb - 1) / cb);
+    hipLaunchKernelGGL(coarsen_kernel, dim3((unsigned)(total < 1 << 20 ? total : 1 << 20)), dim3(CO_TH), 0, st, fine,
+                       nvar, nx, ny, f, coarse);
     return hipGetLastError();
 }
 

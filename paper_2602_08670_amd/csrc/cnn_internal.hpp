@@ -233,14 +233,37 @@ constexpr int ADJ_REC = 20;
 // blocks of the layer-4 input-gradient convolution.
 constexpr int DZ_CH = 96;
 
-// Backward of the network for B solves: adds d loss / d theta into grads
-// (master layout, FP32) and d loss / d q into dq ([B][3][ny][nx], FP32),
-// given dz = d loss / d z (BF16 [p][DZ_CH], channels >= 72 zero) and the
-// activations saved by the forward.
-size_t backward_scratch_bytes(int B, int nx, int ny);
+// Backward of the network for B solves, in two parts.  launch_backward runs
+// the input-gradient chain: given dz = d loss / d z (BF16 [p][DZ_CH], channels
+// >= 72 zero) and the activations saved by the forward it adds d loss / d q
+// into dq ([B][3][ny][nx], FP32) and leaves in a slot what the weight
+// gradients need: G[l] = d loss / d (layer l's output before its ReLU), l =
+// 0..3, BF16 [p][32], and x0, the rounded input, BF16 [p][16].
+// launch_wgrads adds d loss / d theta of `slots` passes into grads (master
+// layout, FP32).  The weights are the same in every stage of a rollout, so
+// the weight gradients of many passes are one launch per layer over all their
+// pixels: at 16 solves of 64^2 a pass is 256 tiles, too few to fill the chip
+// or to pay for 37 to 92 KB of partial sums per tile (68 us of launches per
+// pass); sixteen passes together take 365 us, 23 each.  bwd_slots passes are
+// kept at a time, about a million pixels (448 bytes each), beyond which a
+// launch gains nothing more.
+struct BwdSlot {
+    void *G[4], *x0;
+};
+struct WgradArgs {
+    int slots, B, nx, ny;
+    const void *acts[4];  // the first slot's activations; the others act_slot bytes apart
+    const void *dz;       // likewise, dz_slot bytes apart
+    BwdSlot first;        // likewise, g_slot bytes apart
+    size_t act_slot, dz_slot, g_slot;
+    void *partial;        // scratch of wgrad_partial_bytes()
+    float *grads;
+};
+int bwd_slots(int B, int nx, int ny, int passes);  // 1 .. passes
+size_t wgrad_partial_bytes();
 hipError_t launch_backward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                           void *const acts[4], const void *dz, float *dq, float *grads, void *scratch,
-                           hipStream_t st);
+                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st);
+hipError_t launch_wgrads(const WgradArgs &a, hipStream_t st);
 
 // ------------------------------------------------------------------------
 // Network of the learned Euler step (the same stack on the four conserved
@@ -277,13 +300,11 @@ hipError_t launch_forward_euler_fused(const void *packed, const ENorm &nrm, cons
 // [B][ny][nx][32] BF16) for the backward.
 hipError_t launch_forward_euler_keep(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
                                      void *const acts[4], float *z, hipStream_t st);
-// Backward of the Euler network: grads (master layout) += d loss / d theta,
-// dq ([B][4][ny][nx]) += d loss / d q, given dz (BF16 [p][96]) and the
-// activations of launch_forward_euler_keep.
-size_t backward_scratch_bytes_euler(int B, int nx, int ny);
+// Backward of the Euler network, as the planar one's (dz BF16 [p][96], dq
+// [B][4][ny][nx], the activations of launch_forward_euler_keep).
 hipError_t launch_backward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                 void *const acts[4], const void *dz, float *dq, float *grads, void *scratch,
-                                 hipStream_t st);
+                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st);
+hipError_t launch_wgrads_euler(const WgradArgs &a, hipStream_t st);
 
 // Projector onto the null space of the moment conditions of the given order
 // (exactness for cell averages of polynomials of degree <= order) and Fromm's

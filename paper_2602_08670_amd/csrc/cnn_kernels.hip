@@ -2438,20 +2438,31 @@ __global__ __launch_bounds__(256) void conv_dgrad_input_kernel(const bf16 *G, co
     }
 }
 
-// Weight and bias gradient of a convolution over one 16 x 16 tile of pixels
-// of one solve per workgroup:
-//   dW[t][co][ci] += sum_p G[p][co] In[p + d_t][ci],  db[co] += sum_p G[p][co].
-// MFMA with K = the tile's pixels, two tile rows (32 pixels) per step.  The
-// workgroup stages G transposed ([co][256 pixels]) and the input's 18-row
-// halo transposed three times, shifted by dx = -1, 0, +1 ([dx][ci][18 rows]
-// [16 columns]), so that for every tap the operand fragment (eight pixels of
-// one row, one channel) is one aligned 16-byte LDS read and every input pixel
-// is loaded once per tile instead of once per tap.  A staging job loads eight
-// (G) or ten (input: the union of the three shifts) consecutive pixels' eight
-// channels and transposes them in registers.  Rows past ny contribute nothing
-// (their G is staged as zero).  The bias is one more MFMA per co tile against
-// a fragment whose column 0 is all ones.  Each workgroup writes its partial
-// sums; a fixed-order reduction adds the partials of all workgroups.
+// Weight and bias gradient of a convolution:
+//   dW[t][co][ci] += sum_p G[p][co] In[p + d_t][ci],  db[co] += sum_p G[p][co]
+// over 16 x 16 tiles of pixels of every solve of every slot (a slot: one
+// backward pass's G and In, gslot and islot elements apart).  MFMA with K =
+// the tile's pixels, two tile rows (32 pixels) per step.  A workgroup walks
+// over tiles with its sums in registers.  Per tile it stages G transposed
+// ([co][256 pixels]) and the input's 18-row halo transposed three times,
+// shifted by dx = -1, 0, +1 ([dx][ci][18 rows][16 columns]), so that for every
+// tap the operand fragment (eight pixels of one row, one channel) is one
+// aligned 16-byte LDS read and every input pixel is loaded once per tile
+// instead of once per tap.  A staging job loads eight (G) or ten (input: the
+// union of the three shifts) consecutive pixels' eight channels and
+// transposes them in registers; the next tile's loads are in flight while a
+// tile is computed.  Rows past ny contribute nothing (their G is staged as
+// zero).  The bias is one more MFMA per co tile against a fragment whose
+// column 0 is all ones.
+//
+// Work split: a wave owns one tile of 16 input channels, two (hidden layers,
+// on its share of the tile's rows) or three (layer 4, on all rows) of the
+// output tiles, so that an input fragment feeds that many MFMAs, and a
+// fragment read for tap row 2 is tap row 0's of the next step: 32 LDS reads
+// per 72 MFMAs (hidden layers) where one output tile per wave took 80.  The
+// shares are added through LDS at the end, in a fixed order;
+// each workgroup writes its partial sums once and a fixed-order reduction
+// adds those of all workgroups.  Bound by the transposes' vector instructions.
 template <int CO_T, int CI>
 struct WgradShape {
     static constexpr int NCO = CO_T * 16;
@@ -2461,126 +2472,169 @@ struct WgradShape {
     static constexpr int GLD = HT * HT + 8;              // G^T row stride (BF16)
     static constexpr int ILD = (HT + 2) * HT + 8;        // input^T stride per (shift, channel) (BF16)
     static constexpr int PER = 9 * NCO * CI + NCO;       // partial floats per workgroup
+    static constexpr int CGR = CO_T > 2 ? 2 : 1;         // groups of output tiles
+    static constexpr int COW = (CO_T + CGR - 1) / CGR;   // output tiles per wave
+    static constexpr int SH = 4 / (CI / 16) / CGR;       // waves sharing a tile's rows
+    // workgroups of a launch: as many as are resident at once, each with
+    // several tiles.  32 input channels: one per CU with all registers (66 us
+    // per hidden layer over 1 Mi pixels; two per CU spill, 102 us); 16: two
+    // (35 us; one 47 us).
+    static constexpr int WPC = CI > 16 ? 1 : 2, WGS = 256 * WPC;
 };
 
 template <int CG, int CO_T, int CI>
-__global__ __launch_bounds__(256) void wgrad_kernel(const bf16 *G, const bf16 *In, int H, int W, float *partial)
+__global__ __launch_bounds__(256, (WgradShape<CO_T, CI>::WPC)) void wgrad_kernel(const bf16 *__restrict__ G, size_t gslot,
+                                                    const bf16 *__restrict__ In, size_t islot, int B, int H, int W,
+                                                    int ntiles, float *partial)
 {
     using S = WgradShape<CO_T, CI>;
     constexpr int CI_T = CI / 16, NCO = S::NCO, JI = S::JI, JG = S::JG, SLOTS = S::SLOTS;
     constexpr int GLD = S::GLD, ILD = S::ILD;
-    constexpr int NTILE = CO_T * CI_T;
-    constexpr int TPW = (NTILE + 3) / 4;
+    constexpr int COW = S::COW, SH = S::SH;
+    constexpr int KS = HT / 2 / SH;  // steps of two rows per wave
     __shared__ bf16x8 sG[NCO * GLD / 8];
     __shared__ bf16x8 sI[3 * CI * ILD / 8];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, r16 = lane & 15;
-    const int x0 = blockIdx.x * HT, y0 = blockIdx.y * HT, b = blockIdx.z;
     const size_t hw = (size_t)H * W;
+    const int txn = W / HT, per_solve = txn * ((H + HT - 1) / HT);
 
-    // staging: loads first, then the transposes and LDS writes
     bf16x8 v[SLOTS][10];
+    auto load = [&](int tile) {
+        const int sb = tile / per_solve, tr = tile - sb * per_solve;
+        const int slot = sb / B, b = sb - slot * B;
+        const int y0 = tr / txn * HT, x0 = tr % txn * HT;
+        const bf16 *Gs = G + (size_t)slot * gslot + (size_t)b * hw * CG;
+        const bf16 *Is = In + (size_t)slot * islot + (size_t)b * hw * CI;
 #pragma unroll
-    for (int s = 0; s < SLOTS; s++) {
-        const int j = tid + 256 * s;
-        if (j < JI) {
-            const int c8 = j % (CI / 8), q = (j / (CI / 8)) & 1, h = j / (2 * (CI / 8));
-            int yy = y0 - 1 + h;
-            yy = yy < 0 ? yy + H : yy % H;
-            const bf16 *row = In + ((size_t)b * hw + (size_t)yy * W) * CI + c8 * 8;
-            const int xs = x0 + 8 * q - 1;  // first of the ten columns
+        for (int s = 0; s < SLOTS; s++) {
+            const int j = tid + 256 * s;
+            if (j < JI) {
+                const int c8 = j % (CI / 8), q = (j / (CI / 8)) & 1, h = j / (2 * (CI / 8));
+                int yy = y0 - 1 + h;
+                yy = yy < 0 ? yy + H : yy % H;
+                const bf16 *row = Is + (size_t)yy * W * CI + c8 * 8;
+                const int xs = x0 + 8 * q - 1;  // first of the ten columns
 #pragma unroll
-            for (int i = 0; i < 10; i++) v[s][i] = *(const bf16x8 *)(row + (size_t)wrap(xs + i, W) * CI);
-        } else if (j < JI + JG) {
-            const int jj = j - JI;
-            const int c8 = jj % (NCO / 8), q = (jj / (NCO / 8)) & 1, r = jj / (2 * (NCO / 8));
-            if (y0 + r < H) {
-                const bf16 *src = G + ((size_t)b * hw + (size_t)(y0 + r) * W + x0 + 8 * q) * CG + c8 * 8;
+                for (int i = 0; i < 10; i++) v[s][i] = *(const bf16x8 *)(row + (size_t)wrap(xs + i, W) * CI);
+            } else if (j < JI + JG) {
+                const int jj = j - JI;
+                const int c8 = jj % (NCO / 8), q = (jj / (NCO / 8)) & 1, r = jj / (2 * (NCO / 8));
+                if (y0 + r < H) {
+                    const bf16 *src = Gs + ((size_t)(y0 + r) * W + x0 + 8 * q) * CG + c8 * 8;
 #pragma unroll
-                for (int i = 0; i < 8; i++) v[s][i] = *(const bf16x8 *)(src + (size_t)i * CG);
-            } else {
+                    for (int i = 0; i < 8; i++) v[s][i] = *(const bf16x8 *)(src + (size_t)i * CG);
+                } else {
 #pragma unroll
-                for (int i = 0; i < 8; i++)
+                    for (int i = 0; i < 8; i++)
 #pragma unroll
-                    for (int e = 0; e < 8; e++) v[s][i][e] = (bf16)0.0f;
+                        for (int e = 0; e < 8; e++) v[s][i][e] = (bf16)0.0f;
+                }
             }
         }
-    }
+    };
+
+    const int cit = wave % CI_T, share = S::CGR == 1 ? wave / CI_T : 0;
+    const int cot0 = S::CGR == 1 ? 0 : wave / CI_T * COW;  // first output tile; a tile past the last is skipped
+    floatx4 acc[COW][10];  // nine taps, then the bias (of the waves with cit == 0)
 #pragma unroll
-    for (int s = 0; s < SLOTS; s++) {
-        const int j = tid + 256 * s;
-        if (j < JI) {
-            const int c8 = j % (CI / 8), q = (j / (CI / 8)) & 1, h = j / (2 * (CI / 8));
+    for (int c = 0; c < COW; c++)
 #pragma unroll
-            for (int d = 0; d < 3; d++)
+        for (int t = 0; t < 10; t++) acc[c][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; e++) ones[e] = (bf16)(r16 == 0 ? 1.0f : 0.0f);
+
+    load(blockIdx.x);
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; s++) {
+            const int j = tid + 256 * s;
+            if (j < JI) {
+                const int c8 = j % (CI / 8), q = (j / (CI / 8)) & 1, h = j / (2 * (CI / 8));
+#pragma unroll
+                for (int d = 0; d < 3; d++)
+#pragma unroll
+                    for (int c = 0; c < 8; c++) {
+                        bf16x8 w;
+#pragma unroll
+                        for (int i = 0; i < 8; i++) w[i] = v[s][i + d][c];
+                        sI[((d * CI + c8 * 8 + c) * ILD + h * HT + 8 * q) / 8] = w;
+                    }
+            } else if (j < JI + JG) {
+                const int jj = j - JI;
+                const int c8 = jj % (NCO / 8), q = (jj / (NCO / 8)) & 1, r = jj / (2 * (NCO / 8));
 #pragma unroll
                 for (int c = 0; c < 8; c++) {
                     bf16x8 w;
 #pragma unroll
-                    for (int i = 0; i < 8; i++) w[i] = v[s][i + d][c];
-                    sI[((d * CI + c8 * 8 + c) * ILD + h * HT + 8 * q) / 8] = w;
+                    for (int i = 0; i < 8; i++) w[i] = v[s][i][c];
+                    sG[((c8 * 8 + c) * GLD + r * HT + 8 * q) / 8] = w;
                 }
-        } else if (j < JI + JG) {
-            const int jj = j - JI;
-            const int c8 = jj % (NCO / 8), q = (jj / (NCO / 8)) & 1, r = jj / (2 * (NCO / 8));
-#pragma unroll
-            for (int c = 0; c < 8; c++) {
-                bf16x8 w;
-#pragma unroll
-                for (int i = 0; i < 8; i++) w[i] = v[s][i][c];
-                sG[((c8 * 8 + c) * GLD + r * HT + 8 * q) / 8] = w;
             }
         }
-    }
-    __syncthreads();
+        __syncthreads();
+        if (tile + (int)gridDim.x < ntiles) load(tile + gridDim.x);
 
-    floatx4 acc[TPW][9], accb[TPW];
+        // lane (r16, g) of step ks: tile row 2 ks + (g >> 1), columns 8 (g & 1) .. +7
+        const int cq = 8 * (g & 1);
+        bf16x8 bf[3][3];  // [tap row][dx]
 #pragma unroll
-    for (int j = 0; j < TPW; j++) {
-        accb[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < KS; k++) {
+            const int r = 2 * (share * KS + k) + (g >> 1);
 #pragma unroll
-        for (int t = 0; t < 9; t++) acc[j][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    bf16x8 ones;
+            for (int dy = 0; dy < 3; dy++)
 #pragma unroll
-    for (int e = 0; e < 8; e++) ones[e] = (bf16)(r16 == 0 ? 1.0f : 0.0f);
-    // lane (r16, g) of step ks: tile row 2 ks + (g >> 1), columns 8 (g & 1) .. +7
+                for (int dx = 0; dx < 3; dx++)
+                    bf[dy][dx] = k > 0 && dy == 0
+                                     ? bf[2][dx]
+                                     : sI[((dx * CI + cit * 16 + r16) * ILD + (r + dy) * HT + cq) / 8];
 #pragma unroll
-    for (int j = 0; j < TPW; j++) {
-        const int id = wave + 4 * j;
-        if (id < NTILE) {
-            const int cot = id / CI_T, cit = id - cot * CI_T;
-            for (int ks = 0; ks < HT / 2; ks++) {
-                const int r = 2 * ks + (g >> 1), cq = 8 * (g & 1);
-                const bf16x8 af = sG[((cot * 16 + r16) * GLD + r * HT + cq) / 8];
-                bf16x8 bf[9];
+            for (int c = 0; c < COW; c++) {
+                if (COW * S::CGR > CO_T && cot0 + c >= CO_T) break;
+                const bf16x8 af = sG[(((cot0 + c) * 16 + r16) * GLD + r * HT + cq) / 8];
 #pragma unroll
                 for (int t = 0; t < 9; t++)
-                    bf[t] = sI[(((t % 3) * CI + cit * 16 + r16) * ILD + (r + t / 3) * HT + cq) / 8];
-#pragma unroll
-                for (int t = 0; t < 9; t++)
-                    acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[t], acc[j][t], 0, 0, 0);
-                if (cit == 0) accb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, ones, accb[j], 0, 0, 0);
+                    acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[t / 3][t % 3], acc[c][t], 0, 0, 0);
+                if (cit == 0) acc[c][9] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, ones, acc[c][9], 0, 0, 0);
             }
         }
+        __syncthreads();
     }
-    // partial layout: [9][NCO][CI] then [NCO] bias
-    const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    float *pp = partial + (size_t)blk * S::PER;
+
+    // the waves' shares of an input tile, added in wave order
+    floatx4 *s_x = (floatx4 *)sI;  // [CI_T][10][64]
+    static_assert(sizeof(bf16x8) * 3 * CI * ILD / 8 >= sizeof(floatx4) * CI_T * 10 * 64, "exchange buffer");
 #pragma unroll
-    for (int j = 0; j < TPW; j++) {
-        const int id = wave + 4 * j;
-        if (id < NTILE) {
-            const int cot = id / CI_T, cit = id - cot * CI_T;
+    for (int w = 1; w < SH; w++)
 #pragma unroll
-            for (int t = 0; t < 9; t++)
+        for (int c = 0; c < COW; c++) {
+            if (share == w) {
 #pragma unroll
-                for (int i = 0; i < 4; i++)
-                    pp[((size_t)t * NCO + cot * 16 + 4 * g + i) * CI + cit * 16 + r16] = acc[j][t][i];
-            if (cit == 0 && r16 == 0) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) pp[9 * NCO * CI + cot * 16 + 4 * g + i] = accb[j][i];
+                for (int t = 0; t < 10; t++) s_x[(cit * 10 + t) * 64 + lane] = acc[c][t];
             }
+            __syncthreads();
+            if (share == 0) {
+#pragma unroll
+                for (int t = 0; t < 10; t++) acc[c][t] += s_x[(cit * 10 + t) * 64 + lane];
+            }
+            __syncthreads();
+        }
+    if (share != 0) return;
+    // partial layout: [9][NCO][CI] then [NCO] bias
+    float *pp = partial + (size_t)blockIdx.x * S::PER;
+#pragma unroll
+    for (int c = 0; c < COW; c++) {
+        const int cot = cot0 + c;
+        if (COW * S::CGR > CO_T && cot >= CO_T) break;
+#pragma unroll
+        for (int t = 0; t < 9; t++)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                pp[((size_t)t * NCO + cot * 16 + 4 * g + i) * CI + cit * 16 + r16] = acc[c][t][i];
+        if (cit == 0 && r16 == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) pp[9 * NCO * CI + cot * 16 + 4 * g + i] = acc[c][9][i];
         }
     }
 }
@@ -2624,121 +2678,94 @@ __global__ __launch_bounds__(RED_WAVES * 64) void wgrad_reduce_kernel(const floa
     else grads[woff + (co * ci_real + ci) * 9 + tap] += t;
 }
 
-static dim3 wgrad_grid(int B, int nx, int ny) { return dim3((unsigned)(nx / HT), (unsigned)((ny + HT - 1) / HT), (unsigned)B); }
-
-size_t backward_scratch_bytes(int B, int nx, int ny)
+// Weight and bias gradient of one layer over `slots` backward passes: gslot
+// and islot are the slots' distances in G and In (elements).
+template <int CG, int CO_T, int CI>
+static void wgrad(const void *G, size_t gslot, const void *In, size_t islot, int slots, int B, int H, int W,
+                  float *partial, int co_real, int ci_real, int woff, int boff, float *grads, hipStream_t st)
 {
-    long npix = (long)B * nx * ny;
-    const dim3 wg = wgrad_grid(B, nx, ny);
-    size_t part = (size_t)wg.x * wg.y * wg.z * WgradShape<5, 32>::PER * 4;
-    return 2 * al256(npix * 32 * 2) + al256(npix * 16 * 2) + al256(part);
+    using S = WgradShape<CO_T, CI>;
+    const int ntiles = slots * B * (W / HT) * ((H + HT - 1) / HT);
+    const int nblocks = ntiles < S::WGS ? ntiles : S::WGS;
+    hipLaunchKernelGGL((wgrad_kernel<CG, CO_T, CI>), dim3(nblocks), dim3(256), 0, st, (const bf16 *)G, gslot,
+                       (const bf16 *)In, islot, B, H, W, ntiles, partial);
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((S::PER + 63) / 64), dim3(RED_WAVES * 64), 0, st,
+                       (const float *)partial, nblocks, CO_T * 16, CI, co_real, ci_real, woff, boff, grads);
 }
 
-template <int CG, int CO_T, int CI>
-static void wgrad(const bf16 *G, const bf16 *In, int B, int H, int W, float *partial, int co_real, int ci_real,
-                  int woff, int boff, float *grads, hipStream_t st)
+size_t wgrad_partial_bytes()
 {
-    const dim3 wg = wgrad_grid(B, W, H);
-    const int nblocks = (int)(wg.x * wg.y * wg.z);
-    hipLaunchKernelGGL((wgrad_kernel<CG, CO_T, CI>), wg, dim3(256), 0, st, G, In, H, W, partial);
-    const int per = WgradShape<CO_T, CI>::PER;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((per + 63) / 64), dim3(RED_WAVES * 64), 0, st, (const float *)partial,
-                       nblocks, CO_T * 16, CI, co_real, ci_real, woff, boff, grads);
+    const size_t a = (size_t)WgradShape<6, 32>::PER * WgradShape<6, 32>::WGS;
+    const size_t b = (size_t)WgradShape<2, 32>::PER * WgradShape<2, 32>::WGS;
+    return al256((a > b ? a : b) * sizeof(float));
+}
+
+int bwd_slots(int B, int nx, int ny, int passes)
+{
+    const int64_t npix = (int64_t)B * nx * ny, k = ((int64_t)1 << 20) / npix;
+    return k < 1 ? 1 : (k < passes ? (int)k : passes);
+}
+
+// The input-gradient chain of the network, layer 4 down to the states;
+// CZ channels of dz in KZ 32-channel K blocks.
+template <int C, typename NormT, typename PK>
+static hipError_t backward_chain(const char *P, const PK &pk, const NormT &nrm, const float *q, int B, int nx, int ny,
+                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
+{
+    // the halo-tile kernels take 16-pixel-wide tiles
+    if (nx % HT) return hipErrorInvalidValue;
+    const long npix = (long)B * nx * ny;
+    unsigned eg = (unsigned)((npix * 16 + 255) / 256);
+    if (eg > 8192) eg = 8192;
+    dim3 cg((unsigned)((npix + 63) / 64)), blk(256);
+    launch_halo<3, 2, 2>((const bf16 *)dz, (const bf16 *)(P + pk.wt[4]), nullptr, (const bf16 *)acts[3], s.G[3], B, nx,
+                         ny, st);
+    for (int l = 3; l >= 1; l--)
+        launch_halo<1, 2, 2>((const bf16 *)s.G[l], (const bf16 *)(P + pk.wt[l]), nullptr, (const bf16 *)acts[l - 1],
+                             s.G[l - 1], B, nx, ny, st);
+    // layer 0: the input rebuilt as the forward rounds it, for its weight gradient
+    hipLaunchKernelGGL((x0_kernel<C, NormT>), dim3(eg), blk, 0, st, q, (bf16 *)s.x0, B, ny, nx, nrm);
+    hipLaunchKernelGGL((conv_dgrad_input_kernel<C, NormT>), cg, blk, 0, st, (const bf16 *)s.G[0],
+                       (const bf16 *)(P + pk.wt[0]), dq, B, ny, nx, nrm);
+    return hipGetLastError();
 }
 
 hipError_t launch_backward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                           void *const acts[4], const void *dzv, float *dq, float *grads, void *scratch,
-                           hipStream_t st)
+                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
 {
-    const Packed pk = packed_layout();
-    const MasterLayout ml = master_layout();
-    const char *P = (const char *)packed;
-    const long npix = (long)B * nx * ny;
-    // the halo-tile kernels take 16-pixel-wide tiles
-    if (nx % HT) return hipErrorInvalidValue;
-    const bf16 *dz = (const bf16 *)dzv;
-    char *sc = (char *)scratch;
-    bf16 *dA = (bf16 *)sc;
-    sc += al256(npix * 32 * 2);
-    bf16 *dB = (bf16 *)sc;
-    sc += al256(npix * 32 * 2);
-    bf16 *x0 = (bf16 *)sc;
-    sc += al256(npix * 16 * 2);
-    float *partial = (float *)sc;
-    const bf16 *a[4] = {(const bf16 *)acts[0], (const bf16 *)acts[1], (const bf16 *)acts[2], (const bf16 *)acts[3]};
-    unsigned eg = (unsigned)((npix * 16 + 255) / 256);
-    if (eg > 8192) eg = 8192;
-    dim3 cg((unsigned)((npix + 63) / 64)), blk(256);
-
-    // layer 4: 32 -> 72
-    wgrad<96, 5, 32>(dz, a[3], B, ny, nx, partial, 72, 32, ml.w[4], ml.b[4], grads, st);
-    launch_halo<3, 2, 2>(dz, (const bf16 *)(P + pk.wt[4]), nullptr, a[3], (void *)dA, B, nx, ny, st);
-    // layers 3, 2, 1: 32 -> 32
-    bf16 *cur = dA, *nxt = dB;
-    for (int l = 3; l >= 1; l--) {
-        wgrad<32, 2, 32>(cur, a[l - 1], B, ny, nx, partial, 32, 32, ml.w[l], ml.b[l], grads, st);
-        launch_halo<1, 2, 2>(cur, (const bf16 *)(P + pk.wt[l]), nullptr, a[l - 1], (void *)nxt, B, nx, ny, st);
-        bf16 *t = cur;
-        cur = nxt;
-        nxt = t;
-    }
-    // layer 0: 3 -> 32 (input rebuilt as the forward rounds it)
-    hipLaunchKernelGGL((x0_kernel<3, Norm>), dim3(eg), blk, 0, st, q, x0, B, ny, nx, nrm);
-    wgrad<32, 2, 16>(cur, x0, B, ny, nx, partial, 32, 3, ml.w[0], ml.b[0], grads, st);
-    hipLaunchKernelGGL((conv_dgrad_input_kernel<3, Norm>), cg, blk, 0, st, (const bf16 *)cur,
-                       (const bf16 *)(P + pk.wt[0]), dq, B, ny, nx, nrm);
-    return hipGetLastError();
+    return backward_chain<CIN>((const char *)packed, packed_layout(), nrm, q, B, nx, ny, acts, dz, dq, s, st);
 }
 
-size_t backward_scratch_bytes_euler(int B, int nx, int ny)
-{
-    long npix = (long)B * nx * ny;
-    const dim3 wg = wgrad_grid(B, nx, ny);
-    size_t part = (size_t)wg.x * wg.y * wg.z * WgradShape<6, 32>::PER * 4;
-    return 2 * al256(npix * 32 * 2) + al256(npix * 16 * 2) + al256(part);
-}
-
-// The planar network's backward on the Euler network's shapes: layer 4
-// 32 -> 96 (six co tiles, dz read as three 32-channel K blocks), layer 0
-// 4 -> 32.
 hipError_t launch_backward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                 void *const acts[4], const void *dzv, float *dq, float *grads, void *scratch,
-                                 hipStream_t st)
+                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
 {
-    const EPacked pk = euler_packed_layout();
-    const EMaster ml = euler_master();
-    const char *P = (const char *)packed;
-    const long npix = (long)B * nx * ny;
-    if (nx % HT) return hipErrorInvalidValue;
-    const bf16 *dz = (const bf16 *)dzv;
-    char *sc = (char *)scratch;
-    bf16 *dA = (bf16 *)sc;
-    sc += al256(npix * 32 * 2);
-    bf16 *dB = (bf16 *)sc;
-    sc += al256(npix * 32 * 2);
-    bf16 *x0 = (bf16 *)sc;
-    sc += al256(npix * 16 * 2);
-    float *partial = (float *)sc;
-    const bf16 *a[4] = {(const bf16 *)acts[0], (const bf16 *)acts[1], (const bf16 *)acts[2], (const bf16 *)acts[3]};
-    unsigned eg = (unsigned)((npix * 16 + 255) / 256);
-    if (eg > 8192) eg = 8192;
-    dim3 cg((unsigned)((npix + 63) / 64)), blk(256);
+    return backward_chain<E_CIN>((const char *)packed, euler_packed_layout(), nrm, q, B, nx, ny, acts, dz, dq, s, st);
+}
 
-    wgrad<E_COUT, 6, 32>(dz, a[3], B, ny, nx, partial, E_COUT, 32, ml.w[4], ml.b[4], grads, st);
-    launch_halo<3, 2, 2>(dz, (const bf16 *)(P + pk.wt[4]), nullptr, a[3], (void *)dA, B, nx, ny, st);
-    bf16 *cur = dA, *nxt = dB;
-    for (int l = 3; l >= 1; l--) {
-        wgrad<32, 2, 32>(cur, a[l - 1], B, ny, nx, partial, 32, 32, ml.w[l], ml.b[l], grads, st);
-        launch_halo<1, 2, 2>(cur, (const bf16 *)(P + pk.wt[l]), nullptr, a[l - 1], (void *)nxt, B, nx, ny, st);
-        bf16 *t = cur;
-        cur = nxt;
-        nxt = t;
-    }
-    hipLaunchKernelGGL((x0_kernel<E_CIN, ENorm>), dim3(eg), blk, 0, st, q, x0, B, ny, nx, nrm);
-    wgrad<32, 2, 16>(cur, x0, B, ny, nx, partial, 32, E_CIN, ml.w[0], ml.b[0], grads, st);
-    hipLaunchKernelGGL((conv_dgrad_input_kernel<E_CIN, ENorm>), cg, blk, 0, st, (const bf16 *)cur,
-                       (const bf16 *)(P + pk.wt[0]), dq, B, ny, nx, nrm);
+template <int CIN_, int COUT_, int CO_T, typename ML>
+static hipError_t wgrads(const ML &ml, const WgradArgs &a, hipStream_t st)
+{
+    if (a.nx % HT) return hipErrorInvalidValue;
+    const size_t is = a.act_slot / 2, gs = a.g_slot / 2;
+    float *pt = (float *)a.partial;
+    wgrad<96, CO_T, 32>(a.dz, a.dz_slot / 2, a.acts[3], is, a.slots, a.B, a.ny, a.nx, pt, COUT_, 32, ml.w[4], ml.b[4],
+                        a.grads, st);
+    for (int l = 3; l >= 1; l--)
+        wgrad<32, 2, 32>(a.first.G[l], gs, a.acts[l - 1], is, a.slots, a.B, a.ny, a.nx, pt, 32, 32, ml.w[l], ml.b[l],
+                         a.grads, st);
+    wgrad<32, 2, 16>(a.first.G[0], gs, a.first.x0, gs, a.slots, a.B, a.ny, a.nx, pt, 32, CIN_, ml.w[0], ml.b[0],
+                     a.grads, st);
     return hipGetLastError();
+}
+
+hipError_t launch_wgrads(const WgradArgs &a, hipStream_t st)
+{
+    return wgrads<CIN, COUT, 5>(master_layout(), a, st);
+}
+
+hipError_t launch_wgrads_euler(const WgradArgs &a, hipStream_t st)
+{
+    return wgrads<E_CIN, E_COUT, 6>(euler_master(), a, st);
 }
 
 }  // namespace cnn

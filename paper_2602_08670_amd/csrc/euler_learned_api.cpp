@@ -4,6 +4,7 @@
 // launches); training with the unrolled loss of eq 2.28.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -264,9 +265,10 @@ void fv_euler_learned_destroy(fv_euler_learned *e) { delete e; }
 namespace {
 
 struct TLayout {
-    size_t states, s1, acts, z, plain, s2, flags, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, lossp, loss,
-        scale, total;
-    size_t st, act, zb;
+    size_t states, s1, acts, z, plain, s2, flags, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, part, lossp,
+        loss, scale, total;
+    size_t st, act, zb, dzb, gb;
+    int slots;  // backward passes whose weight gradients are taken together
 };
 
 fv_status validate_train(const fv_euler_train_config *c)
@@ -308,12 +310,16 @@ TLayout tlayout(const fv_euler_train_config *c)
     L.nfb = take((size_t)c->B * 8);
     L.redone = take((size_t)c->B * 8);
     L.fatal = take((size_t)c->B * 4);
-    L.dz = take(npix * cnn::E_COUT * 2);
+    L.slots = cnn::bwd_slots(c->B, c->nx, c->ny, 2 * T);
+    L.dzb = align256(npix * cnn::E_COUT * 2);
+    L.gb = 4 * L.act + align256(npix * 16 * 2);
+    L.dz = take(L.slots * L.dzb);
     L.contrib = take(npix * 2 * eln::ADJ_REC * 4);
     L.G = take(L.st);
     L.Gn = take(L.st);
     L.gS1 = take(L.st);
-    L.bwd = take(cnn::backward_scratch_bytes_euler(c->B, c->nx, c->ny));
+    L.bwd = take(L.slots * L.gb);
+    L.part = take(cnn::wgrad_partial_bytes());
     L.lossp = take(1024 * 8);
     L.loss = take(8);
     L.scale = take(16);
@@ -336,6 +342,31 @@ struct fv_euler_trainer {
     void *act(int t, int stage, int l) { return ws + L.acts + (((size_t)t * 2 + stage) * 4 + l) * L.act; }
     float *zb(int t, int stage) { return (float *)(ws + L.z + ((size_t)t * 2 + stage) * L.zb); }
     int *plain(int t) { return (int *)(ws + L.plain) + (size_t)t * cfg.B; }
+    // pass 2 t + stage keeps its dz and layer gradients in slot pass % slots
+    __bf16 *dz(int pass) { return (__bf16 *)(ws + L.dz + (size_t)(pass % L.slots) * L.dzb); }
+    cnn::BwdSlot slot(int pass)
+    {
+        char *p = ws + L.bwd + (size_t)(pass % L.slots) * L.gb;
+        return cnn::BwdSlot{{p, p + L.act, p + 2 * L.act, p + 3 * L.act}, p + 4 * L.act};
+    }
+    // the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
+    hipError_t wgrads(int pass, int n)
+    {
+        cnn::WgradArgs a;
+        a.slots = n;
+        a.B = cfg.B;
+        a.nx = cfg.nx;
+        a.ny = cfg.ny;
+        for (int l = 0; l < 4; l++) a.acts[l] = act(pass / 2, pass % 2, l);
+        a.dz = dz(pass);
+        a.first = slot(pass);
+        a.act_slot = 4 * L.act;
+        a.dz_slot = L.dzb;
+        a.g_slot = L.gb;
+        a.partial = ws + L.part;
+        a.grads = grads;
+        return cnn::launch_wgrads_euler(a, net->stream);
+    }
 };
 
 extern "C" {
@@ -448,7 +479,12 @@ fv_status fv_euler_train_step(fv_euler_trainer *tr, const float *q0, const float
     ad.gamma = a.gamma;
     ad.pr = net->pr;
     ad.contrib = (float *)(ws + L.contrib);
-    ad.dz = (__bf16 *)(ws + L.dz);
+    // after a pass: the weight gradients of its group of passes, once all of
+    // them (the later ones) are done
+    auto wgrads = [&](int pass) {
+        if (pass % L.slots) return hipSuccess;
+        return tr->wgrads(pass, std::min(L.slots, 2 * T - pass));
+    };
     for (int t = T; t >= 1 && e == hipSuccess; t--) {
         e = cnn::launch_loss(tr->st(t), targets + (size_t)(t - 1) * nst, (const float *)(ws + L.scale), B, nx, ny, G,
                              (double *)(ws + L.lossp), 1024, (double *)(ws + L.loss), st, 4);
@@ -458,17 +494,21 @@ fv_status fv_euler_train_step(fv_euler_trainer *tr, const float *q0, const float
         ad.plain = tr->plain(k);
         // stage 2: out = q/2 + (S1 + dt L(S1))/2
         ad.qs = tr->s1(k); ad.z = tr->zb(k, 1); ad.gout = G; ad.wscale = 0.5f * (float)c.dt;
+        ad.dz = tr->dz(2 * k + 1);
         if (e == hipSuccess) e = eln::adjoint(fl, ad, gS1, 0.5f, 0, st);
         if (e == hipSuccess)
-            e = cnn::launch_backward_euler(packed, net->nrm, tr->s1(k), B, nx, ny, a1, ad.dz, gS1, tr->grads,
-                                           ws + L.bwd, st);
+            e = cnn::launch_backward_euler(packed, net->nrm, tr->s1(k), B, nx, ny, a1, ad.dz, gS1,
+                                           tr->slot(2 * k + 1), st);
+        if (e == hipSuccess) e = wgrads(2 * k + 1);
         // stage 1: S1 = q + dt L(q), after the q/2 term of stage 2
         if (e == hipSuccess) e = cnn::launch_scale(Gn, G, 0.5f, nst, st);
         ad.qs = tr->st(k); ad.z = tr->zb(k, 0); ad.gout = gS1; ad.wscale = (float)c.dt;
+        ad.dz = tr->dz(2 * k);
         if (e == hipSuccess) e = eln::adjoint(fl, ad, Gn, 1.0f, 1, st);
         if (e == hipSuccess)
-            e = cnn::launch_backward_euler(packed, net->nrm, tr->st(k), B, nx, ny, a0, ad.dz, Gn, tr->grads,
-                                           ws + L.bwd, st);
+            e = cnn::launch_backward_euler(packed, net->nrm, tr->st(k), B, nx, ny, a0, ad.dz, Gn,
+                                           tr->slot(2 * k), st);
+        if (e == hipSuccess) e = wgrads(2 * k);
         float *tmp = G;
         G = Gn;
         Gn = tmp;

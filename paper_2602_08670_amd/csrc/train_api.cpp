@@ -2,6 +2,7 @@
 // the loss of eq 2.28, the reverse pass and Adam.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -14,9 +15,10 @@ using fvapi::hip_fail;
 namespace {
 
 struct TrainLayout {
-    size_t states, s1, acts, z, plain, s2, bad, dt, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, lossp, loss,
-        scale, total;
-    size_t st, act, zb;  // per-unit sizes
+    size_t states, s1, acts, z, plain, s2, bad, dt, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, part, lossp,
+        loss, scale, total;
+    size_t st, act, zb, dzb, gb;  // per-unit sizes
+    int slots;                    // backward passes whose weight gradients are taken together
 };
 
 fv_status validate(const fv_train_config *c)
@@ -68,8 +70,11 @@ TrainLayout layout_of(const fv_train_config *c)
     o += align256(c->B * 8);
     L.fatal = o;
     o += align256(c->B * 4);
+    L.slots = cnn::bwd_slots(c->B, c->nx, c->ny, 2 * T);
+    L.dzb = align256(npix * cnn::DZ_CH * 2);
+    L.gb = 4 * L.act + align256(npix * 16 * 2);
     L.dz = o;
-    o += align256(npix * cnn::DZ_CH * 2);
+    o += L.slots * L.dzb;
     L.contrib = o;
     o += align256(npix * 2 * cnn::ADJ_REC * 4);
     L.G = o;
@@ -79,7 +84,9 @@ TrainLayout layout_of(const fv_train_config *c)
     L.gS1 = o;
     o += L.st;
     L.bwd = o;
-    o += align256(cnn::backward_scratch_bytes(c->B, c->nx, c->ny));
+    o += L.slots * L.gb;
+    L.part = o;
+    o += cnn::wgrad_partial_bytes();
     L.lossp = o;
     o += align256(1024 * 8);
     L.loss = o;
@@ -105,6 +112,31 @@ struct fv_trainer {
     void *act(int t, int stage, int l) { return ws + L.acts + (((size_t)t * 2 + stage) * 4 + l) * L.act; }
     float *zb(int t, int stage) { return (float *)(ws + L.z + ((size_t)t * 2 + stage) * L.zb); }
     int *plain(int t) { return (int *)(ws + L.plain) + (size_t)t * cfg.B; }
+    // pass 2 t + stage keeps its dz and layer gradients in slot pass % slots
+    void *dz(int pass) { return ws + L.dz + (size_t)(pass % L.slots) * L.dzb; }
+    cnn::BwdSlot slot(int pass)
+    {
+        char *p = ws + L.bwd + (size_t)(pass % L.slots) * L.gb;
+        return cnn::BwdSlot{{p, p + L.act, p + 2 * L.act, p + 3 * L.act}, p + 4 * L.act};
+    }
+    // the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
+    hipError_t wgrads(int pass, int n)
+    {
+        cnn::WgradArgs a;
+        a.slots = n;
+        a.B = cfg.B;
+        a.nx = cfg.nx;
+        a.ny = cfg.ny;
+        for (int l = 0; l < 4; l++) a.acts[l] = act(pass / 2, pass % 2, l);
+        a.dz = dz(pass);
+        a.first = slot(pass);
+        a.act_slot = 4 * L.act;
+        a.dz_slot = L.dzb;
+        a.g_slot = L.gb;
+        a.partial = ws + L.part;
+        a.grads = grads;
+        return cnn::launch_wgrads(a, m->stream);
+    }
 };
 
 extern "C" {
@@ -229,7 +261,12 @@ fv_status fv_train_step(fv_trainer *tr, const float *q0, const float *targets, i
     as.h0 = sb.h0;
     as.pr = tr->m->pr;
     as.contrib = (float *)(ws + L.contrib);
-    as.dz = ws + L.dz;
+    // after a pass: the weight gradients of its group of passes, once all of
+    // them (the later ones) are done
+    auto wgrads = [&](int pass) {
+        if (pass % L.slots) return hipSuccess;
+        return tr->wgrads(pass, std::min(L.slots, 2 * T - pass));
+    };
     for (int t = T; t >= 1 && e == hipSuccess; t--) {
         e = cnn::launch_loss(tr->st(t), targets + (size_t)(t - 1) * nst, (const float *)(ws + L.scale), B, nx, ny, G,
                              (double *)(ws + L.lossp), 1024, (double *)(ws + L.loss), st);
@@ -238,18 +275,21 @@ fv_status fv_train_step(fv_trainer *tr, const float *q0, const float *targets, i
         void *a1[4] = {tr->act(k, 1, 0), tr->act(k, 1, 1), tr->act(k, 1, 2), tr->act(k, 1, 3)};
         // stage 2: out = q/2 + (S1 + dt L(S1))/2
         as.qs = tr->s1(k); as.z = tr->zb(k, 1); as.gout = G; as.a1 = 0.5f; as.plain = tr->plain(k);
-        as.gqs = gS1; as.accumulate = 0;
+        as.gqs = gS1; as.accumulate = 0; as.dz = tr->dz(2 * k + 1);
         if (e == hipSuccess) e = cnn::launch_adjoint(fl, as, st);
         if (e == hipSuccess)
-            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->s1(k), B, nx, ny, a1, as.dz, gS1, tr->grads,
-                                     ws + L.bwd, st);
+            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->s1(k), B, nx, ny, a1, as.dz, gS1,
+                                     tr->slot(2 * k + 1), st);
+        if (e == hipSuccess) e = wgrads(2 * k + 1);
         // stage 1: S1 = q + dt L(q); the q/2 term of stage 2 first
         if (e == hipSuccess) e = cnn::launch_scale(Gn, G, 0.5f, nst, st);
         as.qs = tr->st(k); as.z = tr->zb(k, 0); as.gout = gS1; as.a1 = 1.0f; as.gqs = Gn; as.accumulate = 1;
+        as.dz = tr->dz(2 * k);
         if (e == hipSuccess) e = cnn::launch_adjoint(fl, as, st);
         if (e == hipSuccess)
-            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->st(k), B, nx, ny, a0, as.dz, Gn, tr->grads,
-                                     ws + L.bwd, st);
+            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->st(k), B, nx, ny, a0, as.dz, Gn, tr->slot(2 * k),
+                                     st);
+        if (e == hipSuccess) e = wgrads(2 * k);
         float *tmp = G;
         G = Gn;
         Gn = tmp;

@@ -59,16 +59,16 @@ hipError_t launch_pack(const float *master, void *packed, hipStream_t st);
 // Forward of B solves of size ny x nx (nx % 16 == 0, ny*nx % 64 == 0).
 //   q    : [B][3][ny][nx] FP32 states;
 //   acts : 4 activation buffers [B][ny][nx][32] BF16 (outputs of layers 0..3);
-//          acts[k] may alias acts[k-2] when activations are not kept;
+//          acts[k] may alias acts[k-2] when they are not to be kept (keep false);
 //   z    : [B][ny][nx][72] FP32.
 hipError_t launch_forward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                          void *const acts[4], float *z, hipStream_t st);
+                          void *const acts[4], bool keep, float *z, hipStream_t st);
 
 // Device descriptor of one learned solve (periodic nx x ny shallow water,
 // flat bed, fixed Delta t) for the work-list kernels.
 struct LSolve {
     float *q, *s1, *s2;      // state and stage buffers [3][n][n]
-    float *z;                // constrained coefficients [n][n][72] of the separate network pass
+    float *z;                // the separate network pass's output [n][n][72]
     const float *dt;         // fixed step (device)
     int *flags;              // two per-step flag slots
     unsigned long long *nfb, *redone;
@@ -84,7 +84,7 @@ struct LSolve {
 // step uses.
 struct LItem {
     int solve, tb_cnn, tb_st, parity;
-    int tb_h;  // first 16 x 16 tile in the layer-by-layer network pass's numbering
+    int tb_h;  // first tile of the register-weight network pass (net_tiles per solve)
 };
 constexpr int LTILE_CNN = 8;            // network pass tile side
 constexpr int LTILE_X = 32, LTILE_Y = 4;  // stage tile
@@ -93,32 +93,21 @@ inline int ltiles_st(int nx, int ny) { return ((nx + LTILE_X - 1) / LTILE_X) * (
 
 // Work-list launches over the listed solves (one != 0: exactly one solve,
 // tab[items[0].solve]).  Network pass: stage 1 reads q, stage 2 reads S1,
-// both write alpha to z; its workgroups (at most fused_max_grid()) stride
+// both write to z; its workgroups (at most fused_max_grid()) stride
 // over the network tiles.  Learned stage: MODE 0 with stage 1 or 2 (reads
-// alpha from z), MODE 2, 3 (as learned_stage), HLLE, over the stage tiles.
-hipError_t launch_forward_batch(int stage, const void *packed, const Norm &nrm, const Proj &pr, const LSolve *tab,
-                                const LItem *items, const int *nitems, int ntiles, hipStream_t st, int one = 0);
+// z), MODE 2, 3 (as learned_stage), HLLE, over the stage tiles.
+hipError_t launch_forward_batch(int stage, const void *packed, const Norm &nrm, const LSolve *tab, const LItem *items,
+                                const int *nitems, int ntiles, hipStream_t st);
 hipError_t launch_learned_batch(int mode, int stage, const LSolve *tab, const LItem *items, const int *nitems,
                                 int ntiles, const Proj &pr, hipStream_t st, int one = 0);
 // The forms recorded in graphs: wgs workgroups (set before each replay: the
 // list's stage tiles, and for the network pass at most fused_max_grid()),
 // the tile counts read from the list header list = {items, network tiles,
 // stage tiles, 0}.
-hipError_t launch_forward_batch_list(int stage, const void *packed, const Norm &nrm, const Proj &pr,
-                                     const LSolve *tab, const LItem *items, const int *list, int wgs,
-                                     hipStream_t st);
+hipError_t launch_forward_batch_list(int stage, const void *packed, const Norm &nrm, const LSolve *tab,
+                                     const LItem *items, const int *list, int wgs, hipStream_t st);
 hipError_t launch_learned_batch_list(int mode, int stage, const LSolve *tab, const LItem *items, const int *list,
                                      int wgs, const Proj &pr, hipStream_t st);
-// One layer (0..4) of the layer-by-layer network pass of the listed solves
-// (nx, ny multiples of 16) on 16 x 16 tiles, wgs workgroups (the list
-// header's fourth entry, 16 x 16 tiles): layer 0 reads q (stage 1) or S1
-// (stage 2) into act0, layers 1..3 go act0 -> act1 -> act0 -> act1, layer 4
-// writes alpha to each solve's z.  act0 and act1 hold [pixels][32] BF16,
-// solve d's pixels at offset tb_h * 256.  The same alpha as
-// launch_forward_batch_list.
-hipError_t launch_layer_list(int layer, int stage, const void *packed, const Norm &nrm, const Proj &pr,
-                             const LSolve *tab, const LItem *items, const int *list, int wgs, void *act0, void *act1,
-                             hipStream_t st);
 // Workgroups of the tiled network pass resident at once on the current
 // device: its launches use at most this many, each striding over tiles and
 // staging the weights once.
@@ -150,11 +139,27 @@ hipError_t launch_conv_learned_one(int stage, const void *packed, const Norm &nr
 
 // The same forward in one launch, without keeping activations: every
 // workgroup runs all five layers on an 8x8 tile of pixels (nx % 8 == 0,
-// ny % 8 == 0); z is bit-identical to launch_forward's.  With alpha != NULL
-// the output is the constrained coefficients base + P z per group of six
-// instead of z.
+// ny % 8 == 0); z is bit-identical to launch_forward's.
 hipError_t launch_forward_fused(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny, float *z,
-                                hipStream_t st, const Proj *alpha = nullptr);
+                                hipStream_t st);
+
+// Network pass of batches and large grids (net_kernels.hip): every workgroup
+// runs all five layers on tiles of up to 80 x 8 output pixels with its weights
+// in registers.  z, and with acts != NULL the activations acts[0..3] of every
+// layer, are bit-identical to the layer-by-layer pass's.  Takes nx % 16 == 0
+// and ny >= 8.
+inline bool net_takes(int nx, int ny) { return nx >= 16 && nx % 16 == 0 && ny >= 8; }
+hipError_t launch_net(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny, void *const acts[4],
+                      float *z, hipStream_t st);
+// The list form: z of the listed solves (sides multiples of 16) from q
+// (stage 1) or S1 (stage 2) to their z, over net_tiles tiles each (prefix
+// tb_h), their total in the list header's fourth entry; tiles: the same total
+// (a recorded launch's grid is set before each replay, to net_grid of it).
+__host__ __device__ inline int net_tile_cols(int nx) { return nx <= 80 ? nx : 64; }
+int net_tiles(int nx, int ny);
+int net_grid(int tiles);  // workgroups of a launch over that many tiles: at most one per CU
+hipError_t launch_net_list(int stage, const void *packed, const Norm &nrm, const LSolve *tab, const LItem *items,
+                           const int *list, int tiles, hipStream_t st);
 
 struct LearnedArgs;
 
@@ -162,8 +167,7 @@ struct LearnedArgs;
 struct StageBatch {
     const float *qs, *q0;
     float *out;
-    const float *z;          // raw coefficients, or (alpha != 0) constrained ones, [B][ny][nx][72]
-    int alpha;
+    const float *z;          // network output [B][ny][nx][72]
     int B, nx, ny;
     float rdx, rdy, g, h0;
     float a0, a1;
@@ -288,20 +292,19 @@ struct ENorm {
     float mean[4], inv_std[4];
 };
 hipError_t launch_pack_euler(const float *master, void *packed, hipStream_t st);
-// Forward of B solves [B][4][ny][nx] (nx % 16 == 0): act0, act1 are two
-// activation buffers [B][ny][nx][32] BF16 (ping-pong), z [B][ny][nx][96] FP32.
+// Forward of B solves [B][4][ny][nx] (nx % 16 == 0), as launch_forward: z
+// [B][ny][nx][96] FP32.
 hipError_t launch_forward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                void *act0, void *act1, float *z, hipStream_t st);
+                                void *const acts[4], bool keep, float *z, hipStream_t st);
 // The same forward in one launch (nx % 8 == 0, ny % 8 == 0): every
 // workgroup runs all five layers on 8 x 8 tiles in LDS; z is bit-identical.
 hipError_t launch_forward_euler_fused(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
                                       float *z, hipStream_t st);
-// The same forward keeping every layer's activation (acts[0..3], each
-// [B][ny][nx][32] BF16) for the backward.
-hipError_t launch_forward_euler_keep(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                     void *const acts[4], float *z, hipStream_t st);
+// launch_net for the Euler network.
+hipError_t launch_net_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
+                            void *const acts[4], float *z, hipStream_t st);
 // Backward of the Euler network, as the planar one's (dz BF16 [p][96], dq
-// [B][4][ny][nx], the activations of launch_forward_euler_keep).
+// [B][4][ny][nx], the activations of launch_forward_euler).
 hipError_t launch_backward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
                                  void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st);
 hipError_t launch_wgrads_euler(const WgradArgs &a, hipStream_t st);

@@ -150,23 +150,6 @@ __device__ __forceinline__ void barrier_after_weights()
     __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Constrained coefficients of one group of six (side 0: left state, 1: right
-// state), in place: alpha_k = base_k + sum_j P[k][j] z_j.
-__device__ __forceinline__ void alpha_group(float *zz, int side, const Proj &pr)
-{
-    float zv[6], al[6];
-#pragma unroll
-    for (int j = 0; j < 6; j++) zv[j] = zz[j];
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-        al[k] = pr.base[side * 6 + k];
-#pragma unroll
-        for (int j = 0; j < 6; j++) al[k] += pr.P[k * 6 + j] * zv[j];
-    }
-#pragma unroll
-    for (int k = 0; k < 6; k++) zz[k] = al[k];
-}
-
 constexpr int HT = 16;  // width of the layer-by-layer pass's tiles
 
 // First layer on a 16-pixel-wide, 4R-row tile (columns x0 .. x0+15, rows
@@ -403,141 +386,18 @@ static void launch_halo(const bf16 *in, const bf16 *wp, const float *bias, const
     else hipLaunchKernelGGL((conv_halo_kernel<KB, NT, EPI, 1>), grid, blk, 0, st, in, wp, bias, mask, out, ny, nx);
 }
 
-// ------------------------------------------- layer-by-layer work lists
-// The network pass of a round's listed learned solves, one launch per layer
-// on 16 x 16 tiles (nx, ny multiples of 16): workgroup w is tile w of the
-// list (items' tb_h prefix, binary search).  Solve d's activations are NHWC
-// [ny][nx][32] BF16 at pixel offset tb_h * 256 of two ping-pong buffers.
-// Layer 0 reads q (stage 1) or S1 (stage 2); the last layer writes
-// alpha = base + P z (per group of six) to d.z.  Per output the arithmetic is
-// the one-launch pass's, so alpha is the same bits.  The tile count is read
-// from the list header (list = {items, network tiles, stage tiles, 16 x 16
-// tiles}); workgroups past it exit.
-__device__ __forceinline__ LItem find_item_h(const LItem *__restrict__ items, int n, int w)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (items[mid].tb_h <= w) lo = mid;
-        else hi = mid - 1;
-    }
-    return items[lo];
-}
-
-template <int STAGE>
-__global__ __launch_bounds__(256) void conv_first_list_kernel(const LSolve *__restrict__ tab,
-                                                              const LItem *__restrict__ items,
-                                                              const int *__restrict__ list, const bf16 *wp,
-                                                              const float *bias, bf16 *act, Norm nrm)
-{
-    const int w = blockIdx.x;
-    if (w >= list[3]) return;
-    __shared__ bf16x8 s_w[32 * 32 / 8];
-    __shared__ bf16 s_q[3 * 18 * (HT + 2)];
-    const bf16x8 *gw = (const bf16x8 *)wp;
-    for (int i = threadIdx.x; i < 32 * 32 / 8; i += 256) s_w[i] = gw[i];
-    const LItem it = find_item_h(items, list[0], w);
-    const LSolve &d = tab[it.solve];
-    const int tile = w - it.tb_h, tx_n = d.nx / HT;
-    const int ty = tile / tx_n, tx = tile - ty * tx_n;
-    first_layer_tile<4>(STAGE == 1 ? d.q : d.s1, d.ny, d.nx, tx * HT, ty * HT, s_w, s_q, bias, nrm,
-                        act + (size_t)it.tb_h * HT * HT * 32);
-}
-
-// EPI 0: hidden layer (+ bias, ReLU, BF16 act); EPI 1: last layer (+ bias,
-// then alpha through LDS, FP32 [ny][nx][72] to d.z).
-template <int NT, int EPI>
-__global__ __launch_bounds__(256) void conv_halo_list_kernel(const LSolve *__restrict__ tab,
-                                                             const LItem *__restrict__ items,
-                                                             const int *__restrict__ list, const bf16 *wp,
-                                                             const float *bias, const bf16 *in, bf16 *out, Proj pr)
-{
-    using S = HaloShape<1, NT, 4>;
-    constexpr int ZB = EPI == 1 ? HT * HT * 72 * 4 : 0;  // the tile's z for the alpha epilogue
-    __shared__ __align__(16) char smem[S::BYTES > ZB ? S::BYTES : ZB];
-    const int w = blockIdx.x;
-    if (w >= list[3]) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, px = lane & 15;
-    const LItem it = find_item_h(items, list[0], w);
-    const LSolve &d = tab[it.solve];
-    const int tile = w - it.tb_h, tx_n = d.nx / HT;
-    const int ty = tile / tx_n, tx = tile - ty * tx_n;
-    const int x0 = tx * HT, y0 = ty * HT;
-    const size_t off = (size_t)it.tb_h * HT * HT;  // the solve's first pixel in the activation buffers
-    floatx4 acc[4][NT];
-    halo_conv<1, NT, 4>(in + off * 32, wp, d.ny, d.nx, x0, y0, smem, acc);
-    if (EPI == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const size_t p = off + (size_t)(y0 + wave * 4 + r) * d.nx + x0 + px;
-#pragma unroll
-            for (int t = 0; t < NT; t++) {
-                const int co0 = 16 * t + 4 * g;
-                bf16x4 o;
-#pragma unroll
-                for (int i = 0; i < 4; i++) o[i] = (bf16)__builtin_fmaxf(acc[r][t][i] + bias[co0 + i], 0.0f);
-                *(bf16x4 *)(out + p * 32 + co0) = o;
-            }
-        }
-    } else {
-        float *s_z = (float *)smem;  // [256 tile pixels][72]
-        __syncthreads();             // the MFMAs' LDS reads are done
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int pl = (wave * 4 + r) * HT + px;
-#pragma unroll
-            for (int t = 0; t < NT; t++) {
-                const int co0 = 16 * t + 4 * g;
-                if (co0 < 72) {
-                    floatx4 o;
-#pragma unroll
-                    for (int i = 0; i < 4; i++) o[i] = acc[r][t][i] + bias[co0 + i];
-                    *(floatx4 *)(s_z + pl * 72 + co0) = o;
-                }
-            }
-        }
-        __syncthreads();
-        for (int task = threadIdx.x; task < HT * HT * 12; task += 256) {
-            const int pl = task / 12, grp = task - pl * 12;
-            alpha_group(s_z + pl * 72 + grp * 6, (grp / 3) & 1, pr);
-        }
-        __syncthreads();
-        // each tile row's 16 x 72 values are contiguous in d.z
-        constexpr int RV = HT * 72 / 4;  // float4 per tile row
-        for (int i = threadIdx.x; i < HT * RV; i += 256) {
-            const int row = i / RV, c = i - row * RV;
-            ((float4 *)(d.z + ((size_t)(y0 + row) * d.nx + x0) * 72))[c] = ((const float4 *)(s_z + row * HT * 72))[c];
-        }
-    }
-}
-
-hipError_t launch_layer_list(int layer, int stage, const void *packed, const Norm &nrm, const Proj &pr,
-                             const LSolve *tab, const LItem *items, const int *list, int wgs, void *act0, void *act1,
-                             hipStream_t st)
-{
-    const Packed pk = packed_layout();
-    const char *P = (const char *)packed;
-    const dim3 grid((unsigned)(wgs > 0 ? wgs : 1)), blk(256);
-    bf16 *a[2] = {(bf16 *)act0, (bf16 *)act1};
-    const bf16 *w = (const bf16 *)(P + pk.w[layer]);
-    const float *b = (const float *)(P + pk.b[layer]);
-    if (layer == 0) {
-        if (stage == 1) hipLaunchKernelGGL(conv_first_list_kernel<1>, grid, blk, 0, st, tab, items, list, w, b, a[0], nrm);
-        else hipLaunchKernelGGL(conv_first_list_kernel<2>, grid, blk, 0, st, tab, items, list, w, b, a[0], nrm);
-    } else if (layer < 4) {
-        hipLaunchKernelGGL((conv_halo_list_kernel<2, 0>), grid, blk, 0, st, tab, items, list, w, b,
-                           (const bf16 *)a[(layer - 1) & 1], a[layer & 1], pr);
-    } else {
-        hipLaunchKernelGGL((conv_halo_list_kernel<5, 1>), grid, blk, 0, st, tab, items, list, w, b,
-                           (const bf16 *)a[1], (bf16 *)nullptr, pr);
-    }
-    return hipGetLastError();
-}
+constexpr int FT = 8;  // output tile side of the fused pass
 
 hipError_t launch_forward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                          void *const acts[4], float *z, hipStream_t st)
+                          void *const acts[4], bool keep, float *z, hipStream_t st)
 {
+    if (net_takes(nx, ny)) {
+        // 8 x 8 tiles of four waves while each gets a workgroup of its own
+        // (4 solves of 64^2: 9.5 us, 13.4 us in wide tiles; 6: 14.6 and 13.8)
+        if (!keep && ny % FT == 0 && (int64_t)B * (nx / FT) * (ny / FT) <= fused_max_grid())
+            return launch_forward_fused(packed, nrm, q, B, nx, ny, z, st);
+        return launch_net(packed, nrm, q, B, nx, ny, keep ? acts : nullptr, z, st);
+    }
     const Packed pk = packed_layout();
     const char *P = (const char *)packed;
     if (nx % HT) return hipErrorInvalidValue;
@@ -731,9 +591,14 @@ __global__ __launch_bounds__(256) void conv_first_euler_kernel(const float *q, c
     }
 }
 
-hipError_t launch_forward_euler_keep(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                     void *const acts[4], float *z, hipStream_t st)
+hipError_t launch_forward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
+                                void *const acts[4], bool keep, float *z, hipStream_t st)
 {
+    if (net_takes(nx, ny)) {
+        if (!keep && ny % FT == 0 && (int64_t)B * (nx / FT) * (ny / FT) <= fused_euler_grid())  // as launch_forward
+            return launch_forward_euler_fused(packed, nrm, q, B, nx, ny, z, st);
+        return launch_net_euler(packed, nrm, q, B, nx, ny, keep ? acts : nullptr, z, st);
+    }
     const EPacked pk = euler_packed_layout();
     const char *P = (const char *)packed;
     if (nx % HT) return hipErrorInvalidValue;
@@ -753,33 +618,6 @@ hipError_t launch_forward_euler_keep(const void *packed, const ENorm &nrm, const
     return hipGetLastError();
 }
 
-hipError_t launch_forward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                void *act0, void *act1, float *z, hipStream_t st)
-{
-    const EPacked pk = euler_packed_layout();
-    const char *P = (const char *)packed;
-    if (nx % HT) return hipErrorInvalidValue;
-    const int R = halo_rows(B, nx, ny);
-    const dim3 fg = halo_grid(B, nx, ny, R), blk(256);
-    const bf16 *w0 = (const bf16 *)(P + pk.w[0]);
-    const float *b0 = (const float *)(P + pk.b[0]);
-    bf16 *a0 = (bf16 *)act0, *a1 = (bf16 *)act1;
-    if (R == 4) hipLaunchKernelGGL(conv_first_euler_kernel<4>, fg, blk, 0, st, q, w0, b0, a0, ny, nx, nrm);
-    else if (R == 2) hipLaunchKernelGGL(conv_first_euler_kernel<2>, fg, blk, 0, st, q, w0, b0, a0, ny, nx, nrm);
-    else hipLaunchKernelGGL(conv_first_euler_kernel<1>, fg, blk, 0, st, q, w0, b0, a0, ny, nx, nrm);
-    bf16 *src = a0, *dst = a1;
-    for (int l = 1; l < 4; l++) {
-        launch_halo<1, 2, 0>(src, (const bf16 *)(P + pk.w[l]), (const float *)(P + pk.b[l]), nullptr, dst, B, nx, ny,
-                             st);
-        bf16 *t = src;
-        src = dst;
-        dst = t;
-    }
-    launch_halo<1, 6, 3>(src, (const bf16 *)(P + pk.w[4]), (const float *)(P + pk.b[4]), nullptr, (void *)z, B, nx,
-                         ny, st);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------- fused inference
 // All five layers for one FT x FT tile of output pixels in one workgroup.
 // Layer l's output is computed on the (FT + 2(4 - l))^2 region around the
@@ -790,7 +628,6 @@ hipError_t launch_forward_euler(const void *packed, const ENorm &nrm, const floa
 // the same order as the layer-by-layer pass (taps 0..8, K slices within a tap), with
 // the same bias, ReLU and BF16 rounding, so z is bit-identical to the
 // layer-by-layer pass; only the halo pixels are computed more than once.
-constexpr int FT = 8;            // output tile side
 static_assert(FT == LTILE_CNN, "network pass tile of the work lists");
 constexpr int FW_EL = 9 * 5 * 16 * 32;  // largest packed weight block (layer 4), bf16 elements
 
@@ -1089,19 +926,14 @@ __device__ __noinline__ float *redo_region(const float *xprev, float *xk, const 
     return sr;
 }
 
-// ALPHA: instead of z, write the constrained coefficients alpha = base + P z
-// of every group of six (same operation order as the learned stage's own
-// projection, so alpha is bit-identical to projecting this kernel's z).
 // One workgroup's network pass for the FO x FO output region at (x0 - FO +
 // FT, y0 - FO + FT): the FT x FT tile (FO = FT), or the tile and its low halo
-// row and column (FO = FT + 1).  OUT_Z writes raw z to zb, OUT_ALPHA the
-// constrained coefficients alpha = base + P z (same operation order as the
-// learned stage's own projection) to zb, OUT_Z_LDS keeps z in LDS
+// row and column (FO = FT + 1).  OUT_Z writes z to zb, OUT_Z_LDS keeps z in LDS
 // ([FO*FO][72], returned) and the tile's FP32 stage input with a 3-cell halo
 // in qf for a learned stage in the same workgroup, which projects each face's
 // coefficients itself (each group of six serves exactly one face).  load_w: stage the
 // weights (a workgroup's first tile; its later tiles find them in LDS).
-enum { OUT_Z = 0, OUT_ALPHA = 1, OUT_Z_LDS = 2 };
+enum { OUT_Z = 0, OUT_Z_LDS = 1 };
 // rd (OUT_Z_LDS only, or NULL): when rd->xprev is set and *rd->flag is not
 // zero, the input region is the plain redo of the previous step
 // (redo_region) instead of qb.  LO: cells of the output region before the
@@ -1110,14 +942,13 @@ enum { OUT_Z = 0, OUT_ALPHA = 1, OUT_Z_LDS = 2 };
 // same per-pixel arithmetic on more, smaller workgroups).
 template <int FO, int OUT, int LO = FO - FT, int TS = FT>
 __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, const Packed &pk, const Norm &nrm, float *zb,
-                                             int H, int W, int y0, int x0, const Proj &pr, bool load_w, float *qf,
+                                             int H, int W, int y0, int x0, bool load_w, float *qf,
                                              const PlainRedo *rd = nullptr);
 
 // Workgroups stride over the B x (H/FT) x (W/FT) tiles: a grid of at most the
 // workgroups resident at once stages the weights once per workgroup.
-template <bool ALPHA>
 __global__ __launch_bounds__(FNW * 64) void conv_fused_kernel(const float *q, const char *P, Packed pk, Norm nrm, float *z,
-                                                              int B, int H, int W, Proj pr)
+                                                              int B, int H, int W)
 {
     const int tx_n = W / FT, ty_n = H / FT, total = B * tx_n * ty_n;
     const size_t hw = (size_t)H * W;
@@ -1126,8 +957,8 @@ __global__ __launch_bounds__(FNW * 64) void conv_fused_kernel(const float *q, co
         if (!first) __syncthreads();  // the previous tile's LDS reads are done
         const int b = tile / (tx_n * ty_n);
         const int r = tile - b * tx_n * ty_n;
-        fused_tile<FT, ALPHA ? OUT_ALPHA : OUT_Z>(q + (size_t)b * 3 * hw, P, pk, nrm, z + (size_t)b * hw * 72, H, W,
-                                                  (r / tx_n) * FT, (r % tx_n) * FT, pr, first, nullptr);
+        fused_tile<FT, OUT_Z>(q + (size_t)b * 3 * hw, P, pk, nrm, z + (size_t)b * hw * 72, H, W,
+                                                  (r / tx_n) * FT, (r % tx_n) * FT, first, nullptr);
     }
 }
 
@@ -1138,37 +969,29 @@ template <int STAGE>
 __global__ __launch_bounds__(FNW * 64) void conv_fused_batch_kernel(const LSolve *__restrict__ tab,
                                                                     const LItem *__restrict__ items,
                                                                     const int *__restrict__ nitems, int ntiles,
-                                                                    int one, const char *P, Packed pk, Norm nrm,
-                                                                    Proj pr)
+                                                                    const char *P, Packed pk, Norm nrm)
 {
     const int total = ntiles > 0 ? ntiles : nitems[1];
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
         const bool first = w == (int)blockIdx.x;
         if (!first) __syncthreads();  // the previous tile's LDS reads are done
-        LItem it;
-        if (one) {
-            it = items[0];
-        } else {
-            const int n = *nitems;
-            int lo = 0, hi = n - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (items[mid].tb_cnn <= w) lo = mid;
-                else hi = mid - 1;
-            }
-            it = items[lo];
+        int lo = 0, hi = *nitems - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (items[mid].tb_cnn <= w) lo = mid;
+            else hi = mid - 1;
         }
+        const LItem it = items[lo];
         const LSolve &d = tab[it.solve];
         const int tile = w - it.tb_cnn, tx_n = d.nx / FT;
         const int ty = tile / tx_n, tx = tile - ty * tx_n;
-        fused_tile<FT, OUT_ALPHA>(STAGE == 1 ? d.q : d.s1, P, pk, nrm, d.z, d.ny, d.nx, ty * FT, tx * FT, pr, first,
-                                  nullptr);
+        fused_tile<FT, OUT_Z>(STAGE == 1 ? d.q : d.s1, P, pk, nrm, d.z, d.ny, d.nx, ty * FT, tx * FT, first, nullptr);
     }
 }
 
 template <int FO, int OUT, int LO, int TS>
 __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, const Packed &pk, const Norm &nrm, float *zb,
-                                             int H, int W, int y0, int x0, const Proj &pr, bool load_w, float *qf,
+                                             int H, int W, int y0, int x0, bool load_w, float *qf,
                                              const PlainRedo *rd)
 {
     static_assert((FO == TS && LO == 0) || (OUT == OUT_Z_LDS && ((FO == TS + 1 && LO == 1) || (FO == TS + 2 && LO == 1))),
@@ -1322,12 +1145,12 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
     // first store
     float *s_z = (float *)s_act;
     static_assert(FO * FO * 72 * 4 <= sizeof(s_act), "coefficient region fits over the activations");
-    constexpr bool ALPHA = OUT != OUT_Z;  // z staged in LDS
+    constexpr bool ZL = OUT != OUT_Z;  // z kept in LDS
     constexpr int NG4 = (FO * FO + 15) / 16;
     if constexpr (NG4 <= 3) {
         floatx4 acc[NG4];
         last_layer_by_tile<NG4, 5, FO, AS>(s_a1, s_w, wave, g, px, acc);
-        if (ALPHA) __syncthreads();  // every wave past its layer-4 reads of s_a1 before it holds z
+        if (ZL) __syncthreads();  // every wave past its layer-4 reads of s_a1 before it holds z
         const float *bias = s_bias + 128;
         const int co0 = 16 * wave + 4 * g;
         if (wave < 5 && co0 < 72) {
@@ -1338,7 +1161,7 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
                     floatx4 o;
 #pragma unroll
                     for (int i = 0; i < 4; i++) o[i] = acc[k][i] + bias[co0 + i];
-                    if (ALPHA) {
+                    if (ZL) {
                         *(floatx4 *)(s_z + p * 72 + co0) = o;
                     } else {
                         const int py = p / FO, pxx = p - py * FO;
@@ -1375,7 +1198,7 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
                 }
             }
         }
-        if (ALPHA) __syncthreads();  // every wave past its layer-4 reads of s_a1 before it holds z
+        if (ZL) __syncthreads();  // every wave past its layer-4 reads of s_a1 before it holds z
 #pragma unroll
         for (int k = 0; k < GPW; k++) {
             const int gi = wave + k * FNW, p = gi * 16 + px;
@@ -1388,30 +1211,14 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
                         floatx4 o;
 #pragma unroll
                         for (int i = 0; i < 4; i++) o[i] = acc[k][t][i] + bias[co0 + i];
-                        if (ALPHA) *(floatx4 *)(s_z + p * 72 + co0) = o;
+                        if (ZL) *(floatx4 *)(s_z + p * 72 + co0) = o;
                         else *(floatx4 *)(zb + ((size_t)(y0 + py) * W + x0 + pxx) * 72 + co0) = o;
                     }
                 }
             }
         }
     }
-    if (ALPHA) __syncthreads();
-    if (OUT == OUT_ALPHA) {
-        // FO^2 pixels x 12 groups of six, (axis*2 + side)*3 + var: alpha
-        // replaces z in place
-        for (int task = threadIdx.x; task < FO * FO * 12; task += FNW * 64) {
-            const int p = task / 12, grp = task - p * 12;
-            alpha_group(s_z + p * 72 + grp * 6, (grp / 3) & 1, pr);
-        }
-        __syncthreads();
-        // each tile row's 8 x 72 values, contiguous in the output, leave as
-        // 16-byte stores
-        constexpr int RV = TS * 72 / 4;  // float4 per tile row
-        for (int i = threadIdx.x; i < TS * RV; i += FNW * 64) {
-            const int row = i / RV, c = i - row * RV;
-            ((float4 *)(zb + ((size_t)(y0 + row) * W + x0) * 72))[c] = ((const float4 *)(s_z + row * TS * 72))[c];
-        }
-    }
+    if (ZL) __syncthreads();
     return s_z;
 }
 
@@ -2097,7 +1904,7 @@ __global__ __launch_bounds__(FNW * 64) void conv_learned_batch_kernel(const LSol
         const int ty = tile / tx_n, tx = tile - ty * tx_n;
         const float dt = d.dt[0];  // its latency behind the network pass
         float *s_z = fused_tile<FT + 1, OUT_Z_LDS>(STAGE == 1 ? d.q : d.s1, P, pk, nrm, nullptr, d.ny, d.nx, ty * FT,
-                                                   tx * FT, pr, first, s_qf);
+                                                   tx * FT, first, s_qf);
         learned_epilogue<STAGE, BL>(d, it, s_z, s_qf, pr, tx * FT, ty * FT, dt);
     }
 }
@@ -2157,7 +1964,7 @@ __global__ __launch_bounds__(FNW * 64) void conv_learned_one_kernel(LSolve d, in
             for (int v = 0; v < 3; v++) q0v[v] = d.q[idx + v * plane];
         }
         float *s_z = fused_tile<DIR ? TS + 2 : TS + 1, OUT_Z_LDS, 1, TS>(
-            STAGE == 1 ? d.q : d.s1, P, pk, nrm, nullptr, d.ny, d.nx, ty * TS, tx * TS, pr, first, s_qf, &rd);
+            STAGE == 1 ? d.q : d.s1, P, pk, nrm, nullptr, d.ny, d.nx, ty * TS, tx * TS, first, s_qf, &rd);
         learned_epilogue<STAGE, BL, DIR, TS>(d, it, s_z, s_qf, pr, tx * TS, ty * TS, dt0, sig, PRE ? q0v : nullptr);
         w += gridDim.x;
     } while (w < total);
@@ -2180,10 +1987,9 @@ int fused_max_grid()
     if (hipGetDevice(&dev) != hipSuccess) return 256;
     if (dev < 0 || dev >= 64) return 256;
     if (!cache[dev]) {
-        int cus = 0, a = 0, b = 0, c = 0, e = 0;
+        int cus = 0, a = 0, c = 0, e = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, conv_fused_kernel<true>, FNW * 64, 0) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, conv_fused_kernel<false>, FNW * 64, 0) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, conv_fused_kernel, FNW * 64, 0) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&c, conv_learned_batch_kernel<1>, FNW * 64, 0) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&e, conv_learned_batch_kernel<2>, FNW * 64, 0) != hipSuccess)
             return 256;
@@ -2230,7 +2036,7 @@ int fused_max_grid()
                                                          0) != hipSuccess)
             return 256;
         for (int i = 0; i < 6; i++) k4 = k4 < t[i] ? k4 : t[i];
-        int m = a < b ? a : b;
+        int m = a;
         m = m < k1 ? m : k1;
         m = m < k2 ? m : k2;
         m = m < k3 ? m : k3;
@@ -2246,34 +2052,32 @@ int fused_max_grid()
     return cache[dev];
 }
 
-hipError_t launch_forward_batch(int stage, const void *packed, const Norm &nrm, const Proj &pr, const LSolve *tab,
-                                const LItem *items, const int *nitems, int ntiles, hipStream_t st, int one)
+static hipError_t forward_batch_go(int stage, const void *packed, const Norm &nrm, const LSolve *tab,
+                                   const LItem *items, const int *nitems, int ntiles, int wgs, hipStream_t st)
 {
-    if (ntiles <= 0) return hipSuccess;
     const Packed pk = packed_layout();
-    const int cap = fused_max_grid(), g = ntiles < cap ? ntiles : cap;
     if (stage == 1)
-        hipLaunchKernelGGL(conv_fused_batch_kernel<1>, dim3(g), dim3(FNW * 64), 0, st, tab, items, nitems, ntiles,
-                           one, (const char *)packed, pk, nrm, pr);
+        hipLaunchKernelGGL(conv_fused_batch_kernel<1>, dim3(wgs), dim3(FNW * 64), 0, st, tab, items, nitems, ntiles,
+                           (const char *)packed, pk, nrm);
     else
-        hipLaunchKernelGGL(conv_fused_batch_kernel<2>, dim3(g), dim3(FNW * 64), 0, st, tab, items, nitems, ntiles,
-                           one, (const char *)packed, pk, nrm, pr);
+        hipLaunchKernelGGL(conv_fused_batch_kernel<2>, dim3(wgs), dim3(FNW * 64), 0, st, tab, items, nitems, ntiles,
+                           (const char *)packed, pk, nrm);
     return hipGetLastError();
 }
 
-hipError_t launch_forward_batch_list(int stage, const void *packed, const Norm &nrm, const Proj &pr,
-                                     const LSolve *tab, const LItem *items, const int *list, int wgs,
-                                     hipStream_t st)
+hipError_t launch_forward_batch(int stage, const void *packed, const Norm &nrm, const LSolve *tab, const LItem *items,
+                                const int *nitems, int ntiles, hipStream_t st)
+{
+    if (ntiles <= 0) return hipSuccess;
+    const int cap = fused_max_grid();
+    return forward_batch_go(stage, packed, nrm, tab, items, nitems, ntiles, ntiles < cap ? ntiles : cap, st);
+}
+
+hipError_t launch_forward_batch_list(int stage, const void *packed, const Norm &nrm, const LSolve *tab,
+                                     const LItem *items, const int *list, int wgs, hipStream_t st)
 {
     if (wgs <= 0) return hipErrorInvalidValue;
-    const Packed pk = packed_layout();
-    if (stage == 1)
-        hipLaunchKernelGGL(conv_fused_batch_kernel<1>, dim3(wgs), dim3(FNW * 64), 0, st, tab, items, list, 0, 0,
-                           (const char *)packed, pk, nrm, pr);
-    else
-        hipLaunchKernelGGL(conv_fused_batch_kernel<2>, dim3(wgs), dim3(FNW * 64), 0, st, tab, items, list, 0, 0,
-                           (const char *)packed, pk, nrm, pr);
-    return hipGetLastError();
+    return forward_batch_go(stage, packed, nrm, tab, items, list, 0, wgs, st);
 }
 
 hipError_t launch_conv_learned(int stage, const void *packed, const Norm &nrm, const Proj &pr, const LSolve *tab,
@@ -2367,17 +2171,13 @@ hipError_t launch_conv_learned_one(int stage, const void *packed, const Norm &nr
 }
 
 hipError_t launch_forward_fused(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny, float *z,
-                                hipStream_t st, const Proj *alpha)
+                                hipStream_t st)
 {
     if (nx % FT || ny % FT) return hipErrorInvalidValue;
     const int tiles = B * (nx / FT) * (ny / FT), cap = fused_max_grid();
     const dim3 g(tiles < cap ? tiles : cap);
-    if (alpha)
-        hipLaunchKernelGGL(conv_fused_kernel<true>, g, dim3(FNW * 64), 0, st, q, (const char *)packed,
-                           packed_layout(), nrm, z, B, ny, nx, *alpha);
-    else
-        hipLaunchKernelGGL(conv_fused_kernel<false>, g, dim3(FNW * 64), 0, st, q, (const char *)packed,
-                           packed_layout(), nrm, z, B, ny, nx, Proj{});
+    hipLaunchKernelGGL(conv_fused_kernel, g, dim3(FNW * 64), 0, st, q, (const char *)packed, packed_layout(), nrm, z, B,
+                       ny, nx);
     return hipGetLastError();
 }
 

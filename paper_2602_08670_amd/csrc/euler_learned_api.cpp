@@ -133,8 +133,9 @@ fv_status fv_euler_learned_forward(fv_euler_learned *e, const float *q, float *z
 {
     if (!e || !q || !z) return fail(FV_E_INVALID, "NULL argument");
     const fv_euler_learned_config &c = e->cfg;
-    hipError_t h = cnn::launch_forward_euler(e->ws + e->L.packed, e->nrm, q, c.B, c.nx, c.ny, e->ws + e->L.act0,
-                                             e->ws + e->L.act1, z, e->stream);
+    char *a0 = e->ws + e->L.act0, *a1 = e->ws + e->L.act1;
+    void *acts[4] = {a0, a1, a0, a1};
+    hipError_t h = cnn::launch_forward_euler(e->ws + e->L.packed, e->nrm, q, c.B, c.nx, c.ny, acts, false, z, e->stream);
     return h == hipSuccess ? FV_OK : hip_fail(h, "Euler network pass");
 }
 
@@ -171,12 +172,10 @@ fv_status fv_euler_learned_step(fv_euler_learned *e, float *q, int64_t nsteps)
     a.pr = e->pr;
     a.z = z;
     hipError_t h = hipSuccess;
-    // the network pass in one launch where the grid is whole 8 x 8 tiles
     const bool tiled = c.nx % 8 == 0 && c.ny % 8 == 0;
+    void *acts[4] = {ws + L.act0, ws + L.act1, ws + L.act0, ws + L.act1};
     auto net = [&](const float *in) {
-        return tiled ? cnn::launch_forward_euler_fused(ws + L.packed, e->nrm, in, c.B, c.nx, c.ny, z, e->stream)
-                     : cnn::launch_forward_euler(ws + L.packed, e->nrm, in, c.B, c.nx, c.ny, ws + L.act0, ws + L.act1,
-                                                 z, e->stream);
+        return cnn::launch_forward_euler(ws + L.packed, e->nrm, in, c.B, c.nx, c.ny, acts, false, z, e->stream);
     };
     // network pass and learned stage in one launch per stage where the grid
     // is whole 8 x 8 tiles and every tile gets a workgroup of its own (with
@@ -444,12 +443,12 @@ fv_status fv_euler_train_step(fv_euler_trainer *tr, const float *q0, const float
         a.parity = t & 1;
         void *a0[4] = {tr->act(t, 0, 0), tr->act(t, 0, 1), tr->act(t, 0, 2), tr->act(t, 0, 3)};
         void *a1[4] = {tr->act(t, 1, 0), tr->act(t, 1, 1), tr->act(t, 1, 2), tr->act(t, 1, 3)};
-        e = cnn::launch_forward_euler_keep(packed, net->nrm, tr->st(t), B, nx, ny, a0, tr->zb(t, 0), st);
+        e = cnn::launch_forward_euler(packed, net->nrm, tr->st(t), B, nx, ny, a0, true, tr->zb(t, 0), st);
         a.qs = tr->st(t); a.q0 = tr->st(t); a.out = tr->s1(t); a.z = tr->zb(t, 0);
         a.a0 = 0.f; a.a1 = 1.f; a.flagbit = 1; a.record = nullptr;
         if (e == hipSuccess) e = eln::stage(0, fl, a, st);
         if (e == hipSuccess)
-            e = cnn::launch_forward_euler_keep(packed, net->nrm, tr->s1(t), B, nx, ny, a1, tr->zb(t, 1), st);
+            e = cnn::launch_forward_euler(packed, net->nrm, tr->s1(t), B, nx, ny, a1, true, tr->zb(t, 1), st);
         a.qs = tr->s1(t); a.q0 = tr->st(t); a.out = S2; a.z = tr->zb(t, 1);
         a.a0 = 0.5f; a.a1 = 0.5f; a.flagbit = 2;
         if (e == hipSuccess) e = eln::stage(0, fl, a, st);

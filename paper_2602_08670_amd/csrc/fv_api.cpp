@@ -664,7 +664,7 @@ fv_status fv_model_forward(const fv_model *m, const float *q, int B, int nx, int
     char *sc = (char *)scratch;
     size_t half = need / 2;
     void *acts[4] = {sc, sc + half, sc, sc + half};
-    hipError_t e = cnn::launch_forward(m->packed, m->nrm, q, B, nx, ny, acts, z, m->stream);
+    hipError_t e = cnn::launch_forward(m->packed, m->nrm, q, B, nx, ny, acts, false, z, m->stream);
     return e == hipSuccess ? FV_OK : hip_fail(e, "network launch");
 }
 
@@ -715,7 +715,7 @@ static fv_status learned_step_impl(fv_solver *s, const fv_model *m, int64_t nste
     const int fl = c.flux == FV_FLUX_RUSANOV ? 1 : 0;  // kernel flux ids: 0 HLLE, 1 Rusanov
     hipError_t e = hipSuccess;
     if (fl == 0 && c.nx % 8 == 0 && c.ny % 8 == 0 &&
-        cnn::ltiles_cnn(c.nx, c.ny) < 4 * cnn::fused_max_grid()) {
+        cnn::ltiles_cnn(c.nx, c.ny) <= (blend || direct ? 4 * cnn::fused_max_grid() - 1 : 3 * cnn::fused_max_grid())) {
         // two launches per step, each the network pass with the learned
         // stage (the server's per-stage arithmetic, so bit-identical to the
         // same solve in a served mix): the step's output goes to the other
@@ -762,12 +762,12 @@ static fv_status learned_step_impl(fv_solver *s, const fv_model *m, int64_t nste
         const auto *tab = (const cnn::LSolve *)(B + LB_TAB);
         const auto *items0 = (const cnn::LItem *)(B + LB_ITEMS);
         const int *nit = (const int *)(B + LB_N);
-        const int tc = cnn::ltiles_cnn(c.nx, c.ny), ts = cnn::ltiles_st(c.nx, c.ny);
+        const int ts = cnn::ltiles_st(c.nx, c.ny);
         if (blend || direct) return fail(FV_E_UNSUPPORTED, "blend or direct: grid too large for the fused form");
         for (int64_t k = 0; k < nsteps && e == hipSuccess; k++, s->lsteps++) {
             const cnn::LItem *it = items0 + (s->lsteps & 1);
             for (int stage = 1; stage <= 2 && e == hipSuccess; stage++) {
-                e = cnn::launch_forward_batch(stage, m->packed, m->nrm, m->pr, tab, it, nit, tc, s->stream, 1);
+                e = cnn::launch_net(m->packed, m->nrm, stage == 1 ? q : S1, 1, c.nx, c.ny, nullptr, z, s->stream);
                 if (e == hipSuccess) e = cnn::launch_learned_batch(0, stage, tab, it, nit, ts, m->pr, s->stream, 1);
             }
             if (e == hipSuccess) e = cnn::launch_learned_batch(2, 0, tab, it, nit, ts, m->pr, s->stream, 1);
@@ -775,16 +775,12 @@ static fv_status learned_step_impl(fv_solver *s, const fv_model *m, int64_t nste
         }
         nsteps = 0;  // done; fall through to the statistics
     }
-    const bool fused = c.ny % 8 == 0;  // whole network in one launch per evaluation
     int *flags = (int *)(sm + SM_BAD);  // two slots: this step's and the next step's
     sb.redone = (unsigned long long *)(sm + SM_REDONE);
     sb.t = &s->ctl()->t;
     sb.steps = &s->ctl()->step;
-    // the tiled network pass also applies the projection: z then holds alpha
-    sb.alpha = fused ? 1 : 0;
     auto forward = [&](const float *in) {
-        return fused ? cnn::launch_forward_fused(m->packed, m->nrm, in, 1, c.nx, c.ny, z, s->stream, &m->pr)
-                     : cnn::launch_forward(m->packed, m->nrm, in, 1, c.nx, c.ny, acts, z, s->stream);
+        return cnn::launch_forward(m->packed, m->nrm, in, 1, c.nx, c.ny, acts, false, z, s->stream);
     };
     for (int64_t k = 0; k < nsteps && e == hipSuccess; k++, s->lsteps++) {
         sb.bad = flags + (s->lsteps & 1);
@@ -860,12 +856,8 @@ static fv_status raw_head_step(fv_solver *s, const fv_model *m, int64_t nsteps, 
     sb.t = &s->ctl()->t;
     sb.steps = &s->ctl()->step;
     const int fl = c.flux == FV_FLUX_RUSANOV ? 1 : 0;
-    // the network's raw output: one launch per evaluation (the tiled pass,
-    // bit-identical) where the grid allows it, else one launch per layer
-    const bool tiled = c.ny % 8 == 0;
     auto forward = [&](const float *in) {
-        return tiled ? cnn::launch_forward_fused(m->packed, m->nrm, in, 1, c.nx, c.ny, z, s->stream, nullptr)
-                     : cnn::launch_forward(m->packed, m->nrm, in, 1, c.nx, c.ny, acts, z, s->stream);
+        return cnn::launch_forward(m->packed, m->nrm, in, 1, c.nx, c.ny, acts, false, z, s->stream);
     };
     hipError_t e = hipSuccess;
     for (int64_t k = 0; k < nsteps && e == hipSuccess; k++, s->lsteps++) {

@@ -13,6 +13,23 @@ using fvk::SweV;
 
 __device__ __forceinline__ int pwrap(int i, int n) { return ((i % n) + n) % n; }
 
+// Constrained coefficients of one group of six (side 0: left state, 1: right
+// state), in place: alpha_k = base_k + sum_j P[k][j] z_j.
+__device__ __forceinline__ void alpha_group(float *zz, int side, const Proj &pr)
+{
+    float zv[6], al[6];
+#pragma unroll
+    for (int j = 0; j < 6; j++) zv[j] = zz[j];
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        al[k] = pr.base[side * 6 + k];
+#pragma unroll
+        for (int j = 0; j < 6; j++) al[k] += pr.P[k * 6 + j] * zv[j];
+    }
+#pragma unroll
+    for (int k = 0; k < 6; k++) zz[k] = al[k];
+}
+
 // Face states of one face from the six stencil values st[v][0..5] (cells
 // i-2..i+3 along the normal).  MODE 0: learned with fallback; MODE 1: MINMOD.
 // AL: zc already holds alpha = base + P z (projected by the network pass).

@@ -59,7 +59,7 @@ struct LearnedArgs {
 // stage's.
 // BL (MODE 0 only): every face's flux is the flux-limiter blend of the
 // learned flux and the flux of the two cell averages (blend_flux).
-template <int MODE, int FLUX, bool AL, bool DIR = false, bool BL = false>
+template <int MODE, int FLUX, bool DIR = false, bool BL = false>
 __device__ __forceinline__ void learned_tile(const LearnedArgs &a, const int b, const int x0, const int y0,
                                              const bool first)
 {
@@ -165,7 +165,7 @@ __device__ __forceinline__ void learned_tile(const LearnedArgs &a, const int b, 
 #pragma unroll
             for (int k = 0; k < 6; k++) st[v][k] = s_q[v][xj + 3][xi + k];
         float QL[3], QR[3], F[3];
-        int c = DIR ? face_states_direct(st, zx, zx + 3, a.sig, QL, QR) : face_states<FS, AL>(st, zx, a.pr, QL, QR);
+        int c = DIR ? face_states_direct(st, zx, zx + 3, a.sig, QL, QR) : face_states<FS>(st, zx, a.pr, QL, QR);
         // each face is counted once: as the left face of a cell of this tile
         if (xi < TX && x0 + xi < nx && y0 + xj < ny) nfb += c;
         flux3<FLUX, 0>(QL, QR, a.ph, F);
@@ -180,7 +180,7 @@ __device__ __forceinline__ void learned_tile(const LearnedArgs &a, const int b, 
 #pragma unroll
             for (int k = 0; k < 6; k++) st[v][k] = s_q[v][yj + k][yi + 3];
         float QL[3], QR[3], F[3];
-        int c = DIR ? face_states_direct(st, zy, zy + 3, a.sig, QL, QR) : face_states<FS, AL>(st, zy, a.pr, QL, QR);
+        int c = DIR ? face_states_direct(st, zy, zy + 3, a.sig, QL, QR) : face_states<FS>(st, zy, a.pr, QL, QR);
         if (yj < TY && y0 + yj < ny && x0 + yi < nx) nfb += c;
         flux3<FLUX, 1>(QL, QR, a.ph, F);
         if (BL) blend_flux<FLUX, 1>(st, a.ph, F);
@@ -219,17 +219,17 @@ __device__ __forceinline__ void learned_tile(const LearnedArgs &a, const int b, 
     }
 }
 
-template <int MODE, int FLUX, bool AL = false, bool DIR = false, bool BL = false>
+template <int MODE, int FLUX, bool DIR = false, bool BL = false>
 __global__ __launch_bounds__(256) void learned_stage_kernel(LearnedArgs a)
 {
-    learned_tile<MODE, FLUX, AL, DIR, BL>(a, blockIdx.z, blockIdx.x * LTILE_X, blockIdx.y * LTILE_Y,
+    learned_tile<MODE, FLUX, DIR, BL>(a, blockIdx.z, blockIdx.x * LTILE_X, blockIdx.y * LTILE_Y,
                                       blockIdx.x == 0 && blockIdx.y == 0);
 }
 
 // Work-list form over a table of solves of any size (serving, and single
 // solves as a batch of one): workgroup w finds its solve by binary search
 // over the items' first stage tile.  MODE 0 with STAGE 1 or 2 (the learned
-// stage after a separate network pass that wrote alpha to z), MODE 2 and 3
+// stage after a separate network pass), MODE 2 and 3
 // (the end of a learned step: commit or plain stage 1; plain stage 2 and
 // bookkeeping).  ntiles == 0: the tile count is read from the list header (nitems[2]; graph
 // replay).
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void learned_batch_kernel(const LSolve *__rest
     const int tile = w - it.tb_st;
     const int tiles_x = (d.nx + LTILE_X - 1) / LTILE_X;
     const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    learned_tile<MODE, fvk::HLLE, true>(a, 0, tx * LTILE_X, ty * LTILE_Y, tile == 0);
+    learned_tile<MODE, fvk::HLLE>(a, 0, tx * LTILE_X, ty * LTILE_Y, tile == 0);
 }
 
 static hipError_t learned_batch_go(int mode, int stage, dim3 g, const LSolve *tab, const LItem *items,
@@ -376,21 +376,18 @@ hipError_t learned_stage(int mode, int flux, const StageBatch &sb, hipStream_t s
     a.steps = sb.steps;
     for (int v = 0; v < 3; v++) a.sig[v] = sb.sig[v];
     if ((mode == 2 && a.commit_src && !a.commit_dst) || (mode == 3 && !a.bad_next)) return hipErrorInvalidValue;
-    if ((sb.direct || sb.blend) && (mode != 0 || sb.alpha)) return hipErrorInvalidValue;
+    if ((sb.direct || sb.blend) && mode != 0) return hipErrorInvalidValue;
     if (sb.direct && sb.blend) return hipErrorInvalidValue;
     dim3 grid((a.nx + LTILE_X - 1) / LTILE_X, (a.ny + LTILE_Y - 1) / LTILE_Y, a.B), blk(256);
     const bool rus = flux == fvk::RUSANOV;
     switch (mode) {
     case 0:
         if (sb.direct) {
-            if (rus) hipLaunchKernelGGL((learned_stage_kernel<0, fvk::RUSANOV, false, true>), grid, blk, 0, st, a);
-            else hipLaunchKernelGGL((learned_stage_kernel<0, fvk::HLLE, false, true>), grid, blk, 0, st, a);
-        } else if (sb.blend) {
-            if (rus) hipLaunchKernelGGL((learned_stage_kernel<0, fvk::RUSANOV, false, false, true>), grid, blk, 0, st, a);
-            else hipLaunchKernelGGL((learned_stage_kernel<0, fvk::HLLE, false, false, true>), grid, blk, 0, st, a);
-        } else if (sb.alpha) {
             if (rus) hipLaunchKernelGGL((learned_stage_kernel<0, fvk::RUSANOV, true>), grid, blk, 0, st, a);
             else hipLaunchKernelGGL((learned_stage_kernel<0, fvk::HLLE, true>), grid, blk, 0, st, a);
+        } else if (sb.blend) {
+            if (rus) hipLaunchKernelGGL((learned_stage_kernel<0, fvk::RUSANOV, false, true>), grid, blk, 0, st, a);
+            else hipLaunchKernelGGL((learned_stage_kernel<0, fvk::HLLE, false, true>), grid, blk, 0, st, a);
         } else {
             if (rus) hipLaunchKernelGGL((learned_stage_kernel<0, fvk::RUSANOV>), grid, blk, 0, st, a);
             else hipLaunchKernelGGL((learned_stage_kernel<0, fvk::HLLE>), grid, blk, 0, st, a);

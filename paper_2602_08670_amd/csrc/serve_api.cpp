@@ -104,7 +104,7 @@ struct fv_server {
     hipStream_t stream;
     std::chrono::steady_clock::time_point t0;
     // pool regions
-    size_t tab_off, items_off, nitems_off, scratch_off, ltab_off, litems_off, lnitems_off, act_off, heap_off;
+    size_t tab_off, items_off, nitems_off, scratch_off, ltab_off, litems_off, lnitems_off, heap_off;
     std::map<size_t, size_t> free_list;  // offset -> size
     // host side
     std::deque<Req *> queue;
@@ -123,8 +123,8 @@ struct fv_server {
     std::map<int, RoundGraph> graphs;
     int64_t rounds = 0, replays = 0, grid_updates = 0, layered_rounds = 0;
     int cnn_cap = 256;  // most workgroups of a network-pass launch
-    int split_at = 1024;  // network tiles from which a round's learned steps use separate launches
-    int layered_at = 768;  // 16 x 16 tiles from which such a round's network pass runs layer by layer (-1: never)
+    int split_at = 0;    // network tiles from which a round's learned steps use separate launches (0: by the round)
+    int layered_at = 1;  // 16 x 16 tiles from which such a round's network pass runs on wide tiles (-1: never)
     double launch_s = 0, wait_s = 0;  // host time enqueueing rounds' work, and waiting for it
     double capture_s = 0;             // host time capturing and instantiating graphs
     double admit_s = 0, retire_s = 0;  // host time admitting requests and retiring finished ones
@@ -183,7 +183,7 @@ void free_host(fv_server *s)
 // headers on the device: plain {items, tiles}, learned {items, network
 // tiles, stage tiles, 0}
 constexpr int HDR = 2, LHDR = 4;
-constexpr size_t ACT_BYTES = 2 * 32 * 2;  // per cell: two BF16 32-channel activations
+constexpr size_t ACT_BYTES = 2 * 32 * 2;  // per cell set aside: two BF16 32-channel activations
 size_t items_capacity(const fv_server_config *c) { return (size_t)c->steps_per_round * 2 * c->max_solves; }
 
 fv_status validate(const fv_server_config *c)
@@ -348,7 +348,7 @@ fv_status admit(fv_server *s, Req *q, std::vector<Req *> &need_h0)
 // Launches of steps 0..nsteps-1 of a round over the uploaded lists, kinds
 // of work in mask (1 SWE, 2 Euler, 4 learned, 8 learned steps with the
 // network pass and the learned stage as separate launches, 16 that network
-// pass layer by layer).  rec == NULL: direct launches
+// pass on wide tiles).  rec == NULL: direct launches
 // of one workgroup per tile with the given per-list tile counts, empty lists
 // skipped.  rec != NULL (graph capture): every launch of the mask, the tile
 // counts read from the list headers, each node recorded in rec; its grid is
@@ -396,9 +396,9 @@ hipError_t enqueue_steps(fv_server *s, int mask, int nsteps, const int *grids, c
         if (!(mask & 4) || e != hipSuccess || (!rec && !lgrid_st[k])) continue;
         // learned solves: the network pass and learned stage of every
         // learned solve in one launch per stage (coefficients on chip), or,
-        // with mask bit 8, a network-pass launch writing alpha (with mask
-        // bit 16: five launches, one per layer) and a learned-stage launch
-        // per stage; then commit-or-redo and redo.
+        // with mask bit 8, a network-pass launch (with mask bit 16: on
+        // wide tiles) and a learned-stage launch per stage; then
+        // commit-or-redo and redo.
         // Kind -2: fused pass, -1: network pass, >= 0: learned-stage mode.
         const cnn::LItem *it = d_litems + (size_t)k * ncap;
         const int *hdr = d_lnitems + (size_t)k * LHDR;
@@ -409,24 +409,19 @@ hipError_t enqueue_steps(fv_server *s, int mask, int nsteps, const int *grids, c
         for (int j = 0; j < nl && e == hipSuccess; j++) {
             const int md = split ? smode[j] : fmode[j], sg = split ? sstg[j] : fstg[j];
             if (md == -1 && (mask & 16)) {
-                void *a0 = P + s->act_off, *a1 = P + s->act_off + (size_t)s->cfg.act_pixels * (ACT_BYTES / 2);
-                for (int layer = 0; layer < 5 && e == hipSuccess; layer++) {
-                    e = cnn::launch_layer_list(layer, sg, m->packed, m->nrm, m->pr, ltab, it, hdr,
-                                               rec ? 1 : lgrid_h[k], a0, a1, s->stream);
-                    if (e == hipSuccess && rec) e = record(3, k);
-                }
+                e = cnn::launch_net_list(sg, m->packed, m->nrm, ltab, it, hdr, rec ? 1 : lgrid_h[k], s->stream);
+                if (e == hipSuccess && rec) e = record(3, k);
                 continue;
             }
             if (!rec) {
                 if (md == -2) e = cnn::launch_conv_learned(sg, m->packed, m->nrm, m->pr, ltab, it, hdr, lgrid_cnn[k],
                                                            s->stream);
-                else if (md == -1) e = cnn::launch_forward_batch(sg, m->packed, m->nrm, m->pr, ltab, it, hdr,
-                                                                 lgrid_cnn[k], s->stream);
+                else if (md == -1) e = cnn::launch_forward_batch(sg, m->packed, m->nrm, ltab, it, hdr, lgrid_cnn[k],
+                                                                 s->stream);
                 else e = cnn::launch_learned_batch(md, sg, ltab, it, hdr, lgrid_st[k], m->pr, s->stream);
             } else {
                 if (md == -2) e = cnn::launch_conv_learned_list(sg, m->packed, m->nrm, m->pr, ltab, it, hdr, 1, s->stream);
-                else if (md == -1) e = cnn::launch_forward_batch_list(sg, m->packed, m->nrm, m->pr, ltab, it, hdr, 1,
-                                                                      s->stream);
+                else if (md == -1) e = cnn::launch_forward_batch_list(sg, m->packed, m->nrm, ltab, it, hdr, 1, s->stream);
                 else e = cnn::launch_learned_batch_list(md, sg, ltab, it, hdr, 1, m->pr, s->stream);
                 if (e == hipSuccess) e = record(md < 0 ? 1 : 2, k);
             }
@@ -474,7 +469,7 @@ hipError_t set_grids(fv_server *s, RoundGraph *rg, const int *grids, const int *
         int want;
         if (n.kind == 0) want = grids[n.idx] ? fvk::xcd_grid(grids[n.idx]) : 8;
         else if (n.kind == 1) want = lgrid_cnn[n.idx] ? (lgrid_cnn[n.idx] < s->cnn_cap ? lgrid_cnn[n.idx] : s->cnn_cap) : 1;
-        else if (n.kind == 3) want = lgrid_h[n.idx] ? lgrid_h[n.idx] : 1;
+        else if (n.kind == 3) want = lgrid_h[n.idx] ? cnn::net_grid(lgrid_h[n.idx]) : 1;
         else want = lgrid_st[n.idx] ? lgrid_st[n.idx] : 1;
         if ((int)n.p.gridDim.x == want) continue;
         n.p.gridDim.x = (unsigned)want;
@@ -516,7 +511,6 @@ fv_status fv_server_create(const fv_server_config *cfg, void *pool, size_t pool_
     s->ltab_off = s->scratch_off + align256(scratch_bytes(cfg));
     s->litems_off = s->ltab_off + align256(sizeof(cnn::LSolve) * cfg->max_solves);
     s->lnitems_off = s->litems_off + align256(litems_capacity(cfg) * sizeof(cnn::LItem));
-    s->act_off = s->lnitems_off + align256((size_t)cfg->steps_per_round * LHDR * sizeof(int));
     s->heap_off = ov;
     s->free_list[s->heap_off] = pool_bytes - s->heap_off;
     s->h_tab.assign(cfg->max_solves, fvk::BatchSolve{});
@@ -532,8 +526,8 @@ fv_status fv_server_create(const fv_server_config *cfg, void *pool, size_t pool_
         return hip_fail(e, "pinned work-list buffers");
     }
     if (cfg->model) s->cnn_cap = cnn::fused_max_grid();
-    s->split_at = cfg->learned_split > 0 ? cfg->learned_split : 4 * s->cnn_cap;
-    s->layered_at = cfg->learned_layered > 0 ? cfg->learned_layered : (cfg->learned_layered == 0 ? 768 : -1);
+    s->split_at = cfg->learned_split;
+    s->layered_at = cfg->learned_layered ? cfg->learned_layered : 1;
     if (!stream) {
         // graphs cannot be captured on the null stream: the server then
         // runs on a stream of its own (default priority)
@@ -680,7 +674,8 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
     const size_t ncap = (size_t)s->cfg.max_solves;
     std::vector<int> counts((size_t)K * 2, 0), grids((size_t)K * 2, 0);
     std::vector<int> lcounts((size_t)K, 0), lgrid_cnn((size_t)K, 0), lgrid_st((size_t)K, 0), lgrid_h((size_t)K, 0);
-    bool all16 = true;  // every learned side a multiple of 16 (the layer-by-layer pass's tiles)
+    bool all16 = true;  // every learned side a multiple of 16 (the wide-tile pass's)
+    int64_t tiles16 = 0;  // 16 x 16 tiles of the first step
     for (int k = 0; k < K; k++)
         for (Req *q : s->active) {
             if (q->r.steps - q->done_steps <= k) continue;
@@ -698,8 +693,12 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
                 lcounts[k]++;
                 lgrid_cnn[k] += tc;
                 lgrid_st[k] += ts;
-                if (q->r.n % 16) all16 = false;
-                else lgrid_h[k] += (q->r.n / 16) * (q->r.n / 16);
+                if (!cnn::net_takes(q->r.n, q->r.n)) {
+                    all16 = false;
+                } else {
+                    lgrid_h[k] += cnn::net_tiles(q->r.n, q->r.n);
+                    if (k == 0) tiles16 += (int64_t)(q->r.n / 16) * (q->r.n / 16);
+                }
                 continue;
             }
             int type = q->r.eqn == FV_EULER ? 1 : 0;
@@ -722,15 +721,14 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
         if (m) nsteps = k + 1;
         mask |= m;
     }
-    // many learned tiles: separate network-pass and learned-stage launches
-    // (the network pass then strides over tiles at full occupancy of the
-    // learned stage); few: one launch per stage, coefficients on chip
-    if ((mask & 4) && lgrid_cnn[0] >= s->split_at) mask |= 8;
-    // many more: the network pass layer by layer (activations in the pool's
-    // scratch; a step's lists only shrink over the round)
-    if ((mask & 8) && all16 && s->layered_at > 0 && lgrid_h[0] >= s->layered_at &&
-        (uint64_t)lgrid_h[0] * 256 <= s->cfg.act_pixels)
-        mask |= 16;
+    // many learned tiles: separate network-pass and learned-stage launches,
+    // the network pass on wide tiles with its weights in registers where
+    // every side allows it; few: one launch per stage, coefficients on chip.
+    // A fourth round of 8 x 8 tiles (11.5 us each) costs more than the wide
+    // tiles and the separate stage; with 8 x 8 tiles either way, the fifth.
+    const bool wide = all16 && s->layered_at > 0 && tiles16 >= s->layered_at;
+    const int split = s->split_at ? s->split_at : wide ? 3 * s->cnn_cap + 1 : 4 * s->cnn_cap;
+    if ((mask & 4) && lgrid_cnn[0] >= split) mask |= wide ? 8 | 16 : 8;
     for (size_t li = 0; li < counts.size(); li++) {
         s->h_nitems[li * HDR] = counts[li];
         s->h_nitems[li * HDR + 1] = grids[li];

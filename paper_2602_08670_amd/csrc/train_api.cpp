@@ -220,11 +220,11 @@ fv_status fv_train_step(fv_trainer *tr, const float *q0, const float *targets, i
     for (int t = 0; t < T && e == hipSuccess; t++) {
         void *a0[4] = {tr->act(t, 0, 0), tr->act(t, 0, 1), tr->act(t, 0, 2), tr->act(t, 0, 3)};
         void *a1[4] = {tr->act(t, 1, 0), tr->act(t, 1, 1), tr->act(t, 1, 2), tr->act(t, 1, 3)};
-        e = cnn::launch_forward(tr->m->packed, tr->m->nrm, tr->st(t), B, nx, ny, a0, tr->zb(t, 0), st);
+        e = cnn::launch_forward(tr->m->packed, tr->m->nrm, tr->st(t), B, nx, ny, a0, true, tr->zb(t, 0), st);
         sb.qs = tr->st(t); sb.q0 = tr->st(t); sb.out = tr->s1(t); sb.z = tr->zb(t, 0);
         sb.a0 = 0.f; sb.a1 = 1.f; sb.flagbit = 1; sb.direct = c.direct; sb.blend = c.blend;
         if (e == hipSuccess) e = cnn::learned_stage(0, fl, sb, st);
-        if (e == hipSuccess) e = cnn::launch_forward(tr->m->packed, tr->m->nrm, tr->s1(t), B, nx, ny, a1, tr->zb(t, 1), st);
+        if (e == hipSuccess) e = cnn::launch_forward(tr->m->packed, tr->m->nrm, tr->s1(t), B, nx, ny, a1, true, tr->zb(t, 1), st);
         sb.qs = tr->s1(t); sb.q0 = tr->st(t); sb.out = S2; sb.z = tr->zb(t, 1);
         sb.a0 = 0.5f; sb.a1 = 0.5f; sb.flagbit = 2;
         if (e == hipSuccess) e = cnn::learned_stage(0, fl, sb, st);

@@ -584,10 +584,11 @@ class Server:
         tiles in a round's first step from which the round runs the network
         pass and the learned stage as separate launches (0: the library's
         default).  learned_layered: 16 x 16 tiles from which such a round's
-        network pass runs layer by layer (0: the library's default, -1:
-        never); act_pixels: cells of its activation scratch, 128 bytes each
-        out of the pool (None: with a model, an eighth of the pool up to 64 Mi
-        cells; without, none).  max_bypass: rounds a queued request may go
+        network pass runs on wide tiles (0: any number, -1: never);
+        act_pixels: cells of activation scratch set aside in the pool, 128
+        bytes each (None: with a model, an eighth of the pool up to 64 Mi
+        cells; without, none; the network pass keeps its activations on chip,
+        so 0 serves as well).  max_bypass: rounds a queued request may go
         without fitting before nothing behind it is admitted (0: the
         library's default, -1: never)."""
         import torch

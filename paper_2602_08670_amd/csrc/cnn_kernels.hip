@@ -752,42 +752,106 @@ __device__ __forceinline__ void last_layer_by_tile(const bf16x8 *act, const bf16
     }
 }
 
-// A layer's packed weights (NB blocks of 64 octets) straight from global
-// memory into LDS, one global_load_lds_dwordx4 per 1 KB block, blocks
-// wave, wave + FNW, ...: lane l of a block writes the block's octet l; with
-// PERM that is octet (l & 15, l >> 4) of the packed row-major fragment
-// (the K-block-major order wfrag reads), else octet l.  These writes are
-// not tracked by the compiler's waits: barrier_after_weights() waits for
-// them before any LDS read.
+// Global memory straight into LDS, N x 4 bytes per lane to lds + 4 N lane.
+// In assembly: the compiler waits for every load into LDS of its own before
+// any access to LDS, which made the first layer wait for all five layers'
+// weights: 5 030 of a 4 x 4-tile workgroup's 16 500 cycles passed before it (a
+// 64^2 learned step's launch 10.4 -> 9.6 us, a four-solve Euler one 17.2 ->
+// 16.8 us).  It counts none of these, so
+// wait_loads<LEFT> / barrier_loads<LEFT> stand before each use of what they
+// bring, and the code between them and the first use of a compiler's own load
+// waits for both.
+template <int N> __device__ __forceinline__ void load_lds(const void *g, const void *lds)
+{
+    const unsigned off = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)lds;
+    if (N == 4)
+        __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(off), "v"(g) : "memory");
+    else
+        __asm__ volatile("s_nop 0\n\tglobal_load_lds_dword %1, off" ::"{m0}"(off), "v"(g) : "memory");
+}
+// At most LEFT of this wave's loads are still under way (they end in order).
+template <int LEFT> __device__ __forceinline__ void wait_loads()
+{
+    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory");
+}
+// The same, this wave's LDS accesses done, and every other wave as far.
+template <int LEFT> __device__ __forceinline__ void barrier_loads()
+{
+    __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
+
+// A layer's packed weights (NB blocks of 64 octets) straight into LDS, a 1 KB
+// block per load, blocks wave, wave + FNW, ... (at least NB / FNW loads of a
+// wave): lane l of a block writes the block's octet l; with PERM that is octet
+// (l & 15, l >> 4) of the packed row-major fragment (the K-block-major order
+// wfrag reads), else octet l.
 template <int NB, bool PERM = true>
 __device__ __forceinline__ void dma_weights(const char *g, bf16x8 *s, int wave, int lane)
 {
-    for (int b = wave; b < NB; b += FNW) {  // wave-uniform
+    auto block = [&](int b) {
         const unsigned i = PERM ? ((unsigned)b * 64 | (unsigned)(lane & 15) << 2 | (unsigned)(lane >> 4))
                                 : (unsigned)b * 64 + lane;
-        __builtin_amdgcn_global_load_lds((const void *)(g + (size_t)i * 16), (void *)(s + b * 64), 16, 0, 0);
+        load_lds<4>(g + (size_t)i * 16, s + b * 64);
+    };
+#pragma unroll
+    for (int k = 0; k < NB / FNW; k++) block(wave + k * FNW);
+    if (NB % FNW && wave < NB % FNW) block(wave + NB / FNW * FNW);  // wave-uniform
+}
+
+// A word that the launches before this one have written, the same for the
+// whole workgroup: a scalar load, waited for apart from the vector loads.
+__device__ __forceinline__ int scalar_int(const int *p)
+{
+    return *(const __attribute__((address_space(4))) int *)(size_t)p;
+}
+
+// v[i] of a kernel argument's array for a lane's own i: by selects of scalars,
+// where an indexed read would be a vector load among the weights'.
+template <int N> __device__ __forceinline__ int pick(const size_t *v, int i)
+{
+    int r = __builtin_amdgcn_readfirstlane((int)v[0]);
+#pragma unroll
+    for (int k = 1; k < N; k++) r = i == k ? __builtin_amdgcn_readfirstlane((int)v[k]) : r;
+    return r;
+}
+template <int N> __device__ __forceinline__ float pick(const float *v, int i)
+{
+    int r = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v[0]));
+#pragma unroll
+    for (int k = 1; k < N; k++) r = i == k ? __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v[k])) : r;
+    return __builtin_bit_cast(float, r);
+}
+
+// All five layers' biases straight into LDS ([4][32] hidden, then the last
+// layer's NL4), one per thread.
+template <int NL4, class PK> __device__ __forceinline__ void dma_biases(const char *P, const PK &pk, float *s, int wave)
+{
+    static_assert(4 * 32 + NL4 <= FNW * 64, "one bias per thread");
+    const int t = threadIdx.x;
+    if (t < 4 * 32 + NL4) {
+        const int off = pick<5>(pk.b, t < 128 ? t >> 5 : 4);
+        load_lds<1>(P + off + 4 * (t < 128 ? (t & 31) : t - 128), s + 64 * wave);
     }
 }
 
-// All five layers' biases in LDS ([4][32] hidden, then the last layer's
-// NL4), so that no layer waits on a global load for them: one float per
-// thread, loaded with the weights and stored with them.
-template <int NL4, class PK> struct BiasChunk {
-    static_assert(4 * 32 + NL4 <= FNW * 64, "one bias per thread");
-    float v = 0.0f;
-    __device__ __forceinline__ void load(const char *P, const PK &pk)
-    {
-        const int t = threadIdx.x;
-        if (t < 4 * 32 + NL4) {
-            const size_t off = t < 32 ? pk.b[0] : t < 64 ? pk.b[1] : t < 96 ? pk.b[2] : t < 128 ? pk.b[3] : pk.b[4];
-            v = ((const float *)(P + off))[t < 128 ? (t & 31) : t - 128];
+// A workgroup's input region, C fields of R x R cells of a periodic H x W
+// grid from (ox, oy), straight into LDS (s_x, in the order of i below): every
+// thread brings the values that it rounds itself.
+template <int C, int R>
+__device__ __forceinline__ void dma_region(const float *q, int H, int W, int oy, int ox, float *s_x, int wave)
+{
+    const size_t hw = (size_t)H * W;
+#pragma unroll
+    for (int k = 0; k < (C * R * R + FNW * 64 - 1) / (FNW * 64); k++) {
+        const int i = threadIdx.x + k * FNW * 64;
+        if (i < C * R * R) {
+            const int ci = i / (R * R), r = i - ci * R * R;
+            const int ry = r / R, rx = r - ry * R;
+            load_lds<1>(q + (size_t)ci * hw + (size_t)wrap(oy + ry, H) * W + wrap(ox + rx, W),
+                        s_x + k * FNW * 64 + 64 * wave);
         }
     }
-    __device__ __forceinline__ void store(float *s) const
-    {
-        if (threadIdx.x < 4 * 32 + NL4) s[threadIdx.x] = v;
-    }
-};
+}
 
 // Plain (MINMOD, HLLE) Heun step of the previous state xprev on the R x R
 // region at (ox, oy), recomputed from xprev on the region grown by four
@@ -1015,71 +1079,57 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
     // must sit behind a real branch (an MFMA does not honour a partial EXEC)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, px = lane & 15;
-    const size_t hw = (size_t)H * W;
     const int ry0 = y0 - OFF - 5, rx0 = x0 - OFF - 5;  // origin of the input region
+    // the redo flag as a scalar load, waited for apart from the vector loads
+    const int rflag = OUT == OUT_Z_LDS && rd && rd->xprev ? scalar_int(rd->flag) : 0;
 
-    // input region, normalised and rounded to BF16 as the first layer reads
-    // it, and all five layers' weights: every global load is issued before
-    // the first LDS store.  qf (OUT_Z_LDS): the FP32 values of the
+    // Input region and all five layers' weights on their way to LDS at once,
+    // the input first.  The raw input lies over the end of s_a1, which nothing
+    // writes before layer 1.  qf (OUT_Z_LDS): the FP32 values of the
     // (TS + 6)^2 cells from (x0 - 3, y0 - 3), kept for the learned stage.
     constexpr int NIN = 3 * FRI_ * FRI_, TIN = (NIN + FNW * 64 - 1) / (FNW * 64);
-    // the redo flag's load first: the decision below then waits for it alone,
-    // not for the input's loads, and the weights' loads follow at once
-    const int rflag = OUT == OUT_Z_LDS && rd && rd->xprev ? *rd->flag : 0;
-    float xin[TIN];
-#pragma unroll
-    for (int k = 0; k < TIN; k++) {
-        const int i = threadIdx.x + k * FNW * 64;
-        if (i < NIN) {
-            const int ci = i / (FRI_ * FRI_), r = i - ci * FRI_ * FRI_;
-            const int ry = r / FRI_, rx = r - ry * FRI_;
-            const int yy = wrap(ry0 + ry, H), xx = wrap(rx0 + rx, W);
-            xin[k] = qb[(size_t)ci * hw + (size_t)yy * W + xx];
-        }
-    }
-    if constexpr (OUT == OUT_Z_LDS) {
-        // the redo decision after the loads have been issued (their values
-        // are discarded on a redo); the activations' LDS is free until layer
-        // 0's first store, which follows the staging barrier below
-        if (rflag) {
-            static_assert(3 * ((FRI_ + 8) * (FRI_ + 8) + (FRI_ + 4) * (FRI_ + 4) + FRI_ * FRI_) * 4 <= sizeof(s_act),
-                          "the redo's three fields fit over the activations");
-            const float *sr = redo_region<FRI_, TS>(rd->xprev, rd->xk, rd->dt, rd->rdx, rd->rdy, rd->ph.g, rd->ph.sqg,
-                                                rd->ph.h0, rd->fatal, H, W, rx0, ry0, x0, y0, (float *)s_act);
-#pragma unroll
-            for (int k = 0; k < TIN; k++) {
-                const int i = threadIdx.x + k * FNW * 64;
-                if (i < NIN) xin[k] = sr[i];
-            }
-        }
-    }
-    // all five layers' weights straight into LDS, waited for at the
-    // staging barrier (the waves issue no LDS writes for them)
-    BiasChunk<80, Packed> cb;
+    constexpr int XOFF = (int)(sizeof(s_act) / 4) - (NIN + 63) / 64 * 64;
+    float *const s_x = (float *)s_act + XOFF;
+    const float *src = s_x;
+    dma_region<3, FRI_>(qb, H, W, ry0, rx0, s_x, wave);
+    constexpr int LH = WH / 64 / FNW, L4 = W4 / 64 / FNW;  // a wave's loads per layer, at least
     if (load_w) {
-        cb.load(P, pk);
+        dma_biases<80>(P, pk, s_bias, wave);
         dma_weights<W0 / 64>(P + pk.w[0], s_wall, wave, lane);
         dma_weights<WH / 64>(P + pk.w[1], s_wall + W0, wave, lane);
         dma_weights<WH / 64>(P + pk.w[2], s_wall + W0 + WH, wave, lane);
         dma_weights<WH / 64>(P + pk.w[3], s_wall + W0 + 2 * WH, wave, lane);
         dma_weights<W4 / 64>(P + pk.w[4], s_wall + W0 + 3 * WH, wave, lane);
     }
+    if constexpr (OUT == OUT_Z_LDS) {
+        // a redo's region takes the place of the input's (whose values are
+        // discarded); the activations' LDS is free until layer 0's first
+        // store, which follows the staging barrier below
+        if (rflag) {
+            constexpr int RD = 3 * ((FRI_ + 8) * (FRI_ + 8) + (FRI_ + 4) * (FRI_ + 4) + FRI_ * FRI_);
+            static_assert(RD <= XOFF, "the redo's three fields fit over the activations, beside the raw input");
+            src = redo_region<FRI_, TS>(rd->xprev, rd->xk, rd->dt, rd->rdx, rd->rdy, rd->ph.g, rd->ph.sqg, rd->ph.h0,
+                                        rd->fatal, H, W, rx0, ry0, x0, y0, (float *)s_act);
+        }
+    }
+    if (load_w) wait_loads<3 * LH + L4>();
+    else wait_loads<0>();
 #pragma unroll
     for (int k = 0; k < TIN; k++) {
         const int i = threadIdx.x + k * FNW * 64;
         if (i < NIN) {
             const int ci = i / (FRI_ * FRI_), r = i - ci * FRI_ * FRI_;
-            s_in[ci][r] = (bf16)((xin[k] - nrm.mean[ci]) * nrm.inv_std[ci]);
+            const float x = src[i];
+            s_in[ci][r] = (bf16)((x - pick<3>(nrm.mean, ci)) * pick<3>(nrm.inv_std, ci));
             if (OUT == OUT_Z_LDS) {
                 // the halo's corner (x0 - 3, y0 - 3) is 2 + OFF cells into the input region
                 constexpr int QS = TS + 6, QO = 2 + OFF;
                 const int rr = r / FRI_, ry = rr - QO, rx = r - rr * FRI_ - QO;
-                if (ry >= 0 && ry < QS && rx >= 0 && rx < QS) qf[(ci * QS + ry) * QS + rx] = xin[k];
+                if (ry >= 0 && ry < QS && rx >= 0 && rx < QS) qf[(ci * QS + ry) * QS + rx] = x;
             }
         }
     }
-    if (load_w) cb.store(s_bias);
-    barrier_after_weights();
+    barrier_loads<3 * LH + L4>();
 
     // layer 0 on the FR0_ x FR0_ region, 16 pixels per group
     {
@@ -1129,13 +1179,16 @@ __device__ __forceinline__ float *fused_tile(const float *qb, const char *P, con
     // hidden layers 1..3: s_a0 -> s_a1 -> s_a0 -> s_a1
 #pragma unroll
     for (int l = 1; l < 4; l++) {
-        __syncthreads();  // previous layer's output written
+        // previous layer's output written
+        if (l == 1) barrier_loads<2 * LH + L4>();
+        else if (l == 2) barrier_loads<LH + L4>();
+        else barrier_loads<L4>();
         const int rin = FR0_ - 2 * (l - 1);
         const bf16x8 *in = (l & 1) ? s_a0 : s_a1;
         bf16 *out = (bf16 *)((l & 1) ? s_a1 : s_a0);
         fused_hidden<AS>(in, rin, out, s_wall + W0 + (l - 1) * WH, s_bias + 32 * l, wave, lane);
     }
-    __syncthreads();
+    barrier_loads<0>();
     // layer 4: s_a1 (FO + 2)^2 -> z on the FO x FO region: NG pixel groups x
     // 5 co tiles of accumulation chains of 9 taps
     const bf16x8 *s_w = s_wall + W0 + 3 * WH;
@@ -1357,64 +1410,52 @@ __device__ __forceinline__ float *fused_tile_euler(const float *qb, const char *
     bf16x8 *const s_a1 = s_act + FR0_ * FR0_ * AS;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, px = lane & 15;
-    const size_t hw = (size_t)H * W;
     const int ry0 = y0 - OFF - 5, rx0 = x0 - OFF - 5;
-    // every global load (input region, weights) before the first LDS store
+    // Input region and all five layers' weights (layer 0's in the packed
+    // order: it reads its two K blocks so), as in fused_tile.
     constexpr int NIN = E_CIN * FRI_ * FRI_, TIN = (NIN + FNW * 64 - 1) / (FNW * 64);
-    float xin[TIN];
-#pragma unroll
-    for (int k = 0; k < TIN; k++) {
-        const int i = threadIdx.x + k * FNW * 64;
-        if (i < NIN) {
-            const int ci = i / (FRI_ * FRI_), r = i - ci * FRI_ * FRI_;
-            const int ry = r / FRI_, rx = r - ry * FRI_;
-            xin[k] = qb[(size_t)ci * hw + (size_t)wrap(ry0 + ry, H) * W + wrap(rx0 + rx, W)];
-        }
-    }
-    if constexpr (ZLDS) {
-        // the redo decision after the loads have been issued (their values
-        // are discarded); the activations' LDS is free until layer 0's first
-        // store, which follows the staging barrier below
-        if (redo_from) {
-            static_assert(4 * ((FRI_ + 8) * (FRI_ + 8) + (FRI_ + 4) * (FRI_ + 4) + FRI_ * FRI_) * 4 <= sizeof(s_act),
-                          "the redo's three fields fit over the activations");
-            const float *sr = euler_redo_region<FRI_, FLUX, TS>(redo_from, (float *)qb, ra->dt, ra->rdx, ra->rdy,
-                                                            ra->gamma, fatal, H, W, rx0, ry0, x0, y0,
-                                                            (float *)s_act);
-#pragma unroll
-            for (int k = 0; k < TIN; k++) {
-                const int i = threadIdx.x + k * FNW * 64;
-                if (i < NIN) xin[k] = sr[i];
-            }
-        }
-    }
-    // all five layers' weights straight into LDS (layer 0's in the packed
-    // order: it reads its two K blocks so), waited for at the staging barrier
-    BiasChunk<E_COUT, EPacked> cb;
+    constexpr int XOFF = (int)(sizeof(s_act) / 4) - (NIN + 63) / 64 * 64;
+    float *const s_x = (float *)s_act + XOFF;
+    const float *src = s_x;
+    dma_region<E_CIN, FRI_>(qb, H, W, ry0, rx0, s_x, wave);
+    constexpr int LH = EWH / 64 / FNW, L4 = EW4 / 64 / FNW;  // a wave's loads per layer, at least
     if (load_w) {
-        cb.load(P, pk);
+        dma_biases<E_COUT>(P, pk, s_bias, wave);
         dma_weights<EW0 / 64, false>(P + pk.w[0], s_wall, wave, lane);
         dma_weights<EWH / 64>(P + pk.w[1], s_wall + EW0, wave, lane);
         dma_weights<EWH / 64>(P + pk.w[2], s_wall + EW0 + EWH, wave, lane);
         dma_weights<EWH / 64>(P + pk.w[3], s_wall + EW0 + 2 * EWH, wave, lane);
         dma_weights<EW4 / 64>(P + pk.w[4], s_wall + EW0 + 3 * EWH, wave, lane);
     }
+    if constexpr (ZLDS) {
+        // a redo's region takes the place of the input's; the activations'
+        // LDS is free until layer 0's first store, which follows the staging
+        // barrier below
+        if (redo_from) {
+            constexpr int RD = 4 * ((FRI_ + 8) * (FRI_ + 8) + (FRI_ + 4) * (FRI_ + 4) + FRI_ * FRI_);
+            static_assert(RD <= XOFF, "the redo's three fields fit over the activations, beside the raw input");
+            src = euler_redo_region<FRI_, FLUX, TS>(redo_from, (float *)qb, ra->dt, ra->rdx, ra->rdy, ra->gamma, fatal,
+                                                    H, W, rx0, ry0, x0, y0, (float *)s_act);
+        }
+    }
+    if (load_w) wait_loads<3 * LH + L4>();
+    else wait_loads<0>();
 #pragma unroll
     for (int k = 0; k < TIN; k++) {
         const int i = threadIdx.x + k * FNW * 64;
         if (i < NIN) {
             const int ci = i / (FRI_ * FRI_), r = i - ci * FRI_ * FRI_;
-            s_in[ci][r] = (bf16)((xin[k] - nrm.mean[ci]) * nrm.inv_std[ci]);
+            const float x = src[i];
+            s_in[ci][r] = (bf16)((x - pick<E_CIN>(nrm.mean, ci)) * pick<E_CIN>(nrm.inv_std, ci));
             if (ZLDS) {
                 // the halo's corner (x0 - 3, y0 - 3) is 2 + OFF cells into the input region
                 constexpr int QS = TS + 6, QO = 2 + OFF;
                 const int rr = r / FRI_, ry = rr - QO, rx = r - rr * FRI_ - QO;
-                if (ry >= 0 && ry < QS && rx >= 0 && rx < QS) qf[(ci * QS + ry) * QS + rx] = xin[k];
+                if (ry >= 0 && ry < QS && rx >= 0 && rx < QS) qf[(ci * QS + ry) * QS + rx] = x;
             }
         }
     }
-    if (load_w) cb.store(s_bias);
-    barrier_after_weights();
+    barrier_loads<3 * LH + L4>();
     // layer 0 on the FR0_ x FR0_ region: K = 36 (tap*4 + ci) in two blocks
     {
         const float *bias = s_bias;
@@ -1456,13 +1497,15 @@ __device__ __forceinline__ float *fused_tile_euler(const float *qb, const char *
     // hidden layers 1..3: s_a0 -> s_a1 -> s_a0 -> s_a1
 #pragma unroll
     for (int l = 1; l < 4; l++) {
-        __syncthreads();
+        if (l == 1) barrier_loads<2 * LH + L4>();
+        else if (l == 2) barrier_loads<LH + L4>();
+        else barrier_loads<L4>();
         const int rin = FR0_ - 2 * (l - 1);
         const bf16x8 *in = (l & 1) ? s_a0 : s_a1;
         bf16 *out = (bf16 *)((l & 1) ? s_a1 : s_a0);
         fused_hidden<AS>(in, rin, out, s_wall + EW0 + (l - 1) * EWH, s_bias + 32 * l, wave, lane);
     }
-    __syncthreads();
+    barrier_loads<0>();
     // layer 4: s_a1 (FO + 2)^2 -> z on the FO x FO region, pixel groups wave,
     // wave + FNW, ... with all six co tiles, each chain in tap order.  ZLDS:
     // z over the activations ([FO*FO][96] covers s_a0 and the start of s_a1),
@@ -1586,8 +1629,8 @@ __global__ __launch_bounds__(FNW * 64) void conv_learned_euler_kernel(eln::Stage
         // 1).  A frozen solve's tiles run the pass but write nothing (live
         // false), so that neither flag is waited for before the input's
         // loads are issued (an early exit makes the compiler wait for them)
-        const int fz = a.fatal[b];
-        const int rf = a.flagbit == 1 && xprev ? a.flags[2 * b + (a.parity ^ 1)] : 0;
+        const int fz = scalar_int(a.fatal + b);
+        const int rf = a.flagbit == 1 && xprev ? scalar_int(a.flags + 2 * b + (a.parity ^ 1)) : 0;
         if (staged) __syncthreads();  // the previous tile's LDS reads are done
         const int rt = tile - b * tx_n * ty_n;
         const int y0 = (rt / tx_n) * TS, x0 = (rt % tx_n) * TS;
@@ -1608,7 +1651,7 @@ __global__ __launch_bounds__(FNW * 64) void conv_learned_euler_kernel(eln::Stage
         int *flag = a.flags + 2 * b + a.parity;
         // stage 2 of a solve whose stage 1 failed is evaluated (its result is
         // discarded by the redo) but its fallback sides are not counted
-        const bool count = !(a.flagbit == 2 && (*flag & 1));
+        const bool count = !(a.flagbit == 2 && (scalar_int(flag) & 1));
         if (tid == 0) {
             s_cnt = 0;
             s_bad = 0;
@@ -1788,7 +1831,8 @@ __device__ __forceinline__ void learned_epilogue(const LSolve &d, const LItem &i
     ph.h0 = d.h0;
     // stage 2 of a solve whose stage 1 failed is evaluated (its result is
     // discarded by the redo) but its fallback faces are not counted
-    const bool count = !(STAGE == 2 && (*bad & 1));
+    // (its bit is constant during stage 2's launch: a scalar load)
+    const bool count = !(STAGE == 2 && (scalar_int(bad) & 1));
     if (tid == 0) {
         s_cnt = 0;
         s_bad = 0;
@@ -1957,8 +2001,8 @@ __global__ __launch_bounds__(FNW * 64) void conv_learned_one_kernel(LSolve d, in
         // its latency behind the network pass
         constexpr bool PRE = STAGE == 2 && TS == 4 && !DIR;
         float q0v[3] = {0.0f, 0.0f, 0.0f};
-        if (PRE && threadIdx.x < TS * TS) {
-            const int cy = threadIdx.x / TS, cx = threadIdx.x - cy * TS;
+        if (PRE) {
+            const int c = threadIdx.x & (TS * TS - 1), cy = c / TS, cx = c - cy * TS;
             const size_t idx = (size_t)(ty * TS + cy) * d.nx + tx * TS + cx, plane = (size_t)d.nx * d.ny;
 #pragma unroll
             for (int v = 0; v < 3; v++) q0v[v] = d.q[idx + v * plane];

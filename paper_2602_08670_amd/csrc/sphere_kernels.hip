@@ -265,24 +265,18 @@ __device__ __forceinline__ T wave_max(T v)
 }
 
 // Flux of one face from the four stencil values c[v][0..3] along its index
-// line (low-1, low, high, high+1) and its frame F9 (n, t, r, length at
-// entry f of planes fp apart): MINMOD (or first-order) face states rotated
-// into (n, t, r), the 1D numerical flux along n with the t and r momenta
-// transported, rotated back and multiplied by the edge length.
+// line (low-1, low, high, high+1) and its frame (n, t, r, length): MINMOD (or
+// first-order) face states rotated into (n, t, r), the 1D numerical flux along
+// n with the t and r momenta transported, rotated back and multiplied by the
+// edge length.
 template <typename T, int FLUX, int RECON>
-__device__ __forceinline__ void face_flux(const T (*c)[4], const T *__restrict__ F9, size_t fp, int f, T g, T *out)
+__device__ __forceinline__ void face_flux(const T (*c)[4], const T *fr, T g, T *out)
 {
     T QL[4], QR[4];
 #pragma unroll
     for (int v = 0; v < 4; v++) fvk::recon_pair<T, RECON>(c[v][0], c[v][1], c[v][2], c[v][3], QL[v], QR[v]);
-    T nn[3], t[3], r[3];
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-        nn[d] = F9[d * fp + f];
-        t[d] = F9[(3 + d) * fp + f];
-        r[d] = F9[(6 + d) * fp + f];
-    }
-    const T len = F9[9 * fp + f];
+    const T *nn = fr, *t = fr + 3, *r = fr + 6;
+    const T len = fr[9];
     T sl[4] = {QL[0], QL[1] * nn[0] + QL[2] * nn[1] + QL[3] * nn[2], QL[1] * t[0] + QL[2] * t[1] + QL[3] * t[2],
                QL[1] * r[0] + QL[2] * r[1] + QL[3] * r[2]};
     T sr[4] = {QR[0], QR[1] * nn[0] + QR[2] * nn[1] + QR[3] * nn[2], QR[1] * t[0] + QR[2] * t[1] + QR[3] * t[2],
@@ -304,7 +298,17 @@ __device__ __forceinline__ void face_flux(const T (*c)[4], const T *__restrict__
 // the projection.  Face fluxes never reach HBM.  The last stage reduces the
 // CFL rate of out into slot rate_out, clears slot rate_clear, flags
 // inadmissible cells and advances time and step count.
-constexpr int STX = 32, STY = 8, SNT = STX * STY;
+//
+// Bound by its loads: 28 geometry values and 8 to 12 of the states per cell,
+// 152 bytes in FP32.  The tile's faces are dealt to the NT threads as one list,
+// x faces first.  PRE: every thread issues all of its loads (the states of
+// cells of the ring, its first two faces' frames, its cell's geometry) before
+// the first barrier, where a load per phase is three more round trips; else
+// each phase loads what it needs, in fewer registers.
+// 1 024 x 512 cells in FP32: 15.0 us a stage (5.3 TB/s; 15.4 us with the faces
+// dealt in four rounds of 256 threads), 1 280 x 640 20.9 us (22.8), FP64 720 x
+// 360 18.0 us (19.5); 80 x 40 cells 4.5 us (6.2).
+constexpr int STX = 32;
 
 // Workgroups are handed to the eight XCDs in turn: for a grid that is a
 // multiple of 8, XCD k gets the contiguous k-th eighth of the tiles, so that
@@ -314,13 +318,14 @@ __device__ __forceinline__ int xcd_tile(int w, int grid)
     return (grid & 7) ? w : (w & 7) * (grid >> 3) + (w >> 3);
 }
 
-template <typename T, int FLUX, int RECON>
-__global__ __launch_bounds__(SNT) void tile_kernel(CellArgs<T> a, int tiles_x)
+template <typename T, int FLUX, int RECON, int STY, int NT, bool PRE>
+__global__ __launch_bounds__(NT) void tile_kernel(CellArgs<T> a, int tiles_x)
 {
-    constexpr int HX = STX + 4, HY = STY + 4;
-    __shared__ T s_q[4][HY][HX];
-    __shared__ T s_fx[4][STY][STX + 1];
-    __shared__ T s_fy[4][STY + 1][STX];
+    constexpr int HX = STX + 4, HY = STY + 4, NXF = (STX + 1) * STY, NFACE = NXF + (STY + 1) * STX;
+    constexpr int NQ = (HX * HY + NT - 1) / NT;
+    static_assert(STX * STY <= NT && NFACE <= 2 * NT && NT >= 128, "a thread's share");
+    __shared__ T s_q[4][HY * HX];
+    __shared__ T s_f[4][NFACE];
     __shared__ double s_dt;
     const int nx = 2 * a.n, ny = a.n;
     const int ncell = nx * ny, nyface = nx * (ny + 1);
@@ -332,74 +337,109 @@ __global__ __launch_bounds__(SNT) void tile_kernel(CellArgs<T> a, int tiles_x)
     const int tw = nx - x0 < STX ? nx - x0 : STX, th = ny - y0 < STY ? ny - y0 : STY;  // cells of this tile
     const bool frozen = a.ctl->bad != 0;
     // the state on the tile and its two-cell ring: x in [x0 - 2, x0 + tw + 2),
-    // y in [y0 - 2, y0 + th + 2), each within one period or mirror of the grid
-    for (int e = tid; e < HY * HX; e += SNT) {
-        const int ly = e / HX, lx = e - ly * HX;
-        if (lx >= tw + 4 || ly >= th + 4) continue;
-        const int k = cell_of(x0 - 2 + lx, y0 - 2 + ly, nx, ny);
+    // y in [y0 - 2, y0 + th + 2), each within one period or mirror of the
+    // grid (a place past it loads the last one's)
+    T q[NQ][4];
 #pragma unroll
-        for (int v = 0; v < 4; v++) s_q[v][ly][lx] = a.qs[v * plane + k];
+    for (int u = 0; u < NQ; u++) {
+        const int e = min(tid + u * NT, HY * HX - 1), ly = e / HX, lx = e - ly * HX;
+        const int k = cell_of(x0 - 2 + min(lx, tw + 3), y0 - 2 + min(ly, th + 3), nx, ny);
+#pragma unroll
+        for (int v = 0; v < 4; v++) q[u][v] = a.qs[v * plane + k];
     }
-    if (tid < 64) {
-        const int lane = tid;
+    // Frame and stencil (first value in s_q, step) of face f of the list, and
+    // whether the tile has it.  x face (fi, fj) lies between cells x0 + fi - 1
+    // and x0 + fi of row y0 + fj, and the x-face arrays index it by cell
+    // (x0 + fi) mod nx; y face (fi, fj) is in row y0 + fj of the y-face arrays
+    // (between cell rows y0 + fj - 1 and y0 + fj), column x0 + fi.
+    auto face = [&](int f, T (&fr)[10], int &at, int &step) {
+        const bool there = f < NFACE;
+        f = min(f, NFACE - 1);
+        const bool xface = f < NXF;
+        const int e = xface ? f : f - NXF, per = xface ? STX + 1 : STX;
+        const int fj = e / per, fi = e - fj * per;
+        at = xface ? (fj + 2) * HX + fi : fj * HX + fi + 2;
+        step = xface ? 1 : HX;
+        const int gj = y0 + min(fj, xface ? th - 1 : th), gi = x0 + min(fi, xface ? tw : tw - 1);
+        const T *F = xface ? a.G.xf : a.G.yf;
+        const size_t fp = xface ? plane : (size_t)nyface;
+        const int k = gj * nx + (gi < nx ? gi : gi - nx);
+#pragma unroll
+        for (int d = 0; d < 10; d++) fr[d] = F[d * fp + k];
+        return there && (xface ? fi <= tw && fj < th : fi < tw && fj <= th);
+    };
+    T fr[2][10];
+    int at[2], step[2];
+    bool on[2] = {false, false};
+    if (PRE)
+#pragma unroll
+        for (int u = 0; u < 2; u++) on[u] = face(tid + u * NT, fr[u], at[u], step[u]);
+    // the thread's cell: geometry and q0
+    const int cj = tid / STX, ci = tid - cj * STX;
+    const bool cell = ci < tw && cj < th;
+    const int k = (y0 + min(cj, th - 1)) * nx + x0 + min(ci, tw - 1);
+    T N[3], x[3], ia, q0[4], rfac;
+    auto geo = [&] {
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            N[d] = a.G.nsum[d * plane + k];
+            x[d] = a.G.cen[d * plane + k];
+        }
+        ia = a.G.inv_area[k];
+#pragma unroll
+        for (int v = 0; v < 4; v++) q0[v] = a.a0 != T(0) ? a.q0[v * plane + k] : T(0);
+        rfac = a.last ? a.G.rate_fac[k] : T(0);
+    };
+    if (PRE) geo();
+    if (tid >= 64 && tid < 128) {
+        const int lane = tid & 63;
         double m = 0.0;
         if (!(a.dt_fixed > 0.0)) m = __longlong_as_double((long long)*rate_slot(a.rates, a.rate_in, lane));
         m = wave_max(m);
         if (lane == 0) s_dt = a.dt_fixed > 0.0 ? a.dt_fixed : a.cfl / m;
     }
+#pragma unroll
+    for (int u = 0; u < NQ; u++)
+        if (tid + u * NT < HY * HX)
+#pragma unroll
+            for (int v = 0; v < 4; v++) s_q[v][tid + u * NT] = q[u][v];
     __syncthreads();
     const T g = a.g;
-    // x faces (fi, fj): between cells x0 + fi - 1 and x0 + fi of row y0 + fj;
-    // the x-face arrays index it by cell (x0 + fi) mod nx
-    for (int f = tid; f < (STX + 1) * STY; f += SNT) {
-        const int fj = f / (STX + 1), fi = f - fj * (STX + 1);
-        if (fi > tw || fj >= th) continue;
-        const int i = x0 + fi < nx ? x0 + fi : x0 + fi - nx;
+    auto eval = [&](int f, const T (&fr)[10], int at, int step) {
         T c[4][4];
 #pragma unroll
         for (int v = 0; v < 4; v++)
 #pragma unroll
-            for (int s = 0; s < 4; s++) c[v][s] = s_q[v][fj + 2][fi + s];
+            for (int s = 0; s < 4; s++) c[v][s] = s_q[v][at + s * step];
         T o[4];
-        face_flux<T, FLUX, RECON>(c, a.G.xf, plane, (y0 + fj) * nx + i, g, o);
+        face_flux<T, FLUX, RECON>(c, fr, g, o);
 #pragma unroll
-        for (int v = 0; v < 4; v++) s_fx[v][fj][fi] = o[v];
-    }
-    // y faces (fi, fj): row y0 + fj of the y-face arrays (between cell rows
-    // y0 + fj - 1 and y0 + fj), column x0 + fi
-    for (int f = tid; f < (STY + 1) * STX; f += SNT) {
-        const int fj = f / STX, fi = f - fj * STX;
-        if (fi >= tw || fj > th) continue;
-        T c[4][4];
+        for (int v = 0; v < 4; v++) s_f[v][f] = o[v];
+    };
+    if (PRE)
 #pragma unroll
-        for (int v = 0; v < 4; v++)
-#pragma unroll
-            for (int s = 0; s < 4; s++) c[v][s] = s_q[v][fj + s][fi + 2];
-        T o[4];
-        face_flux<T, FLUX, RECON>(c, a.G.yf, (size_t)nyface, (y0 + fj) * nx + x0 + fi, g, o);
-#pragma unroll
-        for (int v = 0; v < 4; v++) s_fy[v][fj][fi] = o[v];
-    }
+        for (int u = 0; u < 2; u++)
+            if (on[u]) eval(tid + u * NT, fr[u], at[u], step[u]);
+#pragma unroll 1
+    for (int f = PRE ? NFACE : tid; f < NFACE; f += NT)
+        if (face(f, fr[0], at[0], step[0])) eval(f, fr[0], at[0], step[0]);
     __syncthreads();
     const T dt = (T)s_dt;
-    const int cj = tid / STX, ci = tid - cj * STX;
     T rate = T(0);
     bool bad = false;
-    if (ci < tw && cj < th && !frozen) {
-        const int k = (y0 + cj) * nx + x0 + ci;
+    if (cell && !frozen) {
+        if (!PRE) geo();
         T s[4];
 #pragma unroll
-        for (int v = 0; v < 4; v++) s[v] = s_q[v][cj + 2][ci + 2];
+        for (int v = 0; v < 4; v++) s[v] = s_q[v][(cj + 2) * HX + ci + 2];
         const T ih = fvk::rcp(s[0]);
-        const T N[3] = {a.G.nsum[k], a.G.nsum[plane + k], a.G.nsum[2 * plane + k]};
-        const T x[3] = {a.G.cen[k], a.G.cen[plane + k], a.G.cen[2 * plane + k]};
         const T un = (s[1] * N[0] + s[2] * N[1] + s[3] * N[2]) * ih;
         const T pres = T(0.5) * a.g * s[0] * s[0];
-        const T ia = a.G.inv_area[k];
         T o[4];
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-            T div = (s_fx[v][cj][ci + 1] - s_fx[v][cj][ci]) + (s_fy[v][cj + 1][ci] - s_fy[v][cj][ci]);
+            const T *fx = s_f[v] + cj * (STX + 1) + ci, *fy = s_f[v] + NXF + cj * STX + ci;
+            T div = (fx[1] - fx[0]) + (fy[STX] - fy[0]);
             if (v > 0) div = div - (s[v] * un + pres * N[v - 1]);
             o[v] = -div * ia;
         }
@@ -411,7 +451,7 @@ __global__ __launch_bounds__(SNT) void tile_kernel(CellArgs<T> a, int tiles_x)
 #pragma unroll
         for (int v = 0; v < 4; v++) {
             T r = a.a1 * (s[v] + dt * o[v]);
-            if (a.a0 != T(0)) r = a.a0 * a.q0[v * plane + k] + r;
+            if (a.a0 != T(0)) r = a.a0 * q0[v] + r;
             o[v] = r;
         }
         const T mr = o[1] * x[0] + o[2] * x[1] + o[3] * x[2];
@@ -421,7 +461,7 @@ __global__ __launch_bounds__(SNT) void tile_kernel(CellArgs<T> a, int tiles_x)
         for (int v = 0; v < 4; v++) a.out[v * plane + k] = o[v];
         if (a.last) {
             const T speed = fvk::fsqrt(o[1] * o[1] + o[2] * o[2] + o[3] * o[3]) * fvk::rcp(o[0]);
-            rate = (speed + fvk::fsqrt(a.g * o[0])) * a.G.rate_fac[k];
+            rate = (speed + fvk::fsqrt(a.g * o[0])) * rfac;
             bad = !(o[0] > T(0)) || !(rate < T(__builtin_inf()));
             if (bad) rate = T(0);
         }
@@ -431,7 +471,7 @@ __global__ __launch_bounds__(SNT) void tile_kernel(CellArgs<T> a, int tiles_x)
     if (a.rate_out >= 0) {
         const T m = wave_max(rate);
         if ((tid & 63) == 0)
-            atomicMax(rate_slot(a.rates, a.rate_out, (blockIdx.x * 4 + (tid >> 6)) & (RATE_SUB - 1)),
+            atomicMax(rate_slot(a.rates, a.rate_out, (blockIdx.x * (NT / 64) + (tid >> 6)) & (RATE_SUB - 1)),
                       dmax_bits((double)m));
     }
     if (blockIdx.x == 0) {
@@ -514,12 +554,13 @@ template <typename T> hipError_t geometry(const Geometry<T> &G, int n, hipStream
     return hipGetLastError();
 }
 
-template <typename T> hipError_t stage(int flux, int recon, const CellArgs<T> &a, hipStream_t st)
+template <typename T, int STY, int NT, bool PRE>
+static hipError_t stage_go(int flux, int recon, const CellArgs<T> &a, hipStream_t st)
 {
     const int nx = 2 * a.n, ny = a.n;
     const int tiles_x = (nx + STX - 1) / STX, tiles = tiles_x * ((ny + STY - 1) / STY);
-    const dim3 grid(tiles), blk(SNT);
-#define SPH_TILE(FL, RC) hipLaunchKernelGGL((tile_kernel<T, FL, RC>), grid, blk, 0, st, a, tiles_x)
+    const dim3 grid(tiles), blk(NT);
+#define SPH_TILE(FL, RC) hipLaunchKernelGGL((tile_kernel<T, FL, RC, STY, NT, PRE>), grid, blk, 0, st, a, tiles_x)
     if (recon == fvk::FIRST) {
         if (flux == fvk::RUSANOV) SPH_TILE(fvk::RUSANOV, fvk::FIRST);
         else if (flux == fvk::ROE) SPH_TILE(fvk::ROE, fvk::FIRST);
@@ -531,6 +572,17 @@ template <typename T> hipError_t stage(int flux, int recon, const CellArgs<T> &a
     }
 #undef SPH_TILE
     return hipGetLastError();
+}
+
+template <typename T> hipError_t stage(int flux, int recon, const CellArgs<T> &a, hipStream_t st)
+{
+    // All loads at once where no CU has a second tile to run meanwhile (200 x 100
+    // cells in FP32: 4.7 us a stage against 5.0; 4 rows per tile in FP64:
+    // 5.6 against 6.1); from there on the registers cost more than the loads'
+    // latency (FP32 720 x 360 cells: 13.5 against 12.2 us).
+    constexpr int PY = sizeof(T) == 4 ? 8 : 4, PN = sizeof(T) == 4 ? 320 : 192;
+    if ((2 * a.n + STX - 1) / STX * ((a.n + PY - 1) / PY) <= 256) return stage_go<T, PY, PN, true>(flux, recon, a, st);
+    return stage_go<T, 8, 320, false>(flux, recon, a, st);
 }
 
 template <typename T>

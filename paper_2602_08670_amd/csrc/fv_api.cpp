@@ -210,6 +210,27 @@ fv_status enqueue_step(fv_solver *s)
     return FV_OK;
 }
 
+// nsteps steps.  Small grids of the batched kind go two steps at a time, each
+// a launch, from the state to its stage buffer and back; an odd step at the
+// end takes its two stages' launches.
+fv_status enqueue_run(fv_solver *s, int64_t nsteps)
+{
+    int64_t k = 0;
+    if (s->batched && fvk::step_fits(s->cfg.nx, s->cfg.ny)) {
+        for (; k + 2 <= nsteps; k += 2)
+            for (int h = 0; h < 2; h++, s->enq++) {
+                void *const src = h ? s->bd.s1 : s->bd.q, *const dst = h ? s->bd.q : s->bd.s1;
+                hipError_t e = fvk::launch_step_one(s->d.eqn, s->d.bathy, s->bd, s->bi[s->enq % 3], src, dst, s->stream);
+                if (e != hipSuccess) return hip_fail(e, "step launch");
+            }
+    }
+    for (; k < nsteps; k++) {
+        fv_status rc = enqueue_step(s);
+        if (rc != FV_OK) return rc;
+    }
+    return FV_OK;
+}
+
 // offsets inside the 256-byte block of learned counters
 constexpr size_t SM_DT = 0, SM_BAD = 8, SM_NFB = 16, SM_REDONE = 24;
 
@@ -405,11 +426,7 @@ fv_status fv_run(fv_solver *s, int64_t nsteps)
 {
     if (!s) return fail(FV_E_INVALID, "solver is NULL");
     if (nsteps < 0) return fail(FV_E_INVALID, "nsteps %lld < 0", (long long)nsteps);
-    for (int64_t k = 0; k < nsteps; k++) {
-        fv_status rc = enqueue_step(s);
-        if (rc != FV_OK) return rc;
-    }
-    return FV_OK;
+    return enqueue_run(s, nsteps);
 }
 
 fv_status fv_time(fv_solver *s, double *t, int64_t *step)
@@ -571,10 +588,8 @@ fv_status fv_run_noalloc(const fv_config *cfg, void *q, const void *bathy, int64
     hipError_t e = fvk::launch_reset(s.ctl(), s.rates(), s.stream);
     if (e == hipSuccess) e = fvk::launch_rate(s.d, s.q, s.ctl(), s.rates(), 0, s.stream);
     if (e != hipSuccess) return hip_fail(e, "reset and rate kernels");
-    for (int64_t k = 0; k < nsteps; k++) {
-        rc = enqueue_step(&s);
-        if (rc != FV_OK) return rc;
-    }
+    rc = enqueue_run(&s, nsteps);
+    if (rc != FV_OK) return rc;
     if (info_dev) {
         e = fvk::launch_report(s.ctl(), info_dev, s.stream);
         if (e != hipSuccess) return hip_fail(e, "report kernel");

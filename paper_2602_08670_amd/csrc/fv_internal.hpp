@@ -104,6 +104,13 @@ hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const Ba
 // launches of a single solve.
 hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
                                   int grid, hipStream_t st);
+// One solve's whole Heun step from src to dst (its state or s1, not the same
+// one) in one launch; sides of four cells and more.
+// Larger grids gain nothing (16 steps of 800^2 cells 272 us and 286 as two
+// launches, 1000 x 700 Euler 322 and 323) and lose by the ring (1024^2 425, 327).
+inline bool step_fits(int nx, int ny) { return nx >= 4 && ny >= 4 && (int64_t)nx * ny <= 640000; }
+hipError_t launch_step_one(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
+                           hipStream_t st);
 // The form recorded in graphs: wgs workgroups (a multiple of 8, set to
 // xcd_grid(tiles) before each replay), the tile count read from the list
 // header list = {items, tiles}.

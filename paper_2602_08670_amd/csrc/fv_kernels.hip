@@ -297,6 +297,25 @@ __device__ __forceinline__ void stage_dt(const StageArgs<T> &a, const int tid,
     }
 }
 
+// Where a stage's cells come from and go: the global arrays of its arguments.
+template <typename T, int EQN> struct StageIO {
+    static constexpr bool GLOBAL = true;
+    const StageArgs<T> &a;
+    int x0, y0;
+    size_t tbase;
+    __device__ __forceinline__ bool in(int cy, int lane) const { return x0 + lane < a.nx && y0 + cy < a.ny; }
+    __device__ __forceinline__ T q0(int v, int cy, int lane) const
+    {
+        const unsigned off = in(cy, lane) ? (unsigned)(cy * a.nx + lane) : 0u;
+        return ld_off(a.q0 + v * ((size_t)a.nx * a.ny) + tbase, off);
+    }
+    __device__ __forceinline__ void put(int v, int cy, int lane, T o) const
+    {
+        __builtin_nontemporal_store(o, st_off(a.out + v * ((size_t)a.nx * a.ny) + tbase, (unsigned)(cy * a.nx + lane)));
+    }
+    __device__ __forceinline__ void keep(int, int, const T *) const {}
+};
+
 // One RK stage on the TX x TY tile at (x0, y0) whose halo, faces and Delta t
 // are staged in `sh` (after a barrier).  `tile_linear` is the tile's index
 // within its solve; the tile with index 0 does the per-step bookkeeping of
@@ -315,9 +334,8 @@ __device__ __forceinline__ void stage_dt(const StageArgs<T> &a, const int tid,
 // their reconstruction and the flux was rearranged), 1024^2 21.3 -> 20.4 us a
 // step, 2048^2 76.2 -> 63.6, Euler 1000 x 700 26.6 -> 19.9; by latency on
 // small grids (64^2 13.0 -> 8.0).
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY, int RPW>
-__device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x0, const int y0,
-                                              const int tile_linear, const int tid,
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY, int RPW, typename IO>
+__device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const IO &io, const int tile_linear, const int tid,
                                               StageLds<T, EQN, BATHY, TX, TY, RPW> &sh)
 {
 #pragma clang fp contract(off)
@@ -334,9 +352,6 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
     const bool frozen = gload(a.ctl)->bad != 0;
     const int lane = tid & 63, wave = tid >> 6;
     const int r0 = wave * RPW;
-    const int nx = a.nx, ny = a.ny;
-    const size_t plane = (size_t)nx * ny;
-    const size_t tbase = (size_t)y0 * nx + x0;
     const T dt = (T)sh.dt;
     // stage weight times Delta t over the cell width, per axis
     const T cxs = a.a1 * dt * a.rdx, cys = a.a1 * dt * a.rdy;
@@ -429,10 +444,8 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
         // q0 is needed only in the combine: its latency hides behind the x face
         T q0r[NV];
         if (a.a0 != T(0)) {
-            const bool in = x0 + lane < nx && y0 + cy < ny;
-            const unsigned off = in ? (unsigned)(cy * nx + lane) : 0u;
 #pragma unroll
-            for (int v = 0; v < NV; v++) q0r[v] = ld_off(a.q0 + v * plane + tbase, off);
+            for (int v = 0; v < NV; v++) q0r[v] = io.q0(v, cy, lane);
         }
 #pragma unroll
         for (int v = 0; v < NL; v++)
@@ -446,9 +459,9 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
             if (EQN == SWE && v == 1) tr = tfma(-(a.ph.g * c[0][2]), slope, tr);
             Lv[v] = tr - rt;
         }
-        const bool in = x0 + lane < nx && y0 + cy < ny && !frozen;
-        if (in) {
-            const unsigned off = (unsigned)(cy * nx + lane);
+        const bool in = io.in(cy, lane);
+        if (!IO::GLOBAL && in && frozen) io.keep(cy, lane, q0r);
+        if (in && !frozen) {
             T qn[NV];
 #pragma unroll
             for (int v = 0; v < NV; v++) {
@@ -458,7 +471,7 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const int x
                 const T inc = tfma(cys, Ly[j][v], cxs * Lv[v]);
                 T o = tfma(a.a1, c[v][2], inc);
                 if (a.a0 != T(0)) o = tfma(a.a0, q0r[v], o);
-                __builtin_nontemporal_store(o, st_off(a.out + v * plane + tbase, off));
+                io.put(v, cy, lane, o);
                 qn[v] = o;
             }
             if (a.last) {
@@ -500,7 +513,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T> &a, const int x0, 
         halo_commit(r, sh, tid);
     }
     __syncthreads();
-    stage_compute<T, EQN, BATHY, FLUX, RECON, TX, TY, RPW>(a, x0, y0, tile_linear, tid, sh);
+    const StageIO<T, EQN> io{a, x0, y0, (size_t)y0 * a.nx + x0};
+    stage_compute<T, EQN, BATHY, FLUX, RECON, TX, TY, RPW>(a, io, tile_linear, tid, sh);
 }
 
 // Workgroups are handed to the eight XCDs in turn (workgroup w runs on XCD
@@ -622,6 +636,127 @@ __global__ __launch_bounds__((ShapeLds<T, EQN, BATHY, SHAPE>::NTH), shape_waves(
     const TileRef t = batch_fill<T, STAGE, SHAPE>(d, it, w, a);
     stage_tile<T, EQN, BATHY, HLLE, MINMOD, TILE_X, shape_rows(SHAPE), shape_rpw(SHAPE)>(a, t.x0, t.y0, t.tile,
                                                                                         threadIdx.x);
+}
+
+// ------------------------------------------------- a Heun step in one launch
+// Both stages of a tile of STEP_X x TY cells in one workgroup, from one buffer
+// to another: the first stage on the tile and its two-cell ring (STEP_X + 4 =
+// 64 columns, a wave64 per row), its result in LDS as the second stage's halo
+// tile.  Ghost cells of the result past a wall are mirrored from it, as the
+// second stage's loads would mirror them; past a periodic border they are
+// computed from the same values as their images.  The same arithmetic as the
+// two launches, so the same bits.  A frozen solve's cells are carried over.
+// On small grids a launch is its chain (start, load, two barriers, store) and
+// little work: 16 steps over a bed, two launches a step and one: 64^2 128 and
+// 95 us, 256^2 131 and 103, 400^2 160 and 115, 600^2 192 and 143.
+constexpr int STEP_X = 60;
+
+// The first stage's results to LDS, all of them.
+template <typename T, typename L2> struct RingIO {
+    static constexpr bool GLOBAL = false;
+    L2 &to;
+    __device__ __forceinline__ bool in(int, int) const { return true; }
+    __device__ __forceinline__ T q0(int, int, int) const { return T(0); }
+    __device__ __forceinline__ void put(int v, int cy, int lane, T o) const { to.q[v][cy][lane] = o; }
+    __device__ __forceinline__ void keep(int cy, int lane, const T *q0r) const
+    {
+#pragma unroll
+        for (int v = 0; v < L2::NV; v++) to.q[v][cy][lane] = T(0);
+    }
+};
+// The second stage's: q0 from the first stage's halo tile.
+template <typename T, typename L1> struct StepIO {
+    static constexpr bool GLOBAL = false;
+    const StageArgs<T> &a;
+    const L1 &from;
+    int x0, y0;
+    __device__ __forceinline__ bool in(int cy, int lane) const
+    {
+        return lane < STEP_X && x0 + lane < a.nx && y0 + cy < a.ny;
+    }
+    __device__ __forceinline__ T q0(int v, int cy, int lane) const { return from.q[v][cy + 4][min(lane, STEP_X) + 4]; }
+    __device__ __forceinline__ void put(int v, int cy, int lane, T o) const
+    {
+        *st_off(a.out + v * ((size_t)a.nx * a.ny) + (size_t)y0 * a.nx + x0, (unsigned)(cy * a.nx + lane)) = o;
+    }
+    __device__ __forceinline__ void keep(int cy, int lane, const T *q0r) const
+    {
+#pragma unroll
+        for (int v = 0; v < L1::NV; v++) put(v, cy, lane, q0r[v]);
+    }
+};
+
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TY>
+__device__ __forceinline__ void step_tile(const StageArgs<T> &a, const int x0, const int y0, const int tile_linear,
+                                          const int tid)
+{
+    constexpr int RY = TY + 4;  // rows of the first stage, a wave each
+    using L1 = StageLds<T, EQN, BATHY, 64, RY, 1>;
+    using L2 = StageLds<T, EQN, BATHY, 64, TY, 1>;
+    constexpr int NV = L1::NV;
+    __shared__ L1 s1;
+    __shared__ L2 s2;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nx = a.nx, ny = a.ny, ox = x0 - 2, oy = y0 - 2;  // origin of the first stage's cells
+    StageArgs<T> a1 = a, a2 = a;
+    a1.a0 = T(0);
+    a1.a1 = T(1);
+    a1.last = 0;
+    a2.a0 = T(0.5);
+    a2.a1 = T(0.5);
+    a2.last = 1;
+    // the ring's image of this lane's cell, and the bed there
+    bool fx = false, fy = false;
+    const int gx = ghost_index(ox + lane, nx, a.bc_x, fx), gy = ghost_index(oy + wave, ny, a.bc_y, fy);
+    T bed = T(0);
+    {
+        HaloRegs<T, EQN, BATHY, 64, RY, 1> r;
+        if (inner_tile<64, RY>(ox, oy, nx, ny)) halo_issue<T, EQN, BATHY, 64, RY, 1, false>(a1, ox, oy, tid, r);
+        else halo_issue<T, EQN, BATHY, 64, RY, 1, true>(a1, ox, oy, tid, r);
+        if (BATHY) bed = ld_off(a.bed + (size_t)gy * nx, (unsigned)gx);
+        stage_dt(a1, tid, s1);
+        halo_commit(r, s1, tid);
+    }
+    __syncthreads();
+    if (tid == 0) s2.dt = s1.dt;
+    stage_compute<T, EQN, BATHY, FLUX, RECON, 64, RY, 1>(a1, RingIO<T, L2>{s2}, tile_linear, tid, s1);
+    __syncthreads();
+    // a cell past a wall takes its image's values, the normal momentum negated
+    T m[NV];
+    {
+        const int lx = fx ? min(max(gx - ox, 0), 63) : lane, ly = fy ? min(max(gy - oy, 0), RY - 1) : wave;
+#pragma unroll
+        for (int v = 0; v < NV; v++) m[v] = s2.q[v][ly][lx];
+        m[1] = fx ? -m[1] : m[1];
+        m[2] = fy ? -m[2] : m[2];
+    }
+    if (BATHY) s2.q[NV][wave][lane] = m[0] + bed;
+    if ((a.bc_x != 0 || a.bc_y != 0) && !(ox >= 0 && oy >= 0 && ox + 64 <= nx && oy + RY <= ny)) {
+        __syncthreads();  // a cell's image may be another wave's
+#pragma unroll
+        for (int v = 0; v < NV; v++) s2.q[v][wave][lane] = m[v];
+    }
+    __syncthreads();
+    if (wave < TY) {
+        stage_compute<T, EQN, BATHY, FLUX, RECON, 64, TY, 1>(a2, StepIO<T, L1>{a, s1, x0, y0}, tile_linear, tid, s2);
+    } else {
+        __syncthreads();  // stage_compute's
+    }
+}
+
+// One solve's step from src to dst, its descriptor and list entry by value.
+template <typename T, int EQN, bool BATHY, int TY>
+__global__ __launch_bounds__(64 * (TY + 4)) void step_one_kernel(BatchSolve d, WorkItem it, const void *src, void *dst,
+                                                                  int tiles_x, int ntiles)
+{
+    const int w = xcd_tile(blockIdx.x, gridDim.x);
+    if (w >= ntiles) return;
+    StageArgs<T> a;
+    (void)batch_fill<T, 2, 0>(d, it, 0, a);
+    a.qs = a.q0 = (const T *)src;
+    a.out = (T *)dst;
+    const int ty = w / tiles_x, tx = w - ty * tiles_x;
+    step_tile<T, EQN, BATHY, HLLE, MINMOD, TY>(a, tx * STEP_X, ty * TY, w, threadIdx.x);
 }
 
 // ------------------------------------------------------------ CFL rate of q
@@ -944,6 +1079,30 @@ hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, cons
     batch_kernel(eqn, bathy, stage, shape, fn, &threads);
     void *args[] = {(void *)&d, (void *)&it, (void *)&grid};
     return hipLaunchKernel(fn[1], dim3(xcd_grid(grid)), dim3(threads), args, 0, st);
+}
+
+template <int TY>
+static hipError_t step_one_go(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
+                              hipStream_t st)
+{
+    int tiles_x = (d.nx + STEP_X - 1) / STEP_X, ntiles = tiles_x * ((d.ny + TY - 1) / TY);
+    const void *fn = eqn == EULER ? (const void *)step_one_kernel<float, EULER, false, TY>
+                     : bathy      ? (const void *)step_one_kernel<float, SWE, true, TY>
+                                  : (const void *)step_one_kernel<float, SWE, false, TY>;
+    void *args[] = {(void *)&d, (void *)&it, (void *)&src, (void *)&dst, (void *)&tiles_x, (void *)&ntiles};
+    return hipLaunchKernel(fn, dim3(xcd_grid(ntiles)), dim3(64 * (TY + 4)), args, 0, st);
+}
+
+hipError_t launch_step_one(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
+                           hipStream_t st)
+{
+    if (it.tile_begin != 0 || d.nx < 4 || d.ny < 4 || src == dst) return hipErrorInvalidValue;
+    // the fewest rows whose tiles all get a CU of their own, else the most
+    // (least of the first stage computed twice)
+    auto tiles = [&](int ty) { return (d.nx + STEP_X - 1) / STEP_X * ((d.ny + ty - 1) / ty); };
+    return tiles(4) <= 256   ? step_one_go<4>(eqn, bathy, d, it, src, dst, st)
+           : tiles(8) <= 256 ? step_one_go<8>(eqn, bathy, d, it, src, dst, st)
+                             : step_one_go<12>(eqn, bathy, d, it, src, dst, st);
 }
 
 hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,

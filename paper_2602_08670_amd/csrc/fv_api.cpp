@@ -210,17 +210,20 @@ fv_status enqueue_step(fv_solver *s)
     return FV_OK;
 }
 
-// nsteps steps.  Small grids of the batched kind go two steps at a time, each
-// a launch, from the state to its stage buffer and back; an odd step at the
-// end takes its two stages' launches.
+// nsteps steps.  Small grids go two steps at a time, each a launch, from the
+// state to its stage buffer and back; an odd step at the end takes a launch
+// per stage.
 fv_status enqueue_run(fv_solver *s, int64_t nsteps)
 {
     int64_t k = 0;
-    if (s->batched && fvk::step_fits(s->cfg.nx, s->cfg.ny)) {
+    if (fvk::step_fits(s->d, s->cfg.rk_stages)) {
+        const bool cfl = !(s->cfg.dt_fixed > 0);
+        void *const S1 = s->ws + s->L.s1;
         for (; k + 2 <= nsteps; k += 2)
             for (int h = 0; h < 2; h++, s->enq++) {
-                void *const src = h ? s->bd.s1 : s->bd.q, *const dst = h ? s->bd.q : s->bd.s1;
-                hipError_t e = fvk::launch_step_one(s->d.eqn, s->d.bathy, s->bd, s->bi[s->enq % 3], src, dst, s->stream);
+                const int n = (int)(s->enq % 3);
+                hipError_t e = fvk::launch_step(s->d, s->cfg.rk_stages, h ? S1 : s->q, h ? s->q : S1, s->bed, s->ctl(),
+                                                s->rates(), n, cfl ? (n + 1) % 3 : -1, cfl ? (n + 2) % 3 : -1, s->stream);
                 if (e != hipSuccess) return hip_fail(e, "step launch");
             }
     }

@@ -409,23 +409,40 @@ __device__ __forceinline__ void eul_face(T *QL, T *QR, const T *CL, const T *CR,
         pl = eul_prim(QL, NM, TM, gm1, irl, ul, vl);
         pr = eul_prim(QR, NM, TM, gm1, irr, ur, vr);
     }
-    if constexpr (FLUX != HLLE) {
-        const EulS<T> L{QL[0], QL[NM], QL[TM], QL[3]}, R{QR[0], QR[NM], QR[TM], QR[3]};
-        T G[4];
-        eul_numflux<T, FLUX>(L, R, ph.gamma, G);
-        F[0] = G[0];
-        F[NM] = G[1];
-        F[TM] = G[2];
-        F[3] = G[3];
-        return;
-    }
     const T cl = fsqrt((ph.gamma * pl) * irl), cr = fsqrt((ph.gamma * pr) * irr);
     const T Hl = (QL[3] + pl) * irl, Hr = (QR[3] + pr) * irr;
     const T dr = QR[0] - QL[0], dm = QR[NM] - QL[NM], du = ur - ul, dv = vr - vl, dH = Hr - Hl, dp = pr - pl;
+    const T ml = QL[NM], mr = QR[NM], dt = QR[TM] - QL[TM], dE = QR[3] - QL[3];
+    // twice the mean flux of the two states
+    const T s0 = ml + mr, s1 = tfma(mr, ur, ml * ul) + (pl + pr), s2 = tfma(mr, vr, ml * vl), s3 = tfma(mr, Hr, ml * Hl);
+    if constexpr (FLUX == RUSANOV) {
+        const T a = tmax(tabs(ul) + cl, tabs(ur) + cr);
+        F[0] = T(0.5) * tfma(-a, dr, s0);
+        F[NM] = T(0.5) * tfma(-a, dm, s1);
+        F[TM] = T(0.5) * tfma(-a, dt, s2);
+        F[3] = T(0.5) * tfma(-a, dE, s3);
+        return;
+    }
     const T wl = fsqrt(QL[0]), wr = fsqrt(QR[0]);
     const T k = wr * rcp(wl + wr);
     const T ua = tfma(k, du, ul), va = tfma(k, dv, vl), Ha = tfma(k, dH, Hl);
     const T ca = fsqrt(tmax(gm1 * tfma(T(-0.5), tfma(va, va, ua * ua), Ha), T(0)));
+    if constexpr (FLUX == ROE) {
+        // acoustic u - c, entropy u, shear u, acoustic u + c
+        const T a3 = tfma(-va, dr, dt);
+        const T d5 = tfma(-a3, va, dE);
+        const T a2 = gm1 * rcp(ca * ca) * (tfma(dr, tfma(-ua, ua, Ha), ua * dm) - d5);
+        const T a1 = (tfma(dr, ua + ca, -dm) - ca * a2) * rcp(T(2) * ca);
+        const T a4 = dr - (a1 + a2);
+        const T w1 = tabs(ua - ca) * a1, w2 = tabs(ua) * a2, w3 = tabs(ua) * a3, w4 = tabs(ua + ca) * a4;
+        const T w = w1 + w2 + w4;
+        F[0] = T(0.5) * (s0 - w);
+        F[NM] = T(0.5) * (s1 - tfma(w, ua, ca * (w4 - w1)));
+        F[TM] = T(0.5) * (s2 - tfma(w, va, w3));
+        F[3] = T(0.5) * (s3 - tfma(w1, tfma(-ua, ca, Ha), tfma(w4, tfma(ua, ca, Ha),
+                                   tfma(w2, T(0.5) * tfma(ua, ua, va * va), w3 * va))));
+        return;
+    }
     const T sL = tmin(tmin(ul - cl, ua - ca), T(0));
     const T sR = tmax(tmax(ur + cr, ua + ca), T(0));
     const T t = sL * rcp(sR - sL);  // sR - sL >= c~ > 0 for admissible states

@@ -51,6 +51,33 @@ hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void
                         double a0, double a1, Ctl *ctl, unsigned long long *rates, int rate_in, int rate_out,
                         int rate_clear, int last, hipStream_t st);
 
+// A whole step of 1, 2 or 3 stages from src to dst (not the same buffer) in
+// one launch, with the last stage's bookkeeping.
+hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
+                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, hipStream_t st);
+// The grids that step so.  One stage: no ring, and no copy back to the state
+// (16 steps of 500^2 cells 86 us, with a launch and a copy 151, 1400^2 324 and
+// 453): all.  FP32 Heun HLLE with MINMOD, in tiles of up to 12 rows: up to where the rings cost what
+// the launches do (800^2 272 us and 286 with a launch per stage, 1000 x 700
+// Euler 322 and 323, 1024^2 425 and 327).  The others, in 4 or 8 rows: while
+// every tile has a CU of its own (FP32 Roe Heun 320^2 108 and 143, 500^2 189
+// and 183; FP64 Heun 320^2 160 and 201; FP64 Roe in three stages, 4 rows:
+// 200^2 193 and 242, 250^2 352 and 245).
+inline int step_rows(const StageDesc &d, int stages)  // most rows of a tile
+{
+    if (stages == 1 || (stages == 3 && d.prec == 1)) return 4;
+    return stages == 2 && d.prec == 0 && d.flux == 0 && d.recon == 0 ? 12 : 8;
+}
+inline bool step_fits(const StageDesc &d, int stages)
+{
+    const int64_t cells = (int64_t)d.nx * d.ny;
+    if (d.nx < 2 * stages || d.ny < 2 * stages) return false;
+    const int rows = step_rows(d, stages), cols = 64 - 4 * (stages - 1);
+    if (stages == 1) return true;
+    if (rows == 12) return cells <= 640000;
+    return (int64_t)((d.nx + cols - 1) / cols) * ((d.ny + rows - 1) / rows) <= 256;
+}
+
 // Batched FP32 Heun stages over many solves (serving).  BatchSolve is one
 // solve's device descriptor; WorkItem one solve of a step's list: where its
 // workgroups start in the launch and its CFL slots at that step.
@@ -104,13 +131,6 @@ hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const Ba
 // launches of a single solve.
 hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
                                   int grid, hipStream_t st);
-// One solve's whole Heun step from src to dst (its state or s1, not the same
-// one) in one launch; sides of four cells and more.
-// Larger grids gain nothing (16 steps of 800^2 cells 272 us and 286 as two
-// launches, 1000 x 700 Euler 322 and 323) and lose by the ring (1024^2 425, 327).
-inline bool step_fits(int nx, int ny) { return nx >= 4 && ny >= 4 && (int64_t)nx * ny <= 640000; }
-hipError_t launch_step_one(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
-                           hipStream_t st);
 // The form recorded in graphs: wgs workgroups (a multiple of 8, set to
 // xcd_grid(tiles) before each replay), the tile count read from the list
 // header list = {items, tiles}.

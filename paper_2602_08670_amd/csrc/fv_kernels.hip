@@ -21,6 +21,8 @@
 #include "fv_device.hpp"
 #include "fv_internal.hpp"
 
+#include <type_traits>
+
 namespace fvk {
 
 __device__ __forceinline__ int map_index(int i, int n, int bc, bool &flip)
@@ -638,125 +640,172 @@ __global__ __launch_bounds__((ShapeLds<T, EQN, BATHY, SHAPE>::NTH), shape_waves(
                                                                                         threadIdx.x);
 }
 
-// ------------------------------------------------- a Heun step in one launch
-// Both stages of a tile of STEP_X x TY cells in one workgroup, from one buffer
-// to another: the first stage on the tile and its two-cell ring (STEP_X + 4 =
-// 64 columns, a wave64 per row), its result in LDS as the second stage's halo
-// tile.  Ghost cells of the result past a wall are mirrored from it, as the
-// second stage's loads would mirror them; past a periodic border they are
-// computed from the same values as their images.  The same arithmetic as the
-// two launches, so the same bits.  A frozen solve's cells are carried over.
-// On small grids a launch is its chain (start, load, two barriers, store) and
-// little work: 16 steps over a bed, two launches a step and one: 64^2 128 and
-// 95 us, 256^2 131 and 103, 400^2 160 and 115, 600^2 192 and 143.
-constexpr int STEP_X = 60;
+// ---------------------------------------------------- a step in one launch
+// All S stages of a tile of step_cols(S) x TY cells in one workgroup, from one
+// buffer to another: stage k on the tile and its 2 (S - k)-cell ring (64
+// columns in the first, a wave64 per row), its result in LDS as the next
+// stage's halo tile.  Ghost cells of a result past a wall are mirrored from
+// it, as the next stage's loads would mirror them; past a periodic border they
+// are computed from the same values as their images.  The same arithmetic as
+// a launch per stage, so the same bits.  A frozen solve's cells are carried
+// over.  On small grids a launch is its chain (start, load, two barriers,
+// store) and little work: 16 Heun steps over a bed, a launch per stage and
+// one: 64^2 128 and 95 us, 256^2 131 and 103, 400^2 160 and 115, 600^2 192 and
+// 143.
+constexpr int step_cols(int s) { return 64 - 4 * (s - 1); }
 
-// The first stage's results to LDS, all of them.
-template <typename T, typename L2> struct RingIO {
+// Stage K's results to LDS, all of them; q0 from the first stage's halo tile.
+template <typename T, int K, typename L1, typename L2> struct RingIO {
     static constexpr bool GLOBAL = false;
+    const L1 &from;
     L2 &to;
     __device__ __forceinline__ bool in(int, int) const { return true; }
-    __device__ __forceinline__ T q0(int, int, int) const { return T(0); }
+    __device__ __forceinline__ T q0(int v, int cy, int lane) const
+    {
+        return from.q[v][cy + 2 * K][min(lane + 2 * K, L1::HX - 1)];
+    }
     __device__ __forceinline__ void put(int v, int cy, int lane, T o) const { to.q[v][cy][lane] = o; }
-    __device__ __forceinline__ void keep(int cy, int lane, const T *q0r) const
+    __device__ __forceinline__ void keep(int cy, int lane, const T *) const
     {
 #pragma unroll
-        for (int v = 0; v < L2::NV; v++) to.q[v][cy][lane] = T(0);
+        for (int v = 0; v < L1::NV; v++) to.q[v][cy][lane] = T(0);
     }
 };
-// The second stage's: q0 from the first stage's halo tile.
-template <typename T, typename L1> struct StepIO {
+// The last stage's (K of K).
+template <typename T, int K, typename L1> struct StepIO {
     static constexpr bool GLOBAL = false;
     const StageArgs<T> &a;
     const L1 &from;
     int x0, y0;
     __device__ __forceinline__ bool in(int cy, int lane) const
     {
-        return lane < STEP_X && x0 + lane < a.nx && y0 + cy < a.ny;
+        return lane < step_cols(K) && x0 + lane < a.nx && y0 + cy < a.ny;
     }
-    __device__ __forceinline__ T q0(int v, int cy, int lane) const { return from.q[v][cy + 4][min(lane, STEP_X) + 4]; }
+    __device__ __forceinline__ T q0(int v, int cy, int lane) const
+    {
+        return from.q[v][cy + 2 * K][min(lane + 2 * K, L1::HX - 1)];
+    }
     __device__ __forceinline__ void put(int v, int cy, int lane, T o) const
     {
         *st_off(a.out + v * ((size_t)a.nx * a.ny) + (size_t)y0 * a.nx + x0, (unsigned)(cy * a.nx + lane)) = o;
     }
-    __device__ __forceinline__ void keep(int cy, int lane, const T *q0r) const
+    __device__ __forceinline__ void keep(int cy, int lane, const T *) const
     {
 #pragma unroll
-        for (int v = 0; v < L1::NV; v++) put(v, cy, lane, q0r[v]);
+        for (int v = 0; v < L1::NV; v++) put(v, cy, lane, q0(v, cy, lane));
     }
 };
 
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TY>
-__device__ __forceinline__ void step_tile(const StageArgs<T> &a, const int x0, const int y0, const int tile_linear,
-                                          const int tid)
-{
-    constexpr int RY = TY + 4;  // rows of the first stage, a wave each
-    using L1 = StageLds<T, EQN, BATHY, 64, RY, 1>;
-    using L2 = StageLds<T, EQN, BATHY, 64, TY, 1>;
-    constexpr int NV = L1::NV;
-    __shared__ L1 s1;
-    __shared__ L2 s2;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nx = a.nx, ny = a.ny, ox = x0 - 2, oy = y0 - 2;  // origin of the first stage's cells
-    StageArgs<T> a1 = a, a2 = a;
-    a1.a0 = T(0);
-    a1.a1 = T(1);
-    a1.last = 0;
-    a2.a0 = T(0.5);
-    a2.a1 = T(0.5);
-    a2.last = 1;
-    // the ring's image of this lane's cell, and the bed there
+// This lane's cell of a stage's region from (ox, oy): its image in the grid
+// and the bed there.
+template <typename T, bool BATHY> struct RingCell {
+    int gx, gy;
     bool fx = false, fy = false;
-    const int gx = ghost_index(ox + lane, nx, a.bc_x, fx), gy = ghost_index(oy + wave, ny, a.bc_y, fy);
     T bed = T(0);
+    __device__ __forceinline__ RingCell(const StageArgs<T> &a, int ox, int oy, int wave, int lane)
     {
-        HaloRegs<T, EQN, BATHY, 64, RY, 1> r;
-        if (inner_tile<64, RY>(ox, oy, nx, ny)) halo_issue<T, EQN, BATHY, 64, RY, 1, false>(a1, ox, oy, tid, r);
-        else halo_issue<T, EQN, BATHY, 64, RY, 1, true>(a1, ox, oy, tid, r);
-        if (BATHY) bed = ld_off(a.bed + (size_t)gy * nx, (unsigned)gx);
-        stage_dt(a1, tid, s1);
-        halo_commit(r, s1, tid);
+        gx = ghost_index(ox + lane, a.nx, a.bc_x, fx);
+        gy = ghost_index(oy + wave, a.ny, a.bc_y, fy);
+        if (BATHY) bed = ld_off(a.bed + (size_t)gy * a.nx, (unsigned)gx);
     }
+};
+
+// A stage's result in `to` (ROWS x 64 places from (ox, oy), a wave per row)
+// made the next stage's halo tile: the free surface, and in a cell past a wall
+// its image's values with the normal momentum negated.  Every wave calls it.
+template <typename T, bool BATHY, int ROWS, typename L>
+__device__ __forceinline__ void ring_close(const StageArgs<T> &a, const RingCell<T, BATHY> &r, L &to, int ox, int oy,
+                                           int wave, int lane)
+{
+    constexpr int NV = L::NV;
     __syncthreads();
-    if (tid == 0) s2.dt = s1.dt;
-    stage_compute<T, EQN, BATHY, FLUX, RECON, 64, RY, 1>(a1, RingIO<T, L2>{s2}, tile_linear, tid, s1);
-    __syncthreads();
-    // a cell past a wall takes its image's values, the normal momentum negated
     T m[NV];
-    {
-        const int lx = fx ? min(max(gx - ox, 0), 63) : lane, ly = fy ? min(max(gy - oy, 0), RY - 1) : wave;
+    if (wave < ROWS) {
+        const int lx = r.fx ? min(max(r.gx - ox, 0), 63) : lane, ly = r.fy ? min(max(r.gy - oy, 0), ROWS - 1) : wave;
 #pragma unroll
-        for (int v = 0; v < NV; v++) m[v] = s2.q[v][ly][lx];
-        m[1] = fx ? -m[1] : m[1];
-        m[2] = fy ? -m[2] : m[2];
+        for (int v = 0; v < NV; v++) m[v] = to.q[v][ly][lx];
+        m[1] = r.fx ? -m[1] : m[1];
+        m[2] = r.fy ? -m[2] : m[2];
+        if constexpr (BATHY) to.q[NV][wave][lane] = m[0] + r.bed;
     }
-    if (BATHY) s2.q[NV][wave][lane] = m[0] + bed;
-    if ((a.bc_x != 0 || a.bc_y != 0) && !(ox >= 0 && oy >= 0 && ox + 64 <= nx && oy + RY <= ny)) {
+    if ((a.bc_x != 0 || a.bc_y != 0) && !(ox >= 0 && oy >= 0 && ox + 64 <= a.nx && oy + ROWS <= a.ny)) {
         __syncthreads();  // a cell's image may be another wave's
+        if (wave < ROWS) {
 #pragma unroll
-        for (int v = 0; v < NV; v++) s2.q[v][wave][lane] = m[v];
+            for (int v = 0; v < NV; v++) to.q[v][wave][lane] = m[v];
+        }
     }
     __syncthreads();
-    if (wave < TY) {
-        stage_compute<T, EQN, BATHY, FLUX, RECON, 64, TY, 1>(a2, StepIO<T, L1>{a, s1, x0, y0}, tile_linear, tid, s2);
-    } else {
-        __syncthreads();  // stage_compute's
-    }
 }
 
-// One solve's step from src to dst, its descriptor and list entry by value.
-template <typename T, int EQN, bool BATHY, int TY>
-__global__ __launch_bounds__(64 * (TY + 4)) void step_one_kernel(BatchSolve d, WorkItem it, const void *src, void *dst,
-                                                                  int tiles_x, int ntiles)
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int S, int TY>
+__global__ __launch_bounds__(64 * (TY + 4 * (S - 1))) void step_kernel(StageArgs<T> a, int tiles_x, int ntiles)
 {
+    constexpr int R1 = TY + 4 * (S - 1);  // rows of the first stage, a wave each
+    using L1 = StageLds<T, EQN, BATHY, 64, R1, 1>;
+    __shared__ L1 s1;
     const int w = xcd_tile(blockIdx.x, gridDim.x);
     if (w >= ntiles) return;
-    StageArgs<T> a;
-    (void)batch_fill<T, 2, 0>(d, it, 0, a);
-    a.qs = a.q0 = (const T *)src;
-    a.out = (T *)dst;
     const int ty = w / tiles_x, tx = w - ty * tiles_x;
-    step_tile<T, EQN, BATHY, HLLE, MINMOD, TY>(a, tx * STEP_X, ty * TY, w, threadIdx.x);
+    const int x0 = tx * step_cols(S), y0 = ty * TY;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto weights = [&](double a0, double a1, int last) {
+        StageArgs<T> b = a;
+        b.a0 = (T)a0;
+        b.a1 = (T)a1;
+        b.last = last;
+        return b;
+    };
+    const StageArgs<T> e1 = weights(0.0, 1.0, S == 1);
+    const int o1 = 2 * (S - 1);  // the first stage's ring
+    auto load = [&] {
+        HaloRegs<T, EQN, BATHY, 64, R1, 1> r;
+        if (inner_tile<64, R1>(x0 - o1, y0 - o1, a.nx, a.ny))
+            halo_issue<T, EQN, BATHY, 64, R1, 1, false>(e1, x0 - o1, y0 - o1, tid, r);
+        else
+            halo_issue<T, EQN, BATHY, 64, R1, 1, true>(e1, x0 - o1, y0 - o1, tid, r);
+        stage_dt(e1, tid, s1);
+        halo_commit(r, s1, tid);
+        __syncthreads();
+    };
+    if constexpr (S == 1) {
+        load();
+        stage_compute<T, EQN, BATHY, FLUX, RECON, 64, R1, 1>(e1, StepIO<T, 1, L1>{a, s1, x0, y0}, w, tid, s1);
+    } else {
+        using L2 = StageLds<T, EQN, BATHY, 64, R1 - 4, 1>;
+        __shared__ L2 s2;
+        const RingCell<T, BATHY> c1(a, x0 - o1, y0 - o1, wave, lane);
+        if constexpr (S == 2) {
+            load();
+            if (tid == 0) s2.dt = s1.dt;
+            stage_compute<T, EQN, BATHY, FLUX, RECON, 64, R1, 1>(e1, RingIO<T, 1, L1, L2>{s1, s2}, w, tid, s1);
+            ring_close<T, BATHY, R1>(a, c1, s2, x0 - o1, y0 - o1, wave, lane);
+            if (wave < TY)
+                stage_compute<T, EQN, BATHY, FLUX, RECON, 64, TY, 1>(weights(0.5, 0.5, 1), StepIO<T, 2, L1>{a, s1, x0, y0},
+                                                                     w, tid, s2);
+            else
+                __syncthreads();  // stage_compute's
+        } else {
+            using L3 = StageLds<T, EQN, BATHY, 64, TY, 1>;
+            __shared__ L3 s3;
+            const RingCell<T, BATHY> c2(a, x0 - 2, y0 - 2, wave, lane);
+            load();
+            if (tid == 0) s2.dt = s3.dt = s1.dt;
+            stage_compute<T, EQN, BATHY, FLUX, RECON, 64, R1, 1>(e1, RingIO<T, 1, L1, L2>{s1, s2}, w, tid, s1);
+            ring_close<T, BATHY, R1>(a, c1, s2, x0 - o1, y0 - o1, wave, lane);
+            if (wave < R1 - 4)
+                stage_compute<T, EQN, BATHY, FLUX, RECON, 64, R1 - 4, 1>(weights(0.75, 0.25, 0),
+                                                                         RingIO<T, 2, L1, L3>{s1, s3}, w, tid, s2);
+            else
+                __syncthreads();
+            ring_close<T, BATHY, R1 - 4>(a, c2, s3, x0 - 2, y0 - 2, wave, lane);
+            if (wave < TY)
+                stage_compute<T, EQN, BATHY, FLUX, RECON, 64, TY, 1>(weights(1.0 / 3.0, 2.0 / 3.0, 1),
+                                                                     StepIO<T, 3, L1>{a, s1, x0, y0}, w, tid, s3);
+            else
+                __syncthreads();
+        }
+    }
 }
 
 // ------------------------------------------------------------ CFL rate of q
@@ -911,12 +960,11 @@ __global__ void face_kernel(const T *q, int nx, int ny, int bc_x, int bc_y, Phys
 
 // ----------------------------------------------------------------- dispatch
 
-template <typename T, int EQN, bool BATHY, int FLUX, int RECON>
-static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
-                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
-                          hipStream_t st)
+template <typename T>
+static StageArgs<T> stage_args(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, Ctl *ctl,
+                               unsigned long long *rates, int ri, int ro, int rc)
 {
-    StageArgs<T> a;
+    StageArgs<T> a{};
     a.qs = (const T *)qs;
     a.q0 = (const T *)q0;
     a.out = (T *)out;
@@ -931,8 +979,6 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
     a.ph.sqg = (T)__builtin_sqrt(d.g);
     a.ph.gamma = (T)d.gamma;
     a.ph.h0 = (T)d.h0;
-    a.a0 = (T)a0;
-    a.a1 = (T)a1;
     a.cfl = d.cfl;
     a.dt_fixed = d.dt_fixed;
     a.ctl = ctl;
@@ -940,6 +986,17 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
     a.rate_in = ri;
     a.rate_out = ro;
     a.rate_clear = rc;
+    return a;
+}
+
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON>
+static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
+                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
+                          hipStream_t st)
+{
+    StageArgs<T> a = stage_args<T>(d, qs, q0, out, bed, ctl, rates, ri, ro, rc);
+    a.a0 = (T)a0;
+    a.a1 = (T)a1;
     a.last = last;
     // the shapes with one and with two rows per wave serve every scheme, the
     // other two FP32 HLLE with MINMOD (the scheme of long runs)
@@ -1000,6 +1057,66 @@ hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void
     if (d.prec == 1)
         return stage_p<double>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, last, st);
     return stage_p<float>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, last, st);
+}
+
+// The tile rows of a step's launch: the fewest whose tiles all get a CU of
+// their own, else the most (least of the earlier stages computed twice).
+template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int S>
+static hipError_t step_s(const StageDesc &d, const StageArgs<T> &a, hipStream_t st)
+{
+    auto go = [&](auto rows) {
+        constexpr int TY = decltype(rows)::value;
+        const int tiles_x = (d.nx + step_cols(S) - 1) / step_cols(S), ntiles = tiles_x * ((d.ny + TY - 1) / TY);
+        hipLaunchKernelGGL((step_kernel<T, EQN, BATHY, FLUX, RECON, S, TY>), dim3(xcd_grid(ntiles)),
+                           dim3(64 * (TY + 4 * (S - 1))), 0, st, a, tiles_x, ntiles);
+        return hipGetLastError();
+    };
+    const int most = step_rows(d, S);
+    const int64_t cols = (d.nx + step_cols(S) - 1) / step_cols(S);
+    const bool four = cols * ((d.ny + 3) / 4) <= 256, eight = cols * ((d.ny + 7) / 8) <= 256;
+    if (four || most == 4) return go(std::integral_constant<int, 4>{});
+    if constexpr (S == 2 || (S == 3 && sizeof(T) == 4)) {
+        if constexpr (S == 2 && sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD)
+            if (!eight) return go(std::integral_constant<int, 12>{});
+        return go(std::integral_constant<int, 8>{});
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename T, int EQN, bool BATHY, int FLUX>
+static hipError_t step_f(const StageDesc &d, int stages, const StageArgs<T> &a, hipStream_t st)
+{
+#define FV_STEP(RC)                                                                        \
+    (stages == 1   ? step_s<T, EQN, BATHY, FLUX, RC, 1>(d, a, st)                          \
+     : stages == 2 ? step_s<T, EQN, BATHY, FLUX, RC, 2>(d, a, st)                          \
+                   : step_s<T, EQN, BATHY, FLUX, RC, 3>(d, a, st))
+    return d.recon == FIRST ? FV_STEP(FIRST) : FV_STEP(MINMOD);
+#undef FV_STEP
+}
+
+template <typename T, int EQN, bool BATHY>
+static hipError_t step_e(const StageDesc &d, int stages, const StageArgs<T> &a, hipStream_t st)
+{
+    return d.flux == RUSANOV ? step_f<T, EQN, BATHY, RUSANOV>(d, stages, a, st)
+           : d.flux == ROE   ? step_f<T, EQN, BATHY, ROE>(d, stages, a, st)
+                             : step_f<T, EQN, BATHY, HLLE>(d, stages, a, st);
+}
+
+template <typename T>
+static hipError_t step_p(const StageDesc &d, int stages, const StageArgs<T> &a, hipStream_t st)
+{
+    return d.eqn == EULER ? step_e<T, EULER, false>(d, stages, a, st)
+           : d.bathy      ? step_e<T, SWE, true>(d, stages, a, st)
+                          : step_e<T, SWE, false>(d, stages, a, st);
+}
+
+hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
+                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, hipStream_t st)
+{
+    if (stages < 1 || stages > 3 || d.nx < 2 * stages || d.ny < 2 * stages || src == dst) return hipErrorInvalidValue;
+    return d.prec == 1
+               ? step_p<double>(d, stages, stage_args<double>(d, src, src, dst, bed, ctl, rates, rate_in, rate_out, rate_clear), st)
+               : step_p<float>(d, stages, stage_args<float>(d, src, src, dst, bed, ctl, rates, rate_in, rate_out, rate_clear), st);
 }
 
 template <typename T>
@@ -1079,30 +1196,6 @@ hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, cons
     batch_kernel(eqn, bathy, stage, shape, fn, &threads);
     void *args[] = {(void *)&d, (void *)&it, (void *)&grid};
     return hipLaunchKernel(fn[1], dim3(xcd_grid(grid)), dim3(threads), args, 0, st);
-}
-
-template <int TY>
-static hipError_t step_one_go(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
-                              hipStream_t st)
-{
-    int tiles_x = (d.nx + STEP_X - 1) / STEP_X, ntiles = tiles_x * ((d.ny + TY - 1) / TY);
-    const void *fn = eqn == EULER ? (const void *)step_one_kernel<float, EULER, false, TY>
-                     : bathy      ? (const void *)step_one_kernel<float, SWE, true, TY>
-                                  : (const void *)step_one_kernel<float, SWE, false, TY>;
-    void *args[] = {(void *)&d, (void *)&it, (void *)&src, (void *)&dst, (void *)&tiles_x, (void *)&ntiles};
-    return hipLaunchKernel(fn, dim3(xcd_grid(ntiles)), dim3(64 * (TY + 4)), args, 0, st);
-}
-
-hipError_t launch_step_one(int eqn, int bathy, const BatchSolve &d, const WorkItem &it, const void *src, void *dst,
-                           hipStream_t st)
-{
-    if (it.tile_begin != 0 || d.nx < 4 || d.ny < 4 || src == dst) return hipErrorInvalidValue;
-    // the fewest rows whose tiles all get a CU of their own, else the most
-    // (least of the first stage computed twice)
-    auto tiles = [&](int ty) { return (d.nx + STEP_X - 1) / STEP_X * ((d.ny + ty - 1) / ty); };
-    return tiles(4) <= 256   ? step_one_go<4>(eqn, bathy, d, it, src, dst, st)
-           : tiles(8) <= 256 ? step_one_go<8>(eqn, bathy, d, it, src, dst, st)
-                             : step_one_go<12>(eqn, bathy, d, it, src, dst, st);
 }
 
 hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,

@@ -58,8 +58,6 @@ __device__ __forceinline__ void blend_limiter(const float (*st)[6], float *phi)
     }
 }
 
-__device__ __forceinline__ int pw(int i, int n) { return ((i % n) + n) % n; }
-
 // MINMOD face states of one variable and their derivatives with respect to
 // the stencil cells k = 0..5 (only k = 1..4 are touched).  Branch rules as in
 // the forward: minmod picks a when |a| <= |b| and both share a sign.
@@ -88,6 +86,22 @@ __device__ __forceinline__ void minmod_right(const float *c, float &val, float *
     if (pb) { dv[4] -= 0.5f; dv[3] += 0.5f; }
 }
 
+// The six cells of a periodic line from offset `first` to the cell (x, y)
+// along an axis: one wrap and then steps (an integer remainder per cell was
+// half of the face kernel's instructions).
+__device__ __forceinline__ void line_cells(int axis, int x, int y, int nx, int ny, int first, int (&idx)[6])
+{
+    const int n = axis == 0 ? nx : ny, step = axis == 0 ? 1 : nx, base = axis == 0 ? y * nx : x;
+    int p = (axis == 0 ? x : y) + first;
+#pragma unroll
+    for (int k = 0; k < 3; k++) p = p < 0 ? p + n : p;
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        idx[k] = base + p * step;
+        p = p + 1 == n ? 0 : p + 1;
+    }
+}
+
 // DIR: the direct face-state scheme (section 5.3): the face's left state is
 // the owner's right (top) state and its right state the neighbour's left
 // (bottom) state; a side's depth is h_c softplus(sig_h z_h + c) and its
@@ -101,30 +115,57 @@ __device__ __forceinline__ void minmod_right(const float *c, float &val, float *
 // averages by the flux limiter (blend_limiter, phi frozen): the learned path
 // receives phi g_F and the cell averages of the face (stencil entries 2 and
 // 3) the low-resolution flux's Jacobian times (1 - phi) g_F.
+constexpr int ADJ_CELLS = 128;  // cells of a workgroup
+constexpr int ADJ_ZROW = 19;    // a cell's 18 float4 of z, padded: lanes of consecutive cells hit distinct banks
 template <int FLUX, bool DIR, bool BL = false>
 __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
 {
     const int nx = a.nx, ny = a.ny;
     const size_t plane = (size_t)nx * ny;
-    const size_t nfaces = (size_t)2 * a.B * plane;
-    for (size_t f = (size_t)blockIdx.x * 256 + threadIdx.x; f < nfaces; f += (size_t)gridDim.x * 256) {
-        const int axis = (int)(f / ((size_t)a.B * plane));
-        size_t r = f - (size_t)axis * a.B * plane;
-        const int b = (int)(r / plane);
-        const int cell = (int)(r - (size_t)b * plane);
-        const int y = cell / nx, x = cell - y * nx;
+    // A workgroup has the x faces (waves 0, 1) and the y faces (waves 2, 3) of
+    // ADJ_CELLS cells that follow one another in the batch's arrays: their
+    // rows of z, of the contributions and of dz are whole stretches of memory,
+    // moved as such through LDS (a lane's own 144, 80 and 72 bytes of them
+    // touch a line per lane and instruction: 20.1 us for 16 solves of 64^2,
+    // 16.0 so).
+    __shared__ __align__(16) char s_buf[DIR ? 16 : ADJ_CELLS * ADJ_ZROW * 16];
+    const unsigned total = (unsigned)(a.B * plane), c0 = blockIdx.x * ADJ_CELLS;
+    const int axis = threadIdx.x >= ADJ_CELLS, lc = threadIdx.x & (ADJ_CELLS - 1);
+    const unsigned count = total - c0 < (unsigned)ADJ_CELLS ? total - c0 : (unsigned)ADJ_CELLS;
+    float co[ADJ_REC], gzc[36];
+    if constexpr (!DIR) {
+        const float4 *z = (const float4 *)(a.z + (size_t)c0 * 72);
+        float4 t[9];
+#pragma unroll
+        for (int k = 0; k < 9; k++) t[k] = z[min(threadIdx.x + 256u * k, count * 18 - 1)];
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            const int i = threadIdx.x + 256 * k, r = i / 18;
+            ((float4 *)s_buf)[r * ADJ_ZROW + i - 18 * r] = t[k];
+        }
+        __syncthreads();
+    }
+    if ((unsigned)lc < count) {
+        const unsigned c = c0 + lc;
+        const int b = (int)(c / (unsigned)plane), cell = (int)(c - (unsigned)b * (unsigned)plane);
+        const int y = (int)((unsigned)cell / (unsigned)nx), x = cell - y * nx;
         const int NM = axis == 0 ? 1 : 2, TM = axis == 0 ? 2 : 1;
         const float *q = a.qs + (size_t)b * 3 * plane;
-        // stencil cells i-2 .. i+3 along the normal; owner i at k = 2
+        // stencil cells i-2 .. i+3 along the normal; owner i at k = 2, the cell
+        // across the face (the owner's +x or +y neighbour) at k = 3
         int idx[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++)
-            idx[k] = axis == 0 ? y * nx + pw(x - 2 + k, nx) : pw(y - 2 + k, ny) * nx + x;
+        line_cells(axis, x, y, nx, ny, -2, idx);
+        const int nbc = idx[3];
         float st[3][6];
 #pragma unroll
         for (int v = 0; v < 3; v++)
 #pragma unroll
             for (int k = 0; k < 6; k++) st[v][k] = q[v * plane + idx[k]];
+        // the output's adjoint on both sides
+        const float *go = a.gout + (size_t)b * 3 * plane;
+        float gd[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) gd[c] = go[c * plane + nbc] - go[c * plane + cell];
         const bool learned = !(a.plain && a.plain[b]);
 
         // forward recompute of the face states
@@ -151,8 +192,6 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
         float al[2][3][6];
         float QS[2][3];
         bool useL[2] = {false, false};
-        // the cell across the face (the owner's +x or +y neighbour)
-        const int nbc = axis == 0 ? y * nx + pw(x + 1, nx) : pw(y + 1, ny) * nx + x;
         float dsp[2] = {0.f, 0.f};  // direct: d depth / d z_h of each side
         if (DIR && learned) {
             const float *zo = a.z + ((size_t)b * plane + cell) * 72 + (axis == 0 ? 3 : 9);
@@ -174,9 +213,9 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
             useL[0] = QS[0][0] > 0.f;
             useL[1] = QS[1][0] > 0.f;
         } else if (learned) {
-            // this face's 36 raw coefficients: nine 16-byte loads
+            // this face's 36 raw coefficients
             float zc[36];
-            const float4 *z4 = (const float4 *)(a.z + ((size_t)b * plane + cell) * 72 + axis * 36);
+            const float4 *z4 = (const float4 *)s_buf + lc * ADJ_ZROW + axis * 9;
 #pragma unroll
             for (int q4 = 0; q4 < 9; q4++) {
                 const float4 t = z4[q4];
@@ -226,11 +265,9 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
 
         // adjoint of the face flux
         const float rd = axis == 0 ? a.rdx : a.rdy;
-        const int nb = nbc;
-        const float *go = a.gout + (size_t)b * 3 * plane;
         float gF[3];
 #pragma unroll
-        for (int c = 0; c < 3; c++) gF[c] = a.wscale * rd * (go[c * plane + nb] - go[c * plane + cell]);
+        for (int c = 0; c < 3; c++) gF[c] = a.wscale * rd * gd[c];
         // blend: the learned flux's share of the adjoint and the adjoint of
         // the low-resolution flux's states (phi frozen)
         float gH[3], gLo[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
@@ -279,7 +316,6 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
 
         // stencil contributions and coefficient adjoints, stored as 16-byte
         // vectors (the record of a face is ADJ_REC floats)
-        float co[ADJ_REC], gzc[36];
 #pragma unroll
         for (int v = 0; v < 3; v++) {
 #pragma unroll
@@ -307,11 +343,11 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
         }
 #pragma unroll
         for (int k = 18; k < ADJ_REC; k++) co[k] = 0.f;
-        float4 *co4 = (float4 *)(a.contrib + (((size_t)axis * a.B + b) * plane + cell) * ADJ_REC);
+        if constexpr (DIR) {
+            float4 *co4 = (float4 *)(a.contrib + ((size_t)axis * total + c) * ADJ_REC);
 #pragma unroll
-        for (int q4 = 0; q4 < ADJ_REC / 4; q4++)
-            co4[q4] = make_float4(co[4 * q4], co[4 * q4 + 1], co[4 * q4 + 2], co[4 * q4 + 3]);
-        if (DIR) {
+            for (int q4 = 0; q4 < ADJ_REC / 4; q4++)
+                co4[q4] = make_float4(co[4 * q4], co[4 * q4 + 1], co[4 * q4 + 2], co[4 * q4 + 3]);
             __bf16 *dzo = a.dz + ((size_t)b * plane + cell) * DZ_CH + (axis == 0 ? 3 : 9);
             __bf16 *dzn = a.dz + ((size_t)b * plane + nbc) * DZ_CH + (axis == 0 ? 0 : 6);
 #pragma unroll
@@ -319,16 +355,37 @@ __global__ __launch_bounds__(256) void adj_face_kernel(AdjArgs a)
                 dzo[v] = (__bf16)(useL[0] ? gQ[0][v] * (v == 0 ? dsp[0] : a.sig[v]) : 0.f);
                 dzn[v] = (__bf16)(useL[1] ? gQ[1][v] * (v == 0 ? dsp[1] : a.sig[v]) : 0.f);
             }
-        } else {
-            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-            bf16x4 *dz4 = (bf16x4 *)(a.dz + ((size_t)b * plane + cell) * DZ_CH + axis * 36);
+        }
+    }
+    if constexpr (!DIR) {
+        typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+        __syncthreads();  // z has been read
+        float4 *s_co = (float4 *)s_buf;                          // [axis][cell][ADJ_REC]
+        bf16x4 *s_dz = (bf16x4 *)(s_buf + 2 * ADJ_CELLS * ADJ_REC * 4);  // [cell][72]
+        static_assert(2 * ADJ_CELLS * ADJ_REC * 4 + ADJ_CELLS * 72 * 2 <= ADJ_CELLS * ADJ_ZROW * 16, "results over z");
+        if ((unsigned)lc < count) {
+#pragma unroll
+            for (int q4 = 0; q4 < ADJ_REC / 4; q4++)
+                s_co[threadIdx.x * (ADJ_REC / 4) + q4] =
+                    make_float4(co[4 * q4], co[4 * q4 + 1], co[4 * q4 + 2], co[4 * q4 + 3]);
 #pragma unroll
             for (int q4 = 0; q4 < 9; q4++) {
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; e++) o[e] = (__bf16)gzc[4 * q4 + e];
-                dz4[q4] = o;
+                s_dz[lc * 18 + axis * 9 + q4] = o;
             }
+        }
+        __syncthreads();
+        const unsigned per = count * (ADJ_REC / 4);
+#pragma unroll
+        for (int ax = 0; ax < 2; ax++) {
+            float4 *o = (float4 *)(a.contrib + ((size_t)ax * total + c0) * ADJ_REC);
+            for (unsigned i = threadIdx.x; i < per; i += 256) o[i] = s_co[ax * ADJ_CELLS * (ADJ_REC / 4) + i];
+        }
+        for (unsigned i = threadIdx.x; i < count * 18; i += 256) {
+            const unsigned r = i / 18;
+            ((bf16x4 *)(a.dz + (size_t)(c0 + r) * DZ_CH))[i - 18 * r] = s_dz[i];
         }
     }
 }
@@ -339,22 +396,23 @@ __global__ __launch_bounds__(256) void adj_gather_kernel(float *out, const float
                                                          const float *contrib, int B, int nx, int ny, int accumulate)
 {
     const size_t plane = (size_t)nx * ny;
-    const size_t n = (size_t)B * plane;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const int b = (int)(i / plane);
-        const int cell = (int)(i - (size_t)b * plane);
-        const int y = cell / nx, x = cell - y * nx;
+    const unsigned i = blockIdx.x * 256 + threadIdx.x;
+    if (i < (unsigned)(B * plane)) {
+        const int b = (int)(i / (unsigned)plane), cell = (int)(i - (unsigned)b * (unsigned)plane);
+        const int y = (int)((unsigned)cell / (unsigned)nx), x = cell - y * nx;
         float acc[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-        for (int axis = 0; axis < 2; axis++)
+        for (int axis = 0; axis < 2; axis++) {
+            // this cell is stencil entry k of the face owned by cell - (k - 2)
+            int own[6];
+            line_cells(axis, x, y, nx, ny, -3, own);
 #pragma unroll
             for (int k = 0; k < 6; k++) {
-                // this cell is stencil entry k of the face owned by cell - (k - 2)
-                int own = axis == 0 ? y * nx + pw(x + 2 - k, nx) : pw(y + 2 - k, ny) * nx + x;
-                const float *co = contrib + (((size_t)axis * B + b) * plane + own) * ADJ_REC;
+                const float *co = contrib + (((size_t)axis * B + b) * plane + own[5 - k]) * ADJ_REC;
 #pragma unroll
                 for (int v = 0; v < 3; v++) acc[v] += co[v * 6 + k];
             }
+        }
 #pragma unroll
         for (int v = 0; v < 3; v++) {
             size_t o = (size_t)b * 3 * plane + v * plane + cell;
@@ -385,8 +443,7 @@ hipError_t launch_adjoint(int flux, const AdjStage &s, hipStream_t st)
     a.contrib = s.contrib;
     a.dz = (__bf16 *)s.dz;
     for (int v = 0; v < 3; v++) a.sig[v] = s.sig[v];
-    size_t nf = (size_t)2 * s.B * s.nx * s.ny;
-    unsigned blocks = (unsigned)((nf + 255) / 256);
+    unsigned blocks = (unsigned)(((size_t)s.B * s.nx * s.ny + ADJ_CELLS - 1) / ADJ_CELLS);
     if (s.direct && s.blend) return hipErrorInvalidValue;
     if (s.direct) {
         if (flux == 1) hipLaunchKernelGGL((adj_face_kernel<fvk::RUSANOV, true>), dim3(blocks), dim3(256), 0, st, a);

@@ -702,7 +702,7 @@ template <typename T, bool BATHY> struct RingCell {
     int gx, gy;
     bool fx = false, fy = false;
     T bed = T(0);
-    __device__ __forceinline__ RingCell(const StageArgs<T> &a, int ox, int oy, int wave, int lane)
+    __device__ __forceinline__ void set(const StageArgs<T> &a, int ox, int oy, int wave, int lane)
     {
         gx = ghost_index(ox + lane, a.nx, a.bc_x, fx);
         gy = ghost_index(oy + wave, a.ny, a.bc_y, fy);
@@ -758,12 +758,15 @@ __global__ __launch_bounds__(64 * (TY + 4 * (S - 1))) void step_kernel(StageArgs
     };
     const StageArgs<T> e1 = weights(0.0, 1.0, S == 1);
     const int o1 = 2 * (S - 1);  // the first stage's ring
+    RingCell<T, BATHY> c1, c2;
     auto load = [&] {
         HaloRegs<T, EQN, BATHY, 64, R1, 1> r;
         if (inner_tile<64, R1>(x0 - o1, y0 - o1, a.nx, a.ny))
             halo_issue<T, EQN, BATHY, 64, R1, 1, false>(e1, x0 - o1, y0 - o1, tid, r);
         else
             halo_issue<T, EQN, BATHY, 64, R1, 1, true>(e1, x0 - o1, y0 - o1, tid, r);
+        if (S > 1) c1.set(a, x0 - o1, y0 - o1, wave, lane);
+        if (S > 2) c2.set(a, x0 - 2, y0 - 2, wave, lane);
         stage_dt(e1, tid, s1);
         halo_commit(r, s1, tid);
         __syncthreads();
@@ -774,7 +777,6 @@ __global__ __launch_bounds__(64 * (TY + 4 * (S - 1))) void step_kernel(StageArgs
     } else {
         using L2 = StageLds<T, EQN, BATHY, 64, R1 - 4, 1>;
         __shared__ L2 s2;
-        const RingCell<T, BATHY> c1(a, x0 - o1, y0 - o1, wave, lane);
         if constexpr (S == 2) {
             load();
             if (tid == 0) s2.dt = s1.dt;
@@ -788,7 +790,6 @@ __global__ __launch_bounds__(64 * (TY + 4 * (S - 1))) void step_kernel(StageArgs
         } else {
             using L3 = StageLds<T, EQN, BATHY, 64, TY, 1>;
             __shared__ L3 s3;
-            const RingCell<T, BATHY> c2(a, x0 - 2, y0 - 2, wave, lane);
             load();
             if (tid == 0) s2.dt = s3.dt = s1.dt;
             stage_compute<T, EQN, BATHY, FLUX, RECON, 64, R1, 1>(e1, RingIO<T, 1, L1, L2>{s1, s2}, w, tid, s1);

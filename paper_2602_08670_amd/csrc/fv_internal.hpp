@@ -57,12 +57,12 @@ hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *ds
                        unsigned long long *rates, int rate_in, int rate_out, int rate_clear, hipStream_t st);
 // The grids that step so.  One stage: no ring, and no copy back to the state
 // (16 steps of 500^2 cells 86 us, with a launch and a copy 151, 1400^2 324 and
-// 453): all.  FP32 Heun HLLE with MINMOD, in tiles of up to 12 rows: up to where the rings cost what
-// the launches do (800^2 272 us and 286 with a launch per stage, 1000 x 700
-// Euler 322 and 323, 1024^2 425 and 327).  The others, in 4 or 8 rows: while
-// every tile has a CU of its own (FP32 Roe Heun 320^2 108 and 143, 500^2 189
-// and 183; FP64 Heun 320^2 160 and 201; FP64 Roe in three stages, 4 rows:
-// 200^2 193 and 242, 250^2 352 and 245).
+// 453): all.  FP32 Heun HLLE with MINMOD, in tiles of up to 12 rows: up to
+// where the rings cost what the launches do (800^2 272 us and 286 with a
+// launch per stage, 1000 x 700 Euler 322 and 323, 1024^2 425 and 327).  The
+// others, in 4 or 8 rows: while every tile has a CU of its own (FP32 Roe Heun
+// 320^2 108 and 143, 500^2 189 and 183; FP64 Heun 320^2 160 and 201; FP64 Roe
+// in three stages, 4 rows: 200^2 193 and 242, 250^2 352 and 245).
 inline int step_rows(const StageDesc &d, int stages)  // most rows of a tile
 {
     if (stages == 1 || (stages == 3 && d.prec == 1)) return 4;

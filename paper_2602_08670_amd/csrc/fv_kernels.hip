@@ -18,6 +18,7 @@
 //     reduced over the wave with DPP, then one atomicMax per wave into a
 //     device sub-slot read by the next step, so Delta t never travels
 //     through the host.
+// On small grids one launch takes all stages of a step (step_kernel).
 #include "fv_device.hpp"
 #include "fv_internal.hpp"
 

@@ -697,7 +697,7 @@ fv_status fv_model_forward_tiled(const fv_model *m, const float *q, int B, int n
 
 // blend: the flux-limiter blend of the face fluxes; direct: the direct
 // face-state scheme; callers pass either only where the two-launch branch
-// below runs (HLLE, nx % 8 == ny % 8 == 0, below the split size).
+// below runs (HLLE, nx % 8 == ny % 8 == 0, up to the split size).
 static fv_status learned_step_impl(fv_solver *s, const fv_model *m, int64_t nsteps, fv_learned_stats *stats,
                                    int blend, int direct = 0)
 {
@@ -732,8 +732,12 @@ static fv_status learned_step_impl(fv_solver *s, const fv_model *m, int64_t nste
     sb.z = z;
     const int fl = c.flux == FV_FLUX_RUSANOV ? 1 : 0;  // kernel flux ids: 0 HLLE, 1 Rusanov
     hipError_t e = hipSuccess;
+    // up to three rounds of 8 x 8 tiles (11.5 us each): a fourth costs more than
+    // the wide-tile network pass and the separate stage (208^2, three rounds:
+    // 68 us a step against 75; 256 x 248, four: 85 against 66; direct and
+    // blended 84 and 87 against 63 and 66)
     if (fl == 0 && c.nx % 8 == 0 && c.ny % 8 == 0 &&
-        cnn::ltiles_cnn(c.nx, c.ny) <= (blend || direct ? 4 * cnn::fused_max_grid() - 1 : 3 * cnn::fused_max_grid())) {
+        cnn::ltiles_cnn(c.nx, c.ny) <= 3 * cnn::fused_max_grid()) {
         // two launches per step, each the network pass with the learned
         // stage (the server's per-stage arithmetic, so bit-identical to the
         // same solve in a served mix): the step's output goes to the other
@@ -914,12 +918,12 @@ static fv_status raw_head_step(fv_solver *s, const fv_model *m, int64_t nsteps, 
 
 fv_status fv_direct_step(fv_solver *s, const fv_model *m, int64_t nsteps, fv_learned_stats *stats)
 {
-    // HLLE grids of whole 8 x 8 tiles below the split size: the learned
+    // HLLE grids of whole 8 x 8 tiles up to the split size: the learned
     // step's two-launch form, the network pass (on the tile and a one-cell
     // ring) and the direct stage in one launch per stage; else the network's
     // raw output through HBM and a separate direct stage
     if (s && m && s->cfg.flux == FV_FLUX_HLLE && s->cfg.nx % 8 == 0 && s->cfg.ny % 8 == 0 &&
-        cnn::ltiles_cnn(s->cfg.nx, s->cfg.ny) < 4 * cnn::fused_max_grid())
+        cnn::ltiles_cnn(s->cfg.nx, s->cfg.ny) <= 3 * cnn::fused_max_grid())
         return learned_step_impl(s, m, nsteps, stats, 0, 1);
     return raw_head_step(s, m, nsteps, stats, 1, 0);
 }
@@ -931,11 +935,11 @@ fv_status fv_learned_step(fv_solver *s, const fv_model *m, int64_t nsteps, fv_le
 
 fv_status fv_blend_step(fv_solver *s, const fv_model *m, int64_t nsteps, fv_learned_stats *stats)
 {
-    // HLLE grids of whole 8 x 8 tiles below the split size: the network pass
+    // HLLE grids of whole 8 x 8 tiles up to the split size: the network pass
     // and the blended stage in one launch per stage (z stays in LDS); else
     // the network's raw output through HBM and a separate blended stage
     if (s && m && s->cfg.flux == FV_FLUX_HLLE && s->cfg.nx % 8 == 0 && s->cfg.ny % 8 == 0 &&
-        cnn::ltiles_cnn(s->cfg.nx, s->cfg.ny) < 4 * cnn::fused_max_grid())
+        cnn::ltiles_cnn(s->cfg.nx, s->cfg.ny) <= 3 * cnn::fused_max_grid())
         return learned_step_impl(s, m, nsteps, stats, 1);
     return raw_head_step(s, m, nsteps, stats, 0, 1);
 }

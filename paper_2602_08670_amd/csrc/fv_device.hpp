@@ -49,6 +49,14 @@ __device__ __forceinline__ double minmod(double a, double b)
     return __builtin_fmax(__builtin_fmin(a, b), __builtin_fmin(__builtin_fmax(a, b), 0.0));
 }
 
+// 1/x nearly rounded: the hardware's with one Newton step.
+__device__ __forceinline__ float rcp_near(float x)
+{
+    const float r = rcp(x);
+    return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double rcp_near(double x) { return 1.0 / x; }
+
 // 1/x for x > 0, else 0 (a dry state has zero velocity).
 template <typename T> __device__ __forceinline__ T rcp_pos(T x) { return x > T(0) ? rcp(x) : T(0); }
 
@@ -271,11 +279,20 @@ __device__ __forceinline__ void face_flux(const T (*st)[4], const Phys<T> &ph, T
 // (contraction off), so that a face has the same bits wherever it is
 // evaluated: in any tile shape, at a tile's edge or inside.
 //
-// HLLE is F_L + t (s_R dQ - (F_R - F_L)), t = s_L / (s_R - s_L).  With the mass
-// flux F_0 and b = t (s_R rho_R - m_R), every transported quantity a (a normal
-// or tangential velocity, the enthalpy) has the flux a_L F_0 + (a_R - a_L) b,
-// which is the same value rearranged.  Roe averages are a_L + k (a_R - a_L),
-// k = sqrt(rho_R) / (sqrt(rho_L) + sqrt(rho_R)).
+// Euler's HLLE weighs the two sides, a F_L + b F_R + c dQ with a = s_R w,
+// b = -s_L w, c = s_L s_R w, w = 1 / (s_R - s_L): where all waves run to one
+// side the other side's flux drops out with its rounding, however strong the
+// jump, and a face and its mirror image have the same bits (at a wall the mass
+// flux is exactly zero), so the sums of the two sides are not fused.  Anchored
+// on one side (a_L F_0 + (a_R - a_L) b per transported quantity, 16 steps of
+// 1000 x 700 cells 319 us instead of 334) an FP32 cell's energy update was off
+// from double precision by 5.3e-8 rms where it is 2.9e-8 so (contrasts of
+// e^0.1, Mach 0.5), by up to 1.1e-3 where it is 1.5e-4 (e^3, Mach 5).
+//
+// Shallow water's HLLE is F_L + t (s_R dQ - (F_R - F_L)), t = s_L / (s_R - s_L).
+// With the mass flux F_0 and b = t (s_R h_R - m_R), a velocity a is transported
+// as a_L F_0 + (a_R - a_L) b, which is the same value rearranged.  Its Roe
+// average is a_L + k (a_R - a_L), k = sqrt(h_R) / (sqrt(h_L) + sqrt(h_R)).
 //
 // Shallow water carries the normal momentum flux relative to the pressure
 // g h^2 / 2 of each side's own face state, since a cell's two face states
@@ -411,7 +428,7 @@ __device__ __forceinline__ void eul_face(T *QL, T *QR, const T *CL, const T *CR,
     }
     const T cl = fsqrt((ph.gamma * pl) * irl), cr = fsqrt((ph.gamma * pr) * irr);
     const T Hl = (QL[3] + pl) * irl, Hr = (QR[3] + pr) * irr;
-    const T dr = QR[0] - QL[0], dm = QR[NM] - QL[NM], du = ur - ul, dv = vr - vl, dH = Hr - Hl, dp = pr - pl;
+    const T dr = QR[0] - QL[0], dm = QR[NM] - QL[NM];
     const T ml = QL[NM], mr = QR[NM], dt = QR[TM] - QL[TM], dE = QR[3] - QL[3];
     // twice the mean flux of the two states
     const T s0 = ml + mr, s1 = tfma(mr, ur, ml * ul) + (pl + pr), s2 = tfma(mr, vr, ml * vl), s3 = tfma(mr, Hr, ml * Hl);
@@ -424,8 +441,8 @@ __device__ __forceinline__ void eul_face(T *QL, T *QR, const T *CL, const T *CR,
         return;
     }
     const T wl = fsqrt(QL[0]), wr = fsqrt(QR[0]);
-    const T k = wr * rcp(wl + wr);
-    const T ua = tfma(k, du, ul), va = tfma(k, dv, vl), Ha = tfma(k, dH, Hl);
+    const T iw = rcp(wl + wr), kl = wl * iw, kr = wr * iw;
+    const T ua = kl * ul + kr * ur, va = kl * vl + kr * vr, Ha = kl * Hl + kr * Hr;
     const T ca = fsqrt(tmax(gm1 * tfma(T(-0.5), tfma(va, va, ua * ua), Ha), T(0)));
     if constexpr (FLUX == ROE) {
         // acoustic u - c, entropy u, shear u, acoustic u + c
@@ -445,13 +462,13 @@ __device__ __forceinline__ void eul_face(T *QL, T *QR, const T *CL, const T *CR,
     }
     const T sL = tmin(tmin(ul - cl, ua - ca), T(0));
     const T sR = tmax(tmax(ur + cr, ua + ca), T(0));
-    const T t = sL * rcp(sR - sL);  // sR - sL >= c~ > 0 for admissible states
-    const T f0 = tfma(t, tfma(sR, dr, -dm), QL[NM]);
-    const T b = t * tfma(sR, QR[0], -QR[NM]);
-    F[0] = f0;
-    F[NM] = tfma(du, b, tfma(ul, f0, tfma(-t, dp, pl)));
-    F[TM] = tfma(dv, b, vl * f0);
-    F[3] = tfma(-(t * sR), dp, tfma(dH, b, Hl * f0));
+    const T w = rcp_near(sR - sL);  // sR - sL >= c~ > 0 for admissible states
+    const T a = sR * w, b = -sL * w, c = (sL * sR) * w;
+    const T x = a * ml, y = b * mr;
+    F[0] = tfma(c, dr, x + y);
+    F[NM] = tfma(c, dm, a * tfma(ml, ul, pl) + b * tfma(mr, ur, pr));
+    F[TM] = tfma(c, dt, x * vl + y * vr);
+    F[3] = tfma(c, dE, x * Hl + y * Hr);
 }
 
 // The face between two cells from its two face values, for either system;

@@ -189,8 +189,9 @@ fv_status enqueue_step(fv_solver *s)
     }
     switch (s->cfg.rk_stages) {
     case 1:
-        e = fvk::launch_stage(s->d, s->q, s->q, S1, s->bed, 0.0, 1.0, ctl, s->rates(), ri, ro, rc, 1, s->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(s->q, S1, s->state_bytes, hipMemcpyDeviceToDevice, s->stream);
+        // to the stage buffer and back: a frozen state is carried through both
+        e = fvk::launch_step(s->d, 1, s->q, S1, s->bed, ctl, s->rates(), ri, ro, rc, fvk::BAD_EVEN, s->stream);
+        if (e == hipSuccess) e = fvk::launch_step_copy(s->d, S1, s->q, ctl, s->stream);
         break;
     case 2:
         e = fvk::launch_stage(s->d, s->q, s->q, S1, s->bed, 0.0, 1.0, ctl, s->rates(), ri, -1, -1, 0, s->stream);
@@ -223,7 +224,8 @@ fv_status enqueue_run(fv_solver *s, int64_t nsteps)
             for (int h = 0; h < 2; h++, s->enq++) {
                 const int n = (int)(s->enq % 3);
                 hipError_t e = fvk::launch_step(s->d, s->cfg.rk_stages, h ? S1 : s->q, h ? s->q : S1, s->bed, s->ctl(),
-                                                s->rates(), n, cfl ? (n + 1) % 3 : -1, cfl ? (n + 2) % 3 : -1, s->stream);
+                                                s->rates(), n, cfl ? (n + 1) % 3 : -1, cfl ? (n + 2) % 3 : -1,
+                                                h ? fvk::BAD_ODD : fvk::BAD_EVEN, s->stream);
                 if (e != hipSuccess) return hip_fail(e, "step launch");
             }
     }

@@ -11,11 +11,19 @@ namespace fvk {
 struct Ctl {
     double t;             // simulated time
     long long step;       // completed steps
-    int bad;              // a step produced an inadmissible cell
+    int bad;              // a step produced an inadmissible cell: Bad bits, 0 = none
     int pad0;
     unsigned long long pad1[5];
 };
 static_assert(sizeof(Ctl) == 64, "control block layout");
+// A launch that ends a step raises a bit of its kind and goes on as if it were
+// not set, so that the whole step is stored, whichever workgroup fails first,
+// and counted; every later launch finds a bit that is not its own, skips, and
+// sets BAD_SKIP for those of the same kind behind it.  The kinds alternate: the
+// first launch of a step in several (no bit of its own) or the step's copy
+// stands between two BAD_STEP or BAD_EVEN launches, and steps in pairs take
+// BAD_EVEN and BAD_ODD in turn.
+enum Bad { BAD_SKIP = 1, BAD_STEP = 2, BAD_EVEN = 4, BAD_ODD = 8 };
 
 // CFL rate slots.  Slot k holds RATE_SUB sub-slots, each the bits of a
 // non-negative double reduced with atomicMax on the bit pattern (monotone for
@@ -52,9 +60,12 @@ hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void
                         int rate_clear, int last, hipStream_t st);
 
 // A whole step of 1, 2 or 3 stages from src to dst (not the same buffer) in
-// one launch, with the last stage's bookkeeping.
+// one launch, with the last stage's bookkeeping; own is BAD_EVEN or BAD_ODD.
 hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
-                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, hipStream_t st);
+                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, int own, hipStream_t st);
+// The end of a step whose launch went to another buffer than the state's: the
+// state copied back.
+hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl *ctl, hipStream_t st);
 // The grids that step so.  One stage: no ring, and no copy back to the state
 // (16 steps of 500^2 cells 86 us, with a launch and a copy 151, 1400^2 324 and
 // 453): all.  FP32 Heun HLLE with MINMOD, in tiles of up to 12 rows: up to

@@ -48,6 +48,7 @@ template <typename T> struct StageArgs {
     Ctl *ctl;
     unsigned long long *rates;
     int rate_in, rate_out, rate_clear, last;
+    int own;  // the Bad bit that this launch raises (0: it does not end a step)
 };
 
 // Global-memory view of a pointer.  The batched kernels read their array
@@ -352,7 +353,9 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const IO &i
 
     // An earlier step failed: the state is frozen.  The flag is checked only
     // where something would be written, so its load is off the critical path.
-    const bool frozen = gload(a.ctl)->bad != 0;
+    // Its bits but the launch's own do not change from none to some while the
+    // launch runs: every workgroup and every stage of a step sees the same.
+    const bool frozen = (gload(a.ctl)->bad & ~a.own) != 0;
     const int lane = tid & 63, wave = tid >> 6;
     const int r0 = wave * RPW;
     const T dt = (T)sh.dt;
@@ -484,8 +487,9 @@ __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const IO &i
             }
         }
     }
+    if (frozen && tile_linear == 0 && tid == 0) atomicOr(&a.ctl->bad, BAD_SKIP);
     if (!a.last || frozen) return;
-    if (bad) atomicExch(&a.ctl->bad, 1);
+    if (bad) atomicOr(&a.ctl->bad, a.own);
     if (a.rate_out >= 0) {
         // one atomic per wave: no block-wide reduction, no further barrier
         const T m = wave_max_nonneg(lmax);
@@ -600,6 +604,7 @@ __device__ __forceinline__ TileRef batch_fill(const BatchSolve &d, const WorkIte
     a.rate_out = STAGE == 1 ? -1 : it.ro;
     a.rate_clear = STAGE == 1 ? -1 : it.rc;
     a.last = STAGE == 2;
+    a.own = STAGE == 2 ? BAD_STEP : 0;
     const int ty = tile / it.tiles_x, tx = tile - ty * it.tiles_x;
     return TileRef{tx * TX, ty * TY, tile};
 }
@@ -903,7 +908,7 @@ __global__ void report_kernel(const Ctl *ctl, RunInfo *info)
     if (threadIdx.x == 0) {
         info->t = ctl->t;
         info->steps = ctl->step;
-        info->bad = ctl->bad;
+        info->bad = ctl->bad != 0;
         info->pad = 0;
     }
 }
@@ -1000,6 +1005,7 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
     a.a0 = (T)a0;
     a.a1 = (T)a1;
     a.last = last;
+    a.own = last ? BAD_STEP : 0;
     // the shapes with one and with two rows per wave serve every scheme, the
     // other two FP32 HLLE with MINMOD (the scheme of long runs)
     constexpr bool ALL = sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD;
@@ -1113,12 +1119,35 @@ static hipError_t step_p(const StageDesc &d, int stages, const StageArgs<T> &a, 
 }
 
 hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
-                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, hipStream_t st)
+                       unsigned long long *rates, int rate_in, int rate_out, int rate_clear, int own, hipStream_t st)
 {
     if (stages < 1 || stages > 3 || d.nx < 2 * stages || d.ny < 2 * stages || src == dst) return hipErrorInvalidValue;
-    return d.prec == 1
-               ? step_p<double>(d, stages, stage_args<double>(d, src, src, dst, bed, ctl, rates, rate_in, rate_out, rate_clear), st)
-               : step_p<float>(d, stages, stage_args<float>(d, src, src, dst, bed, ctl, rates, rate_in, rate_out, rate_clear), st);
+    auto go = [&](auto zero) {
+        using T = decltype(zero);
+        StageArgs<T> a = stage_args<T>(d, src, src, dst, bed, ctl, rates, rate_in, rate_out, rate_clear);
+        a.own = own;
+        return step_p<T>(d, stages, a, st);
+    };
+    return d.prec == 1 ? go(0.0) : go(0.0f);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void step_copy_kernel(const T *__restrict__ src, T *__restrict__ dst, size_t n,
+                                                        Ctl *ctl)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0 && ctl->bad) atomicOr(&ctl->bad, BAD_SKIP);
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
+}
+
+hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl *ctl, hipStream_t st)
+{
+    const size_t n = (size_t)(d.eqn == EULER ? 4 : 3) * d.nx * d.ny, blocks = (n + 255) / 256;
+    const dim3 grid((unsigned)(blocks < 8192 ? blocks : 8192));
+    if (d.prec == 1)
+        hipLaunchKernelGGL(step_copy_kernel<double>, grid, dim3(256), 0, st, (const double *)src, (double *)dst, n, ctl);
+    else
+        hipLaunchKernelGGL(step_copy_kernel<float>, grid, dim3(256), 0, st, (const float *)src, (float *)dst, n, ctl);
+    return hipGetLastError();
 }
 
 template <typename T>

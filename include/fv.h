@@ -407,12 +407,14 @@ typedef struct {
 
 typedef struct fv_euler_trainer fv_euler_trainer;
 
+/* As fv_train_workspace_bytes. */
 size_t fv_euler_train_workspace_bytes(const fv_euler_train_config *cfg);
 
 /* net: its master parameters are trained in place (Adam re-packs its
  * weights) and its stream is used; grads, adam_m, adam_v: device FP32
  * vectors of fv_euler_net_param_count() entries (caller-owned, Adam moments
- * zeroed by the caller); workspace 256-byte aligned. */
+ * zeroed by the caller); workspace 256-byte aligned, taken as
+ * fv_train_create's. */
 fv_status fv_euler_train_create(const fv_euler_train_config *cfg, fv_euler_learned *net, float *grads,
                                 float *adam_m, float *adam_v, void *workspace, size_t workspace_bytes,
                                 fv_euler_trainer **out);
@@ -471,13 +473,18 @@ typedef struct {
 typedef struct fv_trainer fv_trainer;
 
 /* Device workspace of a trainer (saved states, activations, coefficients,
- * adjoints); 0 if the configuration is invalid. */
+ * adjoints, and the layer gradients of up to 2 T backward passes of about a
+ * million cells together, 480 bytes per cell, whose weight gradients are then
+ * one launch per layer); 0 if the configuration is invalid. */
 size_t fv_train_workspace_bytes(const fv_train_config *cfg);
 
 /* Create a trainer for model m (its stream is used).  grads, adam_m, adam_v:
  * caller-owned device FP32 vectors of fv_model_param_count() elements
  * (grads is overwritten by each fv_train_step; the Adam moments must start
- * at zero).  workspace: >= fv_train_workspace_bytes, 256-byte aligned. */
+ * at zero).  workspace: fv_train_workspace_bytes, 256-byte aligned; with less
+ * the weight gradients are taken over fewer passes at a time, with none of
+ * them kept layer by layer (the same sums in another order, more launches),
+ * and FV_E_NOMEM is returned where that does not fit either. */
 fv_status fv_train_create(const fv_train_config *cfg, fv_model *m, float *grads, float *adam_m, float *adam_v,
                           void *workspace, size_t workspace_bytes, fv_trainer **out);
 

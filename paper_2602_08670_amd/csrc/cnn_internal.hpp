@@ -249,8 +249,11 @@ constexpr int DZ_CH = 96;
 // pixels: at 16 solves of 64^2 a pass is 256 tiles, too few to fill the chip
 // or to pay for 37 to 92 KB of partial sums per tile (68 us of launches per
 // pass); sixteen passes together take 365 us, 23 each.  bwd_slots passes are
-// kept at a time, about a million pixels (448 bytes each), beyond which a
-// launch gains nothing more.
+// kept at a time, about a million pixels (480 bytes each), beyond which a
+// launch gains nothing more, or as many as the caller's workspace holds.  With
+// none (BwdMem of 0 slots) launch_backward is given the arguments and takes
+// each layer's weight gradient before its G is overwritten: G alternates
+// between two buffers.
 struct BwdSlot {
     void *G[4], *x0;
 };
@@ -260,13 +263,30 @@ struct WgradArgs {
     const void *dz;       // likewise, dz_slot bytes apart
     BwdSlot first;        // likewise, g_slot bytes apart
     size_t act_slot, dz_slot, g_slot;
-    void *partial;        // scratch of wgrad_partial_bytes()
+    void *partial;        // scratch of BwdMem::part bytes
     float *grads;
 };
 int bwd_slots(int B, int nx, int ny, int passes);  // 1 .. passes
-size_t wgrad_partial_bytes();
+// Workspace of a backward that keeps `slots` passes (0: see above).
+struct BwdMem {
+    int slots;
+    size_t act, dz, g, part;  // bytes of an activation, of a slot's dz and G, and of the partial sums
+    BwdMem() = default;
+    BwdMem(int slots, int B, int nx, int ny, int cout);  // cout: COUT or E_COUT
+    size_t dz_bytes() const { return (slots ? slots : 1) * dz; }
+    size_t g_bytes() const { return (slots ? slots : 1) * g; }
+    // a pass's dz and slot in regions of dz_bytes() and g_bytes()
+    char *dz_of(char *base, int pass) const { return base + (slots ? pass % slots : 0) * dz; }
+    BwdSlot slot_of(char *base, int pass) const
+    {
+        if (!slots) return BwdSlot{{base + act, base, base + act, base}, base + 2 * act};
+        char *p = base + (pass % slots) * g;
+        return BwdSlot{{p, p + act, p + 2 * act, p + 3 * act}, p + 4 * act};
+    }
+};
 hipError_t launch_backward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st);
+                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, const WgradArgs *each,
+                           hipStream_t st);
 hipError_t launch_wgrads(const WgradArgs &a, hipStream_t st);
 
 // ------------------------------------------------------------------------
@@ -306,7 +326,8 @@ hipError_t launch_net_euler(const void *packed, const ENorm &nrm, const float *q
 // Backward of the Euler network, as the planar one's (dz BF16 [p][96], dq
 // [B][4][ny][nx], the activations of launch_forward_euler).
 hipError_t launch_backward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st);
+                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s,
+                                 const WgradArgs *each, hipStream_t st);
 hipError_t launch_wgrads_euler(const WgradArgs &a, hipStream_t st);
 
 // Projector onto the null space of the moment conditions of the given order

@@ -2537,11 +2537,25 @@ static void wgrad(const void *G, size_t gslot, const void *In, size_t islot, int
                        (const float *)partial, nblocks, CO_T * 16, CI, co_real, ci_real, woff, boff, grads);
 }
 
-size_t wgrad_partial_bytes()
+BwdMem::BwdMem(int slots, int B, int nx, int ny, int cout) : slots(slots)
 {
-    const size_t a = (size_t)WgradShape<6, 32>::PER * WgradShape<6, 32>::WGS;
-    const size_t b = (size_t)WgradShape<2, 32>::PER * WgradShape<2, 32>::WGS;
-    return al256((a > b ? a : b) * sizeof(float));
+    const int passes = slots ? slots : 1;
+    const size_t npix = (size_t)B * nx * ny;
+    act = al256(npix * CH * 2);
+    dz = al256(npix * DZ_CH * 2);
+    g = (slots ? 4 : 2) * act + al256(npix * 16 * 2);
+    // the partial sums of the layer with most
+    const int64_t tiles = (int64_t)passes * B * (nx / HT) * ((ny + HT - 1) / HT);
+    part = 0;
+    auto layer = [&](auto shape) {
+        using S = decltype(shape);
+        const size_t n = al256((size_t)(tiles < S::WGS ? tiles : S::WGS) * S::PER * sizeof(float));
+        part = part > n ? part : n;
+    };
+    if (cout == E_COUT) layer(WgradShape<6, 32>{});
+    else layer(WgradShape<5, 32>{});
+    layer(WgradShape<2, 32>{});
+    layer(WgradShape<2, 16>{});
 }
 
 int bwd_slots(int B, int nx, int ny, int passes)
@@ -2550,11 +2564,29 @@ int bwd_slots(int B, int nx, int ny, int passes)
     return k < 1 ? 1 : (k < passes ? (int)k : passes);
 }
 
-// The input-gradient chain of the network, layer 4 down to the states;
-// CZ channels of dz in KZ 32-channel K blocks.
-template <int C, typename NormT, typename PK>
-static hipError_t backward_chain(const char *P, const PK &pk, const NormT &nrm, const float *q, int B, int nx, int ny,
-                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
+// The weight gradients of layer l.
+template <int CIN_, int COUT_, int CO_T, typename ML>
+static void layer_wgrad(int l, const ML &ml, const WgradArgs &a, hipStream_t st)
+{
+    const size_t is = a.act_slot / 2, gs = a.g_slot / 2;
+    float *pt = (float *)a.partial;
+    if (l == 4)
+        wgrad<96, CO_T, 32>(a.dz, a.dz_slot / 2, a.acts[3], is, a.slots, a.B, a.ny, a.nx, pt, COUT_, 32, ml.w[4],
+                            ml.b[4], a.grads, st);
+    else if (l > 0)
+        wgrad<32, 2, 32>(a.first.G[l], gs, a.acts[l - 1], is, a.slots, a.B, a.ny, a.nx, pt, 32, 32, ml.w[l], ml.b[l],
+                         a.grads, st);
+    else
+        wgrad<32, 2, 16>(a.first.G[0], gs, a.first.x0, gs, a.slots, a.B, a.ny, a.nx, pt, 32, CIN_, ml.w[0], ml.b[0],
+                         a.grads, st);
+}
+
+// The input-gradient chain of the network, layer 4 down to the states; with
+// `each`, every layer's weight gradient as soon as its G is there.
+template <int C, int COUT_, int CO_T, typename NormT, typename PK, typename ML>
+static hipError_t backward_chain(const char *P, const PK &pk, const ML &ml, const NormT &nrm, const float *q, int B,
+                                 int nx, int ny, void *const acts[4], const void *dz, float *dq, const BwdSlot &s,
+                                 const WgradArgs *each, hipStream_t st)
 {
     // the halo-tile kernels take 16-pixel-wide tiles
     if (nx % HT) return hipErrorInvalidValue;
@@ -2562,43 +2594,46 @@ static hipError_t backward_chain(const char *P, const PK &pk, const NormT &nrm, 
     unsigned eg = (unsigned)((npix * 16 + 255) / 256);
     if (eg > 8192) eg = 8192;
     dim3 cg((unsigned)((npix + 63) / 64)), blk(256);
+    auto take = [&](int l) {
+        if (each) layer_wgrad<C, COUT_, CO_T>(l, ml, *each, st);
+    };
+    take(4);
     launch_halo<3, 2, 2>((const bf16 *)dz, (const bf16 *)(P + pk.wt[4]), nullptr, (const bf16 *)acts[3], s.G[3], B, nx,
                          ny, st);
-    for (int l = 3; l >= 1; l--)
+    for (int l = 3; l >= 1; l--) {
+        take(l);
         launch_halo<1, 2, 2>((const bf16 *)s.G[l], (const bf16 *)(P + pk.wt[l]), nullptr, (const bf16 *)acts[l - 1],
                              s.G[l - 1], B, nx, ny, st);
+    }
     // layer 0: the input rebuilt as the forward rounds it, for its weight gradient
     hipLaunchKernelGGL((x0_kernel<C, NormT>), dim3(eg), blk, 0, st, q, (bf16 *)s.x0, B, ny, nx, nrm);
+    take(0);
     hipLaunchKernelGGL((conv_dgrad_input_kernel<C, NormT>), cg, blk, 0, st, (const bf16 *)s.G[0],
                        (const bf16 *)(P + pk.wt[0]), dq, B, ny, nx, nrm);
     return hipGetLastError();
 }
 
 hipError_t launch_backward(const void *packed, const Norm &nrm, const float *q, int B, int nx, int ny,
-                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
+                           void *const acts[4], const void *dz, float *dq, const BwdSlot &s, const WgradArgs *each,
+                           hipStream_t st)
 {
-    return backward_chain<CIN>((const char *)packed, packed_layout(), nrm, q, B, nx, ny, acts, dz, dq, s, st);
+    return backward_chain<CIN, COUT, 5>((const char *)packed, packed_layout(), master_layout(), nrm, q, B, nx, ny, acts,
+                                        dz, dq, s, each, st);
 }
 
 hipError_t launch_backward_euler(const void *packed, const ENorm &nrm, const float *q, int B, int nx, int ny,
-                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s, hipStream_t st)
+                                 void *const acts[4], const void *dz, float *dq, const BwdSlot &s,
+                                 const WgradArgs *each, hipStream_t st)
 {
-    return backward_chain<E_CIN>((const char *)packed, euler_packed_layout(), nrm, q, B, nx, ny, acts, dz, dq, s, st);
+    return backward_chain<E_CIN, E_COUT, 6>((const char *)packed, euler_packed_layout(), euler_master(), nrm, q, B, nx,
+                                            ny, acts, dz, dq, s, each, st);
 }
 
 template <int CIN_, int COUT_, int CO_T, typename ML>
 static hipError_t wgrads(const ML &ml, const WgradArgs &a, hipStream_t st)
 {
     if (a.nx % HT) return hipErrorInvalidValue;
-    const size_t is = a.act_slot / 2, gs = a.g_slot / 2;
-    float *pt = (float *)a.partial;
-    wgrad<96, CO_T, 32>(a.dz, a.dz_slot / 2, a.acts[3], is, a.slots, a.B, a.ny, a.nx, pt, COUT_, 32, ml.w[4], ml.b[4],
-                        a.grads, st);
-    for (int l = 3; l >= 1; l--)
-        wgrad<32, 2, 32>(a.first.G[l], gs, a.acts[l - 1], is, a.slots, a.B, a.ny, a.nx, pt, 32, 32, ml.w[l], ml.b[l],
-                         a.grads, st);
-    wgrad<32, 2, 16>(a.first.G[0], gs, a.first.x0, gs, a.slots, a.B, a.ny, a.nx, pt, 32, CIN_, ml.w[0], ml.b[0],
-                     a.grads, st);
+    for (int l = 4; l >= 0; l--) layer_wgrad<CIN_, COUT_, CO_T>(l, ml, a, st);
     return hipGetLastError();
 }
 

@@ -266,8 +266,8 @@ namespace {
 struct TLayout {
     size_t states, s1, acts, z, plain, s2, flags, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, part, lossp,
         loss, scale, total;
-    size_t st, act, zb, dzb, gb;
-    int slots;  // backward passes whose weight gradients are taken together
+    size_t st, act, zb;
+    cnn::BwdMem bwm;  // of the backward passes whose weight gradients are taken together
 };
 
 fv_status validate_train(const fv_euler_train_config *c)
@@ -285,7 +285,8 @@ fv_status validate_train(const fv_euler_train_config *c)
     return FV_OK;
 }
 
-TLayout tlayout(const fv_euler_train_config *c)
+// slots: as for cnn::BwdMem.
+TLayout tlayout(const fv_euler_train_config *c, int slots)
 {
     TLayout L;
     const size_t npix = (size_t)c->B * c->nx * c->ny;
@@ -309,22 +310,23 @@ TLayout tlayout(const fv_euler_train_config *c)
     L.nfb = take((size_t)c->B * 8);
     L.redone = take((size_t)c->B * 8);
     L.fatal = take((size_t)c->B * 4);
-    L.slots = cnn::bwd_slots(c->B, c->nx, c->ny, 2 * T);
-    L.dzb = align256(npix * cnn::E_COUT * 2);
-    L.gb = 4 * L.act + align256(npix * 16 * 2);
-    L.dz = take(L.slots * L.dzb);
+    L.bwm = cnn::BwdMem(slots, c->B, c->nx, c->ny, cnn::E_COUT);
+    static_assert(cnn::E_COUT == cnn::DZ_CH, "channels of dz");
+    L.dz = take(L.bwm.dz_bytes());
     L.contrib = take(npix * 2 * eln::ADJ_REC * 4);
     L.G = take(L.st);
     L.Gn = take(L.st);
     L.gS1 = take(L.st);
-    L.bwd = take(L.slots * L.gb);
-    L.part = take(cnn::wgrad_partial_bytes());
+    L.bwd = take(L.bwm.g_bytes());
+    L.part = take(L.bwm.part);
     L.lossp = take(1024 * 8);
     L.loss = take(8);
     L.scale = take(16);
     L.total = o;
     return L;
 }
+
+int most_slots(const fv_euler_train_config *c) { return cnn::bwd_slots(c->B, c->nx, c->ny, 2 * c->T); }
 
 }  // namespace
 
@@ -341,15 +343,11 @@ struct fv_euler_trainer {
     void *act(int t, int stage, int l) { return ws + L.acts + (((size_t)t * 2 + stage) * 4 + l) * L.act; }
     float *zb(int t, int stage) { return (float *)(ws + L.z + ((size_t)t * 2 + stage) * L.zb); }
     int *plain(int t) { return (int *)(ws + L.plain) + (size_t)t * cfg.B; }
-    // pass 2 t + stage keeps its dz and layer gradients in slot pass % slots
-    __bf16 *dz(int pass) { return (__bf16 *)(ws + L.dz + (size_t)(pass % L.slots) * L.dzb); }
-    cnn::BwdSlot slot(int pass)
-    {
-        char *p = ws + L.bwd + (size_t)(pass % L.slots) * L.gb;
-        return cnn::BwdSlot{{p, p + L.act, p + 2 * L.act, p + 3 * L.act}, p + 4 * L.act};
-    }
-    // the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
-    hipError_t wgrads(int pass, int n)
+    // pass 2 t + stage's dz and layer gradients
+    __bf16 *dz(int pass) { return (__bf16 *)L.bwm.dz_of(ws + L.dz, pass); }
+    cnn::BwdSlot slot(int pass) { return L.bwm.slot_of(ws + L.bwd, pass); }
+    // for the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
+    cnn::WgradArgs wgrads(int pass, int n)
     {
         cnn::WgradArgs a;
         a.slots = n;
@@ -360,11 +358,11 @@ struct fv_euler_trainer {
         a.dz = dz(pass);
         a.first = slot(pass);
         a.act_slot = 4 * L.act;
-        a.dz_slot = L.dzb;
-        a.g_slot = L.gb;
+        a.dz_slot = L.bwm.dz;
+        a.g_slot = L.bwm.g;
         a.partial = ws + L.part;
         a.grads = grads;
-        return cnn::launch_wgrads_euler(a, net->stream);
+        return a;
     }
 };
 
@@ -373,7 +371,7 @@ extern "C" {
 size_t fv_euler_train_workspace_bytes(const fv_euler_train_config *cfg)
 {
     if (validate_train(cfg) != FV_OK) return 0;
-    return tlayout(cfg).total;
+    return tlayout(cfg, most_slots(cfg)).total;
 }
 
 fv_status fv_euler_train_create(const fv_euler_train_config *cfg, fv_euler_learned *net, float *grads,
@@ -386,7 +384,9 @@ fv_status fv_euler_train_create(const fv_euler_train_config *cfg, fv_euler_learn
     if (rc != FV_OK) return rc;
     if (!net || !grads || !adam_m || !adam_v || !workspace) return fail(FV_E_INVALID, "NULL argument");
     if (((uintptr_t)workspace & 255) != 0) return fail(FV_E_INVALID, "workspace must be 256-byte aligned");
-    const TLayout L = tlayout(cfg);
+    // as many passes as the workspace holds
+    TLayout L = tlayout(cfg, most_slots(cfg));
+    for (int k = L.bwm.slots; workspace_bytes < L.total && k > 0;) L = tlayout(cfg, --k);
     if (workspace_bytes < L.total) return fail(FV_E_NOMEM, "workspace %zu < %zu", workspace_bytes, L.total);
     fv_euler_trainer *tr = new fv_euler_trainer();
     tr->cfg = *cfg;
@@ -478,11 +478,15 @@ fv_status fv_euler_train_step(fv_euler_trainer *tr, const float *q0, const float
     ad.gamma = a.gamma;
     ad.pr = net->pr;
     ad.contrib = (float *)(ws + L.contrib);
-    // after a pass: the weight gradients of its group of passes, once all of
-    // them (the later ones) are done
-    auto wgrads = [&](int pass) {
-        if (pass % L.slots) return hipSuccess;
-        return tr->wgrads(pass, std::min(L.slots, 2 * T - pass));
+    // the network's backward of a pass, and the weight gradients of its group of
+    // passes once all of them (the later ones) are done
+    auto backward = [&](int pass, const float *q, void *const acts[4], float *dq) {
+        const int slots = L.bwm.slots;
+        const cnn::WgradArgs wa = tr->wgrads(pass, slots ? std::min(slots, 2 * T - pass) : 1);
+        hipError_t r = cnn::launch_backward_euler(packed, net->nrm, q, B, nx, ny, acts, tr->dz(pass), dq,
+                                                  tr->slot(pass), slots ? nullptr : &wa, st);
+        if (r == hipSuccess && slots && pass % slots == 0) r = cnn::launch_wgrads_euler(wa, st);
+        return r;
     };
     for (int t = T; t >= 1 && e == hipSuccess; t--) {
         e = cnn::launch_loss(tr->st(t), targets + (size_t)(t - 1) * nst, (const float *)(ws + L.scale), B, nx, ny, G,
@@ -495,19 +499,13 @@ fv_status fv_euler_train_step(fv_euler_trainer *tr, const float *q0, const float
         ad.qs = tr->s1(k); ad.z = tr->zb(k, 1); ad.gout = G; ad.wscale = 0.5f * (float)c.dt;
         ad.dz = tr->dz(2 * k + 1);
         if (e == hipSuccess) e = eln::adjoint(fl, ad, gS1, 0.5f, 0, st);
-        if (e == hipSuccess)
-            e = cnn::launch_backward_euler(packed, net->nrm, tr->s1(k), B, nx, ny, a1, ad.dz, gS1,
-                                           tr->slot(2 * k + 1), st);
-        if (e == hipSuccess) e = wgrads(2 * k + 1);
+        if (e == hipSuccess) e = backward(2 * k + 1, tr->s1(k), a1, gS1);
         // stage 1: S1 = q + dt L(q), after the q/2 term of stage 2
         if (e == hipSuccess) e = cnn::launch_scale(Gn, G, 0.5f, nst, st);
         ad.qs = tr->st(k); ad.z = tr->zb(k, 0); ad.gout = gS1; ad.wscale = (float)c.dt;
         ad.dz = tr->dz(2 * k);
         if (e == hipSuccess) e = eln::adjoint(fl, ad, Gn, 1.0f, 1, st);
-        if (e == hipSuccess)
-            e = cnn::launch_backward_euler(packed, net->nrm, tr->st(k), B, nx, ny, a0, ad.dz, Gn,
-                                           tr->slot(2 * k), st);
-        if (e == hipSuccess) e = wgrads(2 * k);
+        if (e == hipSuccess) e = backward(2 * k, tr->st(k), a0, Gn);
         float *tmp = G;
         G = Gn;
         Gn = tmp;

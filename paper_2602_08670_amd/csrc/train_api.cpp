@@ -17,8 +17,8 @@ namespace {
 struct TrainLayout {
     size_t states, s1, acts, z, plain, s2, bad, dt, nfb, redone, fatal, dz, contrib, G, Gn, gS1, bwd, part, lossp,
         loss, scale, total;
-    size_t st, act, zb, dzb, gb;  // per-unit sizes
-    int slots;                    // backward passes whose weight gradients are taken together
+    size_t st, act, zb;  // per-unit sizes
+    cnn::BwdMem bwm;     // of the backward passes whose weight gradients are taken together
 };
 
 fv_status validate(const fv_train_config *c)
@@ -39,7 +39,8 @@ fv_status validate(const fv_train_config *c)
     return FV_OK;
 }
 
-TrainLayout layout_of(const fv_train_config *c)
+// slots: as for cnn::BwdMem.
+TrainLayout layout_of(const fv_train_config *c, int slots)
 {
     TrainLayout L;
     const size_t npix = (size_t)c->B * c->nx * c->ny;
@@ -70,11 +71,9 @@ TrainLayout layout_of(const fv_train_config *c)
     o += align256(c->B * 8);
     L.fatal = o;
     o += align256(c->B * 4);
-    L.slots = cnn::bwd_slots(c->B, c->nx, c->ny, 2 * T);
-    L.dzb = align256(npix * cnn::DZ_CH * 2);
-    L.gb = 4 * L.act + align256(npix * 16 * 2);
+    L.bwm = cnn::BwdMem(slots, c->B, c->nx, c->ny, cnn::COUT);
     L.dz = o;
-    o += L.slots * L.dzb;
+    o += L.bwm.dz_bytes();
     L.contrib = o;
     o += align256(npix * 2 * cnn::ADJ_REC * 4);
     L.G = o;
@@ -84,9 +83,9 @@ TrainLayout layout_of(const fv_train_config *c)
     L.gS1 = o;
     o += L.st;
     L.bwd = o;
-    o += L.slots * L.gb;
+    o += L.bwm.g_bytes();
     L.part = o;
-    o += cnn::wgrad_partial_bytes();
+    o += L.bwm.part;
     L.lossp = o;
     o += align256(1024 * 8);
     L.loss = o;
@@ -96,6 +95,8 @@ TrainLayout layout_of(const fv_train_config *c)
     L.total = o;
     return L;
 }
+
+int most_slots(const fv_train_config *c) { return cnn::bwd_slots(c->B, c->nx, c->ny, 2 * c->T); }
 
 }  // namespace
 
@@ -112,15 +113,11 @@ struct fv_trainer {
     void *act(int t, int stage, int l) { return ws + L.acts + (((size_t)t * 2 + stage) * 4 + l) * L.act; }
     float *zb(int t, int stage) { return (float *)(ws + L.z + ((size_t)t * 2 + stage) * L.zb); }
     int *plain(int t) { return (int *)(ws + L.plain) + (size_t)t * cfg.B; }
-    // pass 2 t + stage keeps its dz and layer gradients in slot pass % slots
-    void *dz(int pass) { return ws + L.dz + (size_t)(pass % L.slots) * L.dzb; }
-    cnn::BwdSlot slot(int pass)
-    {
-        char *p = ws + L.bwd + (size_t)(pass % L.slots) * L.gb;
-        return cnn::BwdSlot{{p, p + L.act, p + 2 * L.act, p + 3 * L.act}, p + 4 * L.act};
-    }
-    // the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
-    hipError_t wgrads(int pass, int n)
+    // pass 2 t + stage's dz and layer gradients
+    void *dz(int pass) { return L.bwm.dz_of(ws + L.dz, pass); }
+    cnn::BwdSlot slot(int pass) { return L.bwm.slot_of(ws + L.bwd, pass); }
+    // for the weight gradients of passes pass .. pass + n - 1 (pass a multiple of the slots)
+    cnn::WgradArgs wgrads(int pass, int n)
     {
         cnn::WgradArgs a;
         a.slots = n;
@@ -131,11 +128,11 @@ struct fv_trainer {
         a.dz = dz(pass);
         a.first = slot(pass);
         a.act_slot = 4 * L.act;
-        a.dz_slot = L.dzb;
-        a.g_slot = L.gb;
+        a.dz_slot = L.bwm.dz;
+        a.g_slot = L.bwm.g;
         a.partial = ws + L.part;
         a.grads = grads;
-        return cnn::launch_wgrads(a, m->stream);
+        return a;
     }
 };
 
@@ -144,7 +141,7 @@ extern "C" {
 size_t fv_train_workspace_bytes(const fv_train_config *cfg)
 {
     if (validate(cfg) != FV_OK) return 0;
-    return layout_of(cfg).total;
+    return layout_of(cfg, most_slots(cfg)).total;
 }
 
 fv_status fv_train_create(const fv_train_config *cfg, fv_model *m, float *grads, float *adam_m, float *adam_v,
@@ -156,7 +153,9 @@ fv_status fv_train_create(const fv_train_config *cfg, fv_model *m, float *grads,
     if (rc != FV_OK) return rc;
     if (!m || !grads || !adam_m || !adam_v || !workspace) return fail(FV_E_INVALID, "NULL argument");
     if (((uintptr_t)workspace & 255) != 0) return fail(FV_E_INVALID, "workspace must be 256-byte aligned");
-    TrainLayout L = layout_of(cfg);
+    // as many passes as the workspace holds
+    TrainLayout L = layout_of(cfg, most_slots(cfg));
+    for (int k = L.bwm.slots; workspace_bytes < L.total && k > 0;) L = layout_of(cfg, --k);
     if (workspace_bytes < L.total) return fail(FV_E_NOMEM, "workspace %zu < %zu", workspace_bytes, L.total);
     fv_trainer *tr = new fv_trainer();
     tr->cfg = *cfg;
@@ -261,11 +260,15 @@ fv_status fv_train_step(fv_trainer *tr, const float *q0, const float *targets, i
     as.h0 = sb.h0;
     as.pr = tr->m->pr;
     as.contrib = (float *)(ws + L.contrib);
-    // after a pass: the weight gradients of its group of passes, once all of
-    // them (the later ones) are done
-    auto wgrads = [&](int pass) {
-        if (pass % L.slots) return hipSuccess;
-        return tr->wgrads(pass, std::min(L.slots, 2 * T - pass));
+    // the network's backward of a pass, and the weight gradients of its group of
+    // passes once all of them (the later ones) are done
+    auto backward = [&](int pass, const float *q, void *const acts[4], float *dq) {
+        const int slots = L.bwm.slots;
+        const cnn::WgradArgs wa = tr->wgrads(pass, slots ? std::min(slots, 2 * T - pass) : 1);
+        hipError_t r = cnn::launch_backward(tr->m->packed, tr->m->nrm, q, B, nx, ny, acts, tr->dz(pass), dq,
+                                            tr->slot(pass), slots ? nullptr : &wa, st);
+        if (r == hipSuccess && slots && pass % slots == 0) r = cnn::launch_wgrads(wa, st);
+        return r;
     };
     for (int t = T; t >= 1 && e == hipSuccess; t--) {
         e = cnn::launch_loss(tr->st(t), targets + (size_t)(t - 1) * nst, (const float *)(ws + L.scale), B, nx, ny, G,
@@ -277,19 +280,13 @@ fv_status fv_train_step(fv_trainer *tr, const float *q0, const float *targets, i
         as.qs = tr->s1(k); as.z = tr->zb(k, 1); as.gout = G; as.a1 = 0.5f; as.plain = tr->plain(k);
         as.gqs = gS1; as.accumulate = 0; as.dz = tr->dz(2 * k + 1);
         if (e == hipSuccess) e = cnn::launch_adjoint(fl, as, st);
-        if (e == hipSuccess)
-            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->s1(k), B, nx, ny, a1, as.dz, gS1,
-                                     tr->slot(2 * k + 1), st);
-        if (e == hipSuccess) e = wgrads(2 * k + 1);
+        if (e == hipSuccess) e = backward(2 * k + 1, tr->s1(k), a1, gS1);
         // stage 1: S1 = q + dt L(q); the q/2 term of stage 2 first
         if (e == hipSuccess) e = cnn::launch_scale(Gn, G, 0.5f, nst, st);
         as.qs = tr->st(k); as.z = tr->zb(k, 0); as.gout = gS1; as.a1 = 1.0f; as.gqs = Gn; as.accumulate = 1;
         as.dz = tr->dz(2 * k);
         if (e == hipSuccess) e = cnn::launch_adjoint(fl, as, st);
-        if (e == hipSuccess)
-            e = cnn::launch_backward(tr->m->packed, tr->m->nrm, tr->st(k), B, nx, ny, a0, as.dz, Gn, tr->slot(2 * k),
-                                     st);
-        if (e == hipSuccess) e = wgrads(2 * k);
+        if (e == hipSuccess) e = backward(2 * k, tr->st(k), a0, Gn);
         float *tmp = G;
         G = Gn;
         Gn = tmp;

@@ -586,9 +586,8 @@ class Server:
         default).  learned_layered: 16 x 16 tiles from which such a round's
         network pass runs on wide tiles (0: any number, -1: never);
         act_pixels: cells of activation scratch set aside in the pool, 128
-        bytes each (None: with a model, an eighth of the pool up to 64 Mi
-        cells; without, none; the network pass keeps its activations on chip,
-        so 0 serves as well).  max_bypass: rounds a queued request may go
+        bytes each (None: none, since the network pass keeps its activations on
+        chip).  max_bypass: rounds a queued request may go
         without fitting before nothing behind it is admitted (0: the
         library's default, -1: never)."""
         import torch
@@ -596,11 +595,9 @@ class Server:
         self.model = model  # kept alive while the server runs
         if model is not None:
             torch.cuda.synchronize()  # the model's packed weights are ready
-        if act_pixels is None:
-            act_pixels = min(pool_bytes // 8 // 128, 1 << 26) if model is not None else 0
         self.cfg = fv_server_config(ctypes.sizeof(fv_server_config), max_solves, steps_per_round,
                                     1 if direct else 0, max_items, None if model is None else model.h,
-                                    int(learned_split), int(learned_layered), int(act_pixels), int(max_bypass), 0)
+                                    int(learned_split), int(learned_layered), int(act_pixels or 0), int(max_bypass), 0)
         # zero-filled: the pool's pages are mapped here rather than by the
         # first rounds that reach them
         self.pool = torch.zeros(pool_bytes, dtype=torch.uint8, device=device)

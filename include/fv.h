@@ -245,7 +245,8 @@ fv_status fv_model_update(fv_model *m);
 
 void fv_model_destroy(fv_model *m);
 
-/* Scratch bytes fv_model_forward needs for B solves of ny x nx cells. */
+/* Scratch bytes fv_model_forward needs for B solves of ny x nx cells (256 for
+ * ny >= 8, where the pass keeps its activations on chip). */
 size_t fv_model_forward_scratch_bytes(int B, int nx, int ny);
 
 /* Batched network inference on the model's stream (async):
@@ -253,7 +254,7 @@ size_t fv_model_forward_scratch_bytes(int B, int nx, int ny);
  *           nx*ny % 64 == 0);
  *   z       device [B][ny][nx][72] FP32 raw coefficients (output);
  *   scratch device, >= fv_model_forward_scratch_bytes(B, nx, ny), 256-byte
- *           aligned (BF16 activations). */
+ *           aligned (BF16 activations of grids with ny < 8). */
 fv_status fv_model_forward(const fv_model *m, const float *q, int B, int nx, int ny, float *z, void *scratch,
                            size_t scratch_bytes);
 

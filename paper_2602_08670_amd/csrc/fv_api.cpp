@@ -669,6 +669,7 @@ void fv_model_destroy(fv_model *m) { delete m; }
 size_t fv_model_forward_scratch_bytes(int B, int nx, int ny)
 {
     if (B <= 0 || nx <= 0 || ny <= 0) return 0;
+    if (cnn::net_takes(nx, ny)) return 256;  // activations stay on chip
     return 2 * align256((size_t)B * nx * ny * cnn::CH * 2);
 }
 

@@ -43,3 +43,26 @@ def test_pool_of_one_learned_solve(fv):
     s = fv.Solver(q, prec=fv.FV_F32, dt_fixed=5e-4, learned=1)
     s.learned_step(m, 5)
     assert np.array_equal(out, s.state().astype(np.float32))
+
+
+@pytest.mark.parametrize("B,nx,ny", [(64, 64, 64), (2, 32, 4), (3, 16, 8)])
+def test_forward_scratch(fv, B, nx, ny):
+    """A forward allocates its output and the scratch that its shape uses: two
+    activation planes of 64 bytes per cell below eight rows, none from there
+    on; z is the one-launch pass's where that takes the shape."""
+    import torch
+
+    rng = np.random.default_rng(5)
+    m = fv.Model((rng.standard_normal(fv.fv_model_param_count()) * 0.02).astype(np.float32))
+    q = torch.tensor(rng.uniform(0.8, 1.2, (B, 3, ny, nx)), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    z = m.forward(q)
+    torch.cuda.synchronize()
+    extra = torch.cuda.max_memory_allocated() - before - z.numel() * 4
+    print(f"[pool bytes] forward {B} x {nx}x{ny}: {extra} bytes", flush=True)
+    assert extra <= (1024 if ny >= 8 else 2 * 64 * B * nx * ny + 1024)
+    assert torch.isfinite(z).all()
+    if ny >= 8:
+        assert torch.equal(z, m.forward_tiled(q))

@@ -536,12 +536,11 @@ fv_status fv_coarsen(const float *fine, int nvar, int nx, int ny, int factor, fl
  * coefficients staying on chip; then commit-or-redo and redo), or, in rounds
  * with many learned tiles (learned_split), six (the network pass and the
  * learned stage as separate launches, the network pass on wide tiles with its
- * weights in registers where every learned side is a multiple of 16).  A
- * round's launches are recorded once, per kinds of work present
- * and number of steps, into a hipGraph that every later round replays: the
- * kernels read their tile counts from the device work-lists, and between
- * replays the host rewrites those lists and sets each launch's grid to its
- * list's tiles.
+ * weights in registers).  A round's launches are recorded once, per kinds of
+ * work present and number of steps, into a hipGraph that every later round
+ * replays: the kernels read their tile counts from the device work-lists, and
+ * between replays the host rewrites those lists and sets each launch's grid to
+ * its list's tiles.
  * Finished solves are copied back and their memory returns to the pool.
  * The single-solve calls (fv_run, fv_learned_step) run the same kernels as a
  * batch of one, so a solve's result is bit-identical alone and in any mix.
@@ -564,9 +563,8 @@ typedef struct {
                                 workgroups of the network pass resident at once, or more than 3 x
                                 where the network pass runs on wide tiles.  Same results either way. */
     int32_t learned_layered; /* 16 x 16-cell tiles in a round's first step from which a round with
-                                separate launches runs the network pass on wide tiles (all learned
-                                sides multiples of 16) instead of 8 x 8 ones; 0: any number; -1:
-                                never.  Same results either way. */
+                                separate launches runs the network pass on wide tiles instead of
+                                8 x 8 ones; 0: any number; -1: never.  Same results either way. */
     uint64_t act_pixels;     /* cells of activation scratch to set aside in the pool (128 bytes per
                                 cell, counted in fv_server_pool_overhead).  The network pass keeps
                                 its activations on chip: nothing is read or written there, 0 leaves

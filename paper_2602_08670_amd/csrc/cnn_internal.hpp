@@ -103,7 +103,7 @@ hipError_t launch_learned_batch(int mode, int stage, const LSolve *tab, const LI
 // The forms recorded in graphs: wgs workgroups (set before each replay: the
 // list's stage tiles, and for the network pass at most fused_max_grid()),
 // the tile counts read from the list header list = {items, network tiles,
-// stage tiles, 0}.
+// stage tiles, wide network tiles}.
 hipError_t launch_forward_batch_list(int stage, const void *packed, const Norm &nrm, const LSolve *tab,
                                      const LItem *items, const int *list, int wgs, hipStream_t st);
 hipError_t launch_learned_batch_list(int mode, int stage, const LSolve *tab, const LItem *items, const int *list,

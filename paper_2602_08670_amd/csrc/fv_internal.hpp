@@ -135,9 +135,15 @@ inline int64_t stage_tiles(int nx, int ny, int shape)
 {
     return (int64_t)((nx + TILE_X - 1) / TILE_X) * ((ny + shape_rows(shape) - 1) / shape_rows(shape));
 }
-// One workgroup per tile: grid = the list's tiles of the given shape.
-hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
-                              const WorkItem *items, const int *nitems, int grid, hipStream_t st);
+// The work lists' shape, one for all of a server's rounds, since a captured
+// launch keeps its kernel and a graph per shape would be captured for each.  Of
+// the four this one is within 3 % of the best from half a million cells in a
+// launch on, which a loaded server's rounds hold.
+constexpr int LIST_SHAPE = 2;
+// One workgroup per tile: grid = the list's tiles of LIST_SHAPE.  Shallow water
+// has a bed.
+hipError_t launch_batch_stage(int eqn, int stage, const BatchSolve *solves, const WorkItem *items, const int *nitems,
+                              int grid, hipStream_t st);
 // One solve, descriptor and list entry by value (it.tile_begin == 0): the
 // launches of a single solve.
 hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
@@ -145,8 +151,8 @@ hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, cons
 // The form recorded in graphs: wgs workgroups (a multiple of 8, set to
 // xcd_grid(tiles) before each replay), the tile count read from the list
 // header list = {items, tiles}.
-hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
-                                   const WorkItem *items, const int *list, int wgs, hipStream_t st);
+hipError_t launch_batch_stage_list(int eqn, int stage, const BatchSolve *solves, const WorkItem *items, const int *list,
+                                   int wgs, hipStream_t st);
 // Grid of a tiled launch: the tiles padded to a multiple of the 8 XCDs.
 __host__ __device__ inline int xcd_grid(int ntiles) { return (ntiles + 7) & ~7; }
 

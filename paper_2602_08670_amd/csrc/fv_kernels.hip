@@ -1167,54 +1167,21 @@ static hipError_t rate_t(const StageDesc &d, const void *q, Ctl *ctl, unsigned l
     return hipGetLastError();
 }
 
-// The kernel of a batched launch: form 0 the list's, 1 a single solve's.
-template <int EQN, bool BATHY, int STAGE, int SHAPE>
-static void batch_kernel_s(const void *fn[2], int *threads)
+// A single solve's kernel in every shape; the lists' in theirs, with a bed
+// under shallow water (a flat one is a bed of zeros).
+template <int EQN, bool BATHY, int STAGE, int SHAPE> static const void *one_kernel(int *threads)
 {
-    fn[0] = (const void *)batch_stage_kernel<float, EQN, BATHY, STAGE, SHAPE>;
-    fn[1] = (const void *)batch_stage_one_kernel<float, EQN, BATHY, STAGE, SHAPE>;
     *threads = ShapeLds<float, EQN, BATHY, SHAPE>::NTH;
+    return (const void *)batch_stage_one_kernel<float, EQN, BATHY, STAGE, SHAPE>;
 }
-template <int EQN, bool BATHY, int STAGE>
-static void batch_kernel_e(int shape, const void *fn[2], int *threads)
+template <int EQN, bool BATHY, int STAGE> static const void *one_kernel_e(int shape, int *threads)
 {
     switch (shape) {
-    case 0: return batch_kernel_s<EQN, BATHY, STAGE, 0>(fn, threads);
-    case 1: return batch_kernel_s<EQN, BATHY, STAGE, 1>(fn, threads);
-    case 2: return batch_kernel_s<EQN, BATHY, STAGE, 2>(fn, threads);
-    default: return batch_kernel_s<EQN, BATHY, STAGE, 3>(fn, threads);
+    case 0: return one_kernel<EQN, BATHY, STAGE, 0>(threads);
+    case 1: return one_kernel<EQN, BATHY, STAGE, 1>(threads);
+    case 2: return one_kernel<EQN, BATHY, STAGE, 2>(threads);
+    default: return one_kernel<EQN, BATHY, STAGE, 3>(threads);
     }
-}
-static void batch_kernel(int eqn, int bathy, int stage, int shape, const void *fn[2], int *threads)
-{
-    if (eqn == EULER) {
-        if (stage == 1) batch_kernel_e<EULER, false, 1>(shape, fn, threads);
-        else batch_kernel_e<EULER, false, 2>(shape, fn, threads);
-    } else if (bathy) {
-        if (stage == 1) batch_kernel_e<SWE, true, 1>(shape, fn, threads);
-        else batch_kernel_e<SWE, true, 2>(shape, fn, threads);
-    } else {
-        if (stage == 1) batch_kernel_e<SWE, false, 1>(shape, fn, threads);
-        else batch_kernel_e<SWE, false, 2>(shape, fn, threads);
-    }
-}
-
-static hipError_t go_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves, const WorkItem *items,
-                          const int *nitems, int ntiles, int wgs, hipStream_t st)
-{
-    const void *fn[2];
-    int threads;
-    batch_kernel(eqn, bathy, stage, shape, fn, &threads);
-    void *args[] = {(void *)&solves, (void *)&items, (void *)&nitems, (void *)&ntiles};
-    return hipLaunchKernel(fn[0], dim3(wgs), dim3(threads), args, 0, st);
-}
-
-hipError_t launch_batch_stage(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
-                              const WorkItem *items, const int *nitems, int grid, hipStream_t st)
-{
-    if (grid <= 0) return hipSuccess;
-    if (shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
-    return go_list(eqn, bathy, stage, shape, solves, items, nitems, grid, xcd_grid(grid), st);
 }
 
 hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, const BatchSolve &d, const WorkItem &it,
@@ -1222,18 +1189,46 @@ hipError_t launch_batch_stage_one(int eqn, int bathy, int stage, int shape, cons
 {
     if (grid <= 0) return hipSuccess;
     if (it.tile_begin != 0 || shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
-    const void *fn[2];
     int threads;
-    batch_kernel(eqn, bathy, stage, shape, fn, &threads);
+    const void *fn;
+    if (eqn == EULER)
+        fn = stage == 1 ? one_kernel_e<EULER, false, 1>(shape, &threads) : one_kernel_e<EULER, false, 2>(shape, &threads);
+    else if (bathy)
+        fn = stage == 1 ? one_kernel_e<SWE, true, 1>(shape, &threads) : one_kernel_e<SWE, true, 2>(shape, &threads);
+    else
+        fn = stage == 1 ? one_kernel_e<SWE, false, 1>(shape, &threads) : one_kernel_e<SWE, false, 2>(shape, &threads);
     void *args[] = {(void *)&d, (void *)&it, (void *)&grid};
-    return hipLaunchKernel(fn[1], dim3(xcd_grid(grid)), dim3(threads), args, 0, st);
+    return hipLaunchKernel(fn, dim3(xcd_grid(grid)), dim3(threads), args, 0, st);
 }
 
-hipError_t launch_batch_stage_list(int eqn, int bathy, int stage, int shape, const BatchSolve *solves,
-                                   const WorkItem *items, const int *list, int wgs, hipStream_t st)
+template <int EQN, bool BATHY>
+static hipError_t go_list(int stage, const BatchSolve *solves, const WorkItem *items, const int *nitems, int ntiles,
+                          int wgs, hipStream_t st)
 {
-    if (wgs <= 0 || (wgs & 7) || shape < 0 || shape >= NSHAPES) return hipErrorInvalidValue;
-    return go_list(eqn, bathy, stage, shape, solves, items, list, 0, wgs, st);
+    const dim3 grid(wgs), blk(ShapeLds<float, EQN, BATHY, LIST_SHAPE>::NTH);
+    if (stage == 1)
+        hipLaunchKernelGGL((batch_stage_kernel<float, EQN, BATHY, 1, LIST_SHAPE>), grid, blk, 0, st, solves, items,
+                           nitems, ntiles);
+    else
+        hipLaunchKernelGGL((batch_stage_kernel<float, EQN, BATHY, 2, LIST_SHAPE>), grid, blk, 0, st, solves, items,
+                           nitems, ntiles);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_stage(int eqn, int stage, const BatchSolve *solves, const WorkItem *items, const int *nitems,
+                              int grid, hipStream_t st)
+{
+    if (grid <= 0) return hipSuccess;
+    return eqn == EULER ? go_list<EULER, false>(stage, solves, items, nitems, grid, xcd_grid(grid), st)
+                        : go_list<SWE, true>(stage, solves, items, nitems, grid, xcd_grid(grid), st);
+}
+
+hipError_t launch_batch_stage_list(int eqn, int stage, const BatchSolve *solves, const WorkItem *items, const int *list,
+                                   int wgs, hipStream_t st)
+{
+    if (wgs <= 0 || (wgs & 7)) return hipErrorInvalidValue;
+    return eqn == EULER ? go_list<EULER, false>(stage, solves, items, list, 0, wgs, st)
+                        : go_list<SWE, true>(stage, solves, items, list, 0, wgs, st);
 }
 
 hipError_t launch_rate(const StageDesc &d, const void *q, Ctl *ctl, unsigned long long *rates, int slot,

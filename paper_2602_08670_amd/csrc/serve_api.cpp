@@ -54,12 +54,6 @@ struct Req {
     bool learned() const { return r.learned != 0; }
 };
 
-// Tile shape of the plain solves' batched launches: one for all rounds, since
-// a captured launch keeps its kernel and a graph per shape would be captured
-// for each.  Of the four this one is within 3 % of the best from half a
-// million cells in a launch on, which a loaded server's rounds hold.
-constexpr int PLAIN_SHAPE = 2;
-
 // max_items counts a plain solve's tiles of 64 x 32 cells, whatever the shape
 // of the launches.
 uint64_t plain_items(int n) { return (uint64_t)((n + 63) / 64) * ((n + 31) / 32); }
@@ -181,7 +175,7 @@ void free_host(fv_server *s)
 
 // one list per step and equation type, one item per active solve; list
 // headers on the device: plain {items, tiles}, learned {items, network
-// tiles, stage tiles, 0}
+// tiles, stage tiles, wide network tiles}
 constexpr int HDR = 2, LHDR = 4;
 constexpr size_t ACT_BYTES = 2 * 32 * 2;  // per cell set aside: two BF16 32-channel activations
 size_t items_capacity(const fv_server_config *c) { return (size_t)c->steps_per_round * 2 * c->max_solves; }
@@ -385,11 +379,9 @@ hipError_t enqueue_steps(fv_server *s, int mask, int nsteps, const int *grids, c
                 const fvk::WorkItem *it = d_items + li * ncap;
                 const int *hdr = d_nitems + li * HDR;
                 if (!rec) {
-                    e = fvk::launch_batch_stage(eqn, type == 0, stage, PLAIN_SHAPE, tab, it, hdr, grids[li],
-                                                s->stream);
+                    e = fvk::launch_batch_stage(eqn, stage, tab, it, hdr, grids[li], s->stream);
                 } else {
-                    e = fvk::launch_batch_stage_list(eqn, type == 0, stage, PLAIN_SHAPE, tab, it, hdr, 8,
-                                                     s->stream);
+                    e = fvk::launch_batch_stage_list(eqn, stage, tab, it, hdr, 8, s->stream);
                     if (e == hipSuccess) e = record(0, (int)li);
                 }
             }
@@ -674,7 +666,6 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
     const size_t ncap = (size_t)s->cfg.max_solves;
     std::vector<int> counts((size_t)K * 2, 0), grids((size_t)K * 2, 0);
     std::vector<int> lcounts((size_t)K, 0), lgrid_cnn((size_t)K, 0), lgrid_st((size_t)K, 0), lgrid_h((size_t)K, 0);
-    bool all16 = true;  // every learned side a multiple of 16 (the wide-tile pass's)
     int64_t tiles16 = 0;  // 16 x 16 tiles of the first step
     for (int k = 0; k < K; k++)
         for (Req *q : s->active) {
@@ -693,12 +684,8 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
                 lcounts[k]++;
                 lgrid_cnn[k] += tc;
                 lgrid_st[k] += ts;
-                if (!cnn::net_takes(q->r.n, q->r.n)) {
-                    all16 = false;
-                } else {
-                    lgrid_h[k] += cnn::net_tiles(q->r.n, q->r.n);
-                    if (k == 0) tiles16 += (int64_t)(q->r.n / 16) * (q->r.n / 16);
-                }
+                lgrid_h[k] += cnn::net_tiles(q->r.n, q->r.n);
+                if (k == 0) tiles16 += (int64_t)(q->r.n / 16) * (q->r.n / 16);
                 continue;
             }
             int type = q->r.eqn == FV_EULER ? 1 : 0;
@@ -713,7 +700,7 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
             w.rc = (unsigned char)((st + 2) % 3);
             w.pad = 0;
             counts[li]++;
-            grids[li] += (int)fvk::stage_tiles(q->r.n, q->r.n, PLAIN_SHAPE);
+            grids[li] += (int)fvk::stage_tiles(q->r.n, q->r.n, fvk::LIST_SHAPE);
         }
     int mask = 0, nsteps = 0;  // kinds of work present (1 SWE, 2 Euler, 4 learned), last non-empty step + 1
     for (int k = 0; k < K; k++) {
@@ -722,11 +709,12 @@ fv_status fv_server_round(fv_server *s, int32_t *n_active, int32_t *n_queued)
         mask |= m;
     }
     // many learned tiles: separate network-pass and learned-stage launches,
-    // the network pass on wide tiles with its weights in registers where
-    // every side allows it; few: one launch per stage, coefficients on chip.
-    // A fourth round of 8 x 8 tiles (11.5 us each) costs more than the wide
-    // tiles and the separate stage; with 8 x 8 tiles either way, the fifth.
-    const bool wide = all16 && s->layered_at > 0 && tiles16 >= s->layered_at;
+    // the network pass on wide tiles with its weights in registers unless the
+    // configuration asks for 8 x 8 ones; few: one launch per stage,
+    // coefficients on chip.  A fourth round of 8 x 8 tiles (11.5 us each) costs
+    // more than the wide tiles and the separate stage; with 8 x 8 tiles either
+    // way, the fifth.
+    const bool wide = s->layered_at > 0 && tiles16 >= s->layered_at;
     const int split = s->split_at ? s->split_at : wide ? 3 * s->cnn_cap + 1 : 4 * s->cnn_cap;
     if ((mask & 4) && lgrid_cnn[0] >= split) mask |= wide ? 8 | 16 : 8;
     for (size_t li = 0; li < counts.size(); li++) {

@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfv.so")
 
-SOURCES = ["fv_kernels.hip", "cnn_kernels.hip", "net_kernels.hip", "learned_kernels.hip", "adjoint_kernels.hip", "train_kernels.hip",
+SOURCES = ["fv_kernels.hip", "step_swe_f32.hip", "step_swe_f64.hip", "step_euler_f32.hip", "step_euler_f64.hip",
+           "cnn_kernels.hip", "net_kernels.hip", "learned_kernels.hip", "adjoint_kernels.hip", "train_kernels.hip",
            "sphere_kernels.hip", "euler_learned_kernels.hip", "fv_api.cpp", "train_api.cpp", "serve_api.cpp",
            "sphere_api.cpp", "euler_learned_api.cpp"]
 

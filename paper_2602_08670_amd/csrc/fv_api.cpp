@@ -412,6 +412,10 @@ fv_status fv_init(const fv_config *cfg, void *q, const void *bathy, void *worksp
         if (rc == FV_OK) s->d.h0 = tot[0] / (cfg->lx * cfg->ly);
     }
     if (rc == FV_OK && s->batched) batch_block(s);
+    if (rc == FV_OK && fvk::step_fits(s->d, cfg->rk_stages)) {
+        e = fvk::load_step(s->d.prec, s->d.eqn);
+        if (e != hipSuccess) rc = hip_fail(e, "step kernels");
+    }
     if (rc == FV_OK && cfg->learned) rc = upload_lbatch(s);
     if (rc != FV_OK) {
         delete s;
@@ -551,6 +555,10 @@ fv_status scratch_on_current_device(void **out)
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
         if (!p || ((uintptr_t)p & 255) != 0) return fail(FV_E_HIP, "scratch address %p not 256-byte aligned", p);
+        for (int k = 0; k < 4; k++) {
+            e = fvk::load_step(k & 1, k >> 1);
+            if (e != hipSuccess) return hip_fail(e, "step kernels");
+        }
         g_scratch_ptr[dev] = p;
     }
     *out = g_scratch_ptr[dev];

@@ -63,6 +63,9 @@ hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void
 // one launch, with the last stage's bookkeeping; own is BAD_EVEN or BAD_ODD.
 hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
                        unsigned long long *rates, int rate_in, int rate_out, int rate_clear, int own, hipStream_t st);
+// Has launch_step's kernels of a precision and system loaded on the current
+// device, so that a later launch loads nothing (it may be under capture).
+hipError_t load_step(int prec, int eqn);
 // The end of a step whose launch went to another buffer than the state's: the
 // state copied back.
 hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl *ctl, hipStream_t st);

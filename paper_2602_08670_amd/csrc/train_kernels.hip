@@ -109,7 +109,27 @@ namespace cnn {
 
 // Exact cell-average coarsening: coarse(I, J) = mean of the f x f fine block,
 // accumulated in double precision in a fixed order.  Bound by reading the
-// fine array once.  A workgroup takes
+// fine array once.  Below CO_BLOCK a thread sums a coarse cell's block by
+// itself: a wave's lines are used whole within a few of its loads (3 x 2048^2
+// at f = 2: 15 us, 41 as below; f = 4: 15 and 22; 3 x 2100^2 at f = 7: 16 and
+// 18; 3 x 2048^2 at f = 8: 24 and 11).
+constexpr int CO_BLOCK = 8;
+__global__ void coarsen_cell_kernel(const float *__restrict__ fine, int nvar, int nx, int ny, int f,
+                                    float *__restrict__ coarse)
+{
+    const int cx = nx / f, cy = ny / f;
+    const size_t n = (size_t)nvar * cx * cy;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t v = i / ((size_t)cx * cy);
+        const int r = (int)(i - v * cx * cy), J = r / cx, I = r - J * cx;
+        const float *src = fine + v * nx * ny + (size_t)J * f * nx + (size_t)I * f;
+        double acc = 0.0;
+        for (int a = 0; a < f; a++)
+            for (int b = 0; b < f; b++) acc += (double)src[(size_t)a * nx + b];
+        coarse[i] = (float)(acc / ((double)f * f));
+    }
+}
+// From there on a workgroup takes
 // 256 / f coarse cells of a row (one where f > 256): thread t sums column t of
 // their fine cells down the f rows, so that a wave reads whole lines and has
 // its rows' loads in flight together, then one thread per coarse cell adds its
@@ -148,6 +168,12 @@ __global__ __launch_bounds__(CO_TH) void coarsen_kernel(const float *__restrict_
 
 hipError_t launch_coarsen(const float *fine, int nvar, int nx, int ny, int f, float *coarse, hipStream_t st)
 {
+    if (f < CO_BLOCK) {
+        const size_t blocks = ((size_t)nvar * (nx / f) * (ny / f) + 255) / 256;
+        hipLaunchKernelGGL(coarsen_cell_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st, fine,
+                           nvar, nx, ny, f, coarse);
+        return hipGetLastError();
+    }
     const int cb = f <= CO_TH ? CO_TH / f : 1;
     const long total = (long)nvar * (ny / f) * ((nx / f + cb - 1) / cb);
     hipLaunchKernelGGL(coarsen_kernel, dim3((unsigned)(total < 1 << 20 ? total : 1 << 20)), dim3(CO_TH), 0, st, fine,

@@ -189,21 +189,23 @@ fv_status enqueue_step(fv_solver *s)
     }
     switch (s->cfg.rk_stages) {
     case 1:
-        // to the stage buffer and back: a frozen state is carried through both
-        e = fvk::launch_step(s->d, 1, s->q, S1, s->bed, ctl, s->rates(), ri, ro, rc, fvk::BAD_EVEN, s->stream);
+        e = fvk::launch_stage(s->d, s->q, s->q, S1, s->bed, 0.0, 1.0, ctl, s->rates(), ri, ro, rc, fvk::BAD_EVEN,
+                              s->stream);
         if (e == hipSuccess) e = fvk::launch_step_copy(s->d, S1, s->q, ctl, s->stream);
         break;
     case 2:
         e = fvk::launch_stage(s->d, s->q, s->q, S1, s->bed, 0.0, 1.0, ctl, s->rates(), ri, -1, -1, 0, s->stream);
         if (e == hipSuccess)
-            e = fvk::launch_stage(s->d, S1, s->q, s->q, s->bed, 0.5, 0.5, ctl, s->rates(), ri, ro, rc, 1, s->stream);
+            e = fvk::launch_stage(s->d, S1, s->q, s->q, s->bed, 0.5, 0.5, ctl, s->rates(), ri, ro, rc, fvk::BAD_STEP,
+                                  s->stream);
         break;
     default:
         e = fvk::launch_stage(s->d, s->q, s->q, S1, s->bed, 0.0, 1.0, ctl, s->rates(), ri, -1, -1, 0, s->stream);
         if (e == hipSuccess)
             e = fvk::launch_stage(s->d, S1, s->q, S2, s->bed, 0.75, 0.25, ctl, s->rates(), ri, -1, -1, 0, s->stream);
         if (e == hipSuccess)
-            e = fvk::launch_stage(s->d, S2, s->q, s->q, s->bed, 1.0 / 3.0, 2.0 / 3.0, ctl, s->rates(), ri, ro, rc, 1, s->stream);
+            e = fvk::launch_stage(s->d, S2, s->q, s->q, s->bed, 1.0 / 3.0, 2.0 / 3.0, ctl, s->rates(), ri, ro, rc, fvk::BAD_STEP,
+                                  s->stream);
         break;
     }
     if (e != hipSuccess) return hip_fail(e, "stage launch");

@@ -20,10 +20,10 @@ static_assert(sizeof(Ctl) == 64, "control block layout");
 // not set, so that the whole step is stored, whichever workgroup fails first,
 // and counted; every later launch finds a bit that is not its own, skips, and
 // sets BAD_SKIP for those of the same kind behind it.  The kinds alternate: the
-// first launch of a step in several (no bit of its own) or the step's copy
-// stands between two BAD_STEP or BAD_EVEN launches, and steps in pairs take
-// BAD_EVEN and BAD_ODD in turn.
-enum Bad { BAD_SKIP = 1, BAD_STEP = 2, BAD_EVEN = 4, BAD_ODD = 8 };
+// first launch of a step in several (no bit of its own) or a step's copy
+// (BAD_COPY) stands between two BAD_STEP or BAD_EVEN launches, and steps in
+// pairs take BAD_EVEN and BAD_ODD in turn.
+enum Bad { BAD_SKIP = 1, BAD_STEP = 2, BAD_EVEN = 4, BAD_ODD = 8, BAD_COPY = 16 };
 
 // CFL rate slots.  Slot k holds RATE_SUB sub-slots, each the bits of a
 // non-negative double reduced with atomicMax on the bit pattern (monotone for
@@ -54,10 +54,11 @@ struct StageDesc {
 // One RK stage: out = a0*q0 + a1*(qs + dt*L(qs)); q0 is read only at the
 // updated cell, so out may alias q0.  On the last stage the CFL rate of out
 // is reduced into ctl->rate[rate_out] (rate_out >= 0), rate_clear is zeroed,
-// admissibility is checked and time/step advance.
+// admissibility is checked and time/step advance; own is the Bad bit it raises
+// (0 on the others).
 hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed,
                         double a0, double a1, Ctl *ctl, unsigned long long *rates, int rate_in, int rate_out,
-                        int rate_clear, int last, hipStream_t st);
+                        int rate_clear, int own, hipStream_t st);
 
 // A whole step of 1, 2 or 3 stages from src to dst (not the same buffer) in
 // one launch, with the last stage's bookkeeping; own is BAD_EVEN or BAD_ODD.
@@ -66,8 +67,8 @@ hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *ds
 // Has launch_step's kernels of a precision and system loaded on the current
 // device, so that a later launch loads nothing (it may be under capture).
 hipError_t load_step(int prec, int eqn);
-// The end of a step whose launch went to another buffer than the state's: the
-// state copied back.
+// The end of a step whose BAD_EVEN launch went to another buffer than the
+// state's: the result copied back, unless the launch skipped the step.
 hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl *ctl, hipStream_t st);
 // The grids that step so.  One stage: no ring, and no copy back to the state
 // (16 steps of 500^2 cells 86 us, with a launch and a copy 151, 1400^2 324 and

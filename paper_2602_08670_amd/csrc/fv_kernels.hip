@@ -299,14 +299,14 @@ __global__ void face_kernel(const T *q, int nx, int ny, int bc_x, int bc_y, Phys
 
 template <typename T, int EQN, bool BATHY, int FLUX, int RECON>
 static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
-                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
+                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int own,
                           hipStream_t st)
 {
     StageArgs<T> a = stage_args<T>(d, qs, q0, out, bed, ctl, rates, ri, ro, rc);
     a.a0 = (T)a0;
     a.a1 = (T)a1;
-    a.last = last;
-    a.own = last ? BAD_STEP : 0;
+    a.last = own != 0;
+    a.own = own;
     // the shapes with one and with two rows per wave serve every scheme, the
     // other two FP32 HLLE with MINMOD (the scheme of long runs)
     constexpr bool ALL = sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD;
@@ -329,43 +329,43 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
 
 template <typename T, int EQN, bool BATHY, int FLUX>
 static hipError_t stage_r(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
-                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
+                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int own,
                           hipStream_t st)
 {
     if (d.recon == FIRST)
-        return stage_t<T, EQN, BATHY, FLUX, FIRST>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
-    return stage_t<T, EQN, BATHY, FLUX, MINMOD>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
+        return stage_t<T, EQN, BATHY, FLUX, FIRST>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
+    return stage_t<T, EQN, BATHY, FLUX, MINMOD>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
 }
 
 template <typename T, int EQN, bool BATHY>
 static hipError_t stage_f(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
-                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
+                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int own,
                           hipStream_t st)
 {
     switch (d.flux) {
-    case RUSANOV: return stage_r<T, EQN, BATHY, RUSANOV>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
-    case ROE: return stage_r<T, EQN, BATHY, ROE>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
-    default: return stage_r<T, EQN, BATHY, HLLE>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
+    case RUSANOV: return stage_r<T, EQN, BATHY, RUSANOV>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
+    case ROE: return stage_r<T, EQN, BATHY, ROE>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
+    default: return stage_r<T, EQN, BATHY, HLLE>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
     }
 }
 
 template <typename T>
 static hipError_t stage_p(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
-                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int last,
+                          double a1, Ctl *ctl, unsigned long long *rates, int ri, int ro, int rc, int own,
                           hipStream_t st)
 {
-    if (d.eqn == EULER) return stage_f<T, EULER, false>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
-    if (d.bathy) return stage_f<T, SWE, true>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
-    return stage_f<T, SWE, false>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, last, st);
+    if (d.eqn == EULER) return stage_f<T, EULER, false>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
+    if (d.bathy) return stage_f<T, SWE, true>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
+    return stage_f<T, SWE, false>(d, qs, q0, out, bed, a0, a1, ctl, rates, ri, ro, rc, own, st);
 }
 
 hipError_t launch_stage(const StageDesc &d, const void *qs, const void *q0, void *out, const void *bed, double a0,
                         double a1, Ctl *ctl, unsigned long long *rates, int rate_in, int rate_out, int rate_clear,
-                        int last, hipStream_t st)
+                        int own, hipStream_t st)
 {
     if (d.prec == 1)
-        return stage_p<double>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, last, st);
-    return stage_p<float>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, last, st);
+        return stage_p<double>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, own, st);
+    return stage_p<float>(d, qs, q0, out, bed, a0, a1, ctl, rates, rate_in, rate_out, rate_clear, own, st);
 }
 
 hipError_t launch_step(const StageDesc &d, int stages, const void *src, void *dst, const void *bed, Ctl *ctl,
@@ -391,19 +391,24 @@ template <typename T>
 __global__ __launch_bounds__(256) void step_copy_kernel(const T *__restrict__ src, T *__restrict__ dst, size_t n,
                                                         Ctl *ctl)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0 && ctl->bad) atomicOr(&ctl->bad, BAD_SKIP);
+    const int bad = ctl->bad;
+    if (bad & ~(BAD_EVEN | BAD_COPY)) return;
+    if (bad && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ctl->bad, BAD_COPY);
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
 hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl *ctl, hipStream_t st)
 {
-    const size_t n = (size_t)(d.eqn == EULER ? 4 : 3) * d.nx * d.ny, blocks = (n + 255) / 256;
-    const dim3 grid((unsigned)(blocks < 8192 ? blocks : 8192));
-    if (d.prec == 1)
-        hipLaunchKernelGGL(step_copy_kernel<double>, grid, dim3(256), 0, st, (const double *)src, (double *)dst, n, ctl);
-    else
-        hipLaunchKernelGGL(step_copy_kernel<float>, grid, dim3(256), 0, st, (const float *)src, (float *)dst, n, ctl);
-    return hipGetLastError();
+    const size_t bytes = (size_t)(d.eqn == EULER ? 4 : 3) * d.nx * d.ny * (d.prec == 1 ? 8 : 4);
+    auto go = [&](auto unit) {
+        using U = decltype(unit);
+        const size_t n = bytes / sizeof(U), blocks = (n + 255) / 256;
+        hipLaunchKernelGGL(step_copy_kernel<U>, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st,
+                           (const U *)src, (U *)dst, n, ctl);
+        return hipGetLastError();
+    };
+    // 16 bytes per lane where the caller's state allows it
+    return (((uintptr_t)src | (uintptr_t)dst | bytes) & 15) ? go(0.0f) : go(float4{});
 }
 
 template <typename T>

@@ -7,6 +7,10 @@
 
 namespace fvk {
 
+// Compute units of an MI355X, which the rules on launch shapes count tiles
+// against (a device with fewer takes the same shapes).
+constexpr int CUS = 256;
+
 // Device control block of one solve (lives in the caller's workspace).
 struct Ctl {
     double t;             // simulated time
@@ -73,9 +77,10 @@ hipError_t launch_step_copy(const StageDesc &d, const void *src, void *dst, Ctl 
 // The grids that step so.  One stage: no ring, and no copy back to the state
 // (16 steps of 500^2 cells 86 us, with a launch and a copy 151, 1400^2 324 and
 // 453): all.  FP32 Heun HLLE with MINMOD, in tiles of up to 12 rows: up to
-// where the rings cost what the launches do (800^2 272 us and 286 with a
-// launch per stage, 1000 x 700 Euler 322 and 323, 1024^2 425 and 327).  The
-// others, in 4 or 8 rows: while every tile has a CU of its own (FP32 Roe Heun
+// where the rings cost what the launches do (over a bed 760^2 272 us and 268
+// with a launch per stage, 800^2 275 and 289, 1024^2 425 and 327, a flat bottom
+// alike; Euler, with more work in a ring, 720^2 286 and 311, 760^2 351 and 318).
+// The others, in 4 or 8 rows: while every tile has a CU of its own (FP32 Roe Heun
 // 320^2 108 and 143, 500^2 189 and 183; FP64 Heun 320^2 160 and 201; FP64 Roe
 // in three stages, 4 rows: 200^2 193 and 242, 250^2 352 and 245).
 inline int step_rows(const StageDesc &d, int stages)  // most rows of a tile
@@ -89,8 +94,8 @@ inline bool step_fits(const StageDesc &d, int stages)
     if (d.nx < 2 * stages || d.ny < 2 * stages) return false;
     const int rows = step_rows(d, stages), cols = 64 - 4 * (stages - 1);
     if (stages == 1) return true;
-    if (rows == 12) return cells <= 640000;
-    return (int64_t)((d.nx + cols - 1) / cols) * ((d.ny + rows - 1) / rows) <= 256;
+    if (rows == 12) return cells <= (d.eqn == 1 ? 540000 : 640000);
+    return (int64_t)((d.nx + cols - 1) / cols) * ((d.ny + rows - 1) / rows) <= CUS;
 }
 
 // Batched FP32 Heun stages over many solves (serving).  BatchSolve is one

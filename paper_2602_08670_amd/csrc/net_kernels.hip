@@ -32,6 +32,7 @@
 // 20 000 with its stores); 64 x 80 x 64 81 and 66 us, 16 x 64^2 33 and 20 us;
 // one tile per workgroup is bound by its chain of loads and layers, 11 us.
 #include "cnn_internal.hpp"
+#include "fv_internal.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -488,7 +489,7 @@ NetArgs net_args(const void *packed, const PK &pk, const NormT &nrm, const float
     long best = 0;
     for (int tw = nx <= MAXWRAP ? nx : MAXW; tw >= 16; tw = (tw < nx ? tw : std::min(nx, MAXW + 16)) - 16) {
         const long grown = tw < nx, tiles = (long)B * a.tyn * ((nx + tw - 1) / tw), g = tw / 16;
-        const long cost = (tiles + 255) / 256 * (750 + (g + grown + 1) / 2 * 2 * 36 * 18 + g * 8 * 9 * Net<C>::NT);
+        const long cost = (tiles + fvk::CUS - 1) / fvk::CUS * (750 + (g + grown + 1) / 2 * 2 * 36 * 18 + g * 8 * 9 * Net<C>::NT);
         if (!a.tw || cost < best) {
             best = cost;
             a.tw = tw;
@@ -509,7 +510,7 @@ int net_grid(int ntiles)
         int dev = 0, n = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
+            n = fvk::CUS;
         return n;
     }();
     return ntiles < cus ? ntiles : cus;

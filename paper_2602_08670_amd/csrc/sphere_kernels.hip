@@ -581,7 +581,7 @@ template <typename T> hipError_t stage(int flux, int recon, const CellArgs<T> &a
     // 5.6 against 6.1); from there on the registers cost more than the loads'
     // latency (FP32 720 x 360 cells: 13.5 against 12.2 us).
     constexpr int PY = sizeof(T) == 4 ? 8 : 4, PN = sizeof(T) == 4 ? 320 : 192;
-    if ((2 * a.n + STX - 1) / STX * ((a.n + PY - 1) / PY) <= 256) return stage_go<T, PY, PN, true>(flux, recon, a, st);
+    if ((2 * a.n + STX - 1) / STX * ((a.n + PY - 1) / PY) <= fvk::CUS) return stage_go<T, PY, PN, true>(flux, recon, a, st);
     return stage_go<T, 8, 320, false>(flux, recon, a, st);
 }
 

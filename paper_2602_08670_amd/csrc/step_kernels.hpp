@@ -193,7 +193,7 @@ static hipError_t step_s(const StageDesc &d, const StageArgs<T> &a, hipStream_t 
     };
     const int most = step_rows(d, S);
     const int64_t cols = (d.nx + step_cols(S) - 1) / step_cols(S);
-    const bool four = cols * ((d.ny + 3) / 4) <= 256, eight = cols * ((d.ny + 7) / 8) <= 256;
+    const bool four = cols * ((d.ny + 3) / 4) <= CUS, eight = cols * ((d.ny + 7) / 8) <= CUS;
     if (four || most == 4) return go(std::integral_constant<int, 4>{});
     if constexpr (S == 2 || (S == 3 && sizeof(T) == 4)) {
         if constexpr (S == 2 && sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD)

@@ -305,11 +305,13 @@ template <typename T, int EQN> struct StageIO {
 // owner inside the wave are the tile's right column (one lane per row, wave
 // 0, through LDS), the tile's top row (last wave) and the low face of each
 // wave's first row, which the wave below reads through LDS.
-// Bound by vector-ALU issue where the chip is full: 228 lane instructions per
-// cell and stage of shallow water over a bed (270 before the faces shared
-// their reconstruction and the flux was rearranged), 1024^2 21.3 -> 20.4 us a
-// step, 2048^2 76.2 -> 63.6, Euler 1000 x 700 26.6 -> 19.9; by latency on
-// small grids (64^2 13.0 -> 8.0).
+// Bound by vector-ALU issue and, a grid of one round of tiles, by the wait for
+// its halos: 229 and 253 lane instructions per cell in the two stages of
+// shallow water over a bed (270 and 299 before the faces shared their
+// reconstruction and the flux was rearranged) keep the SIMDs busy for 59 % of
+// the traced kernels at 1024^2; a wave waits 44 % of its time for loads and
+// barriers.  1024^2 21.8 -> 20.6 us a step, 2048^2 76.2 -> 63.6, Euler 1000 x
+// 700 26.6 -> 20.9; by latency on small grids (64^2 13.7 -> 8.1).
 template <typename T, int EQN, bool BATHY, int FLUX, int RECON, int TX, int TY, int RPW, typename IO>
 __device__ __forceinline__ void stage_compute(const StageArgs<T> &a, const IO &io, const int tile_linear, const int tid,
                                               StageLds<T, EQN, BATHY, TX, TY, RPW> &sh)

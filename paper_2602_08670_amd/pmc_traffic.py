@@ -27,7 +27,7 @@ import os
 import statistics
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/fv_kernels.hip", "csrc/fv_device.hpp", "csrc/fv_internal.hpp")
+KERNEL_SOURCES = ("csrc/fv_kernels.hip", "csrc/stage_device.hpp", "csrc/fv_device.hpp", "csrc/fv_internal.hpp")
 
 
 def kernel_sources_sha256() -> str:

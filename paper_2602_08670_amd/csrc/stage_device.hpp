@@ -308,7 +308,7 @@ template <typename T, int EQN> struct StageIO {
 // Bound by vector-ALU issue and, a grid of one round of tiles, by the wait for
 // its halos: 229 and 253 lane instructions per cell in the two stages of
 // shallow water over a bed (270 and 299 before the faces shared their
-// reconstruction and the flux was rearranged) keep the SIMDs busy for 59 % of
+// reconstruction and the flux was rearranged) keep the SIMDs busy for 62 % of
 // the traced kernels at 1024^2; a wave waits 44 % of its time for loads and
 // barriers.  1024^2 21.8 -> 20.6 us a step, 2048^2 76.2 -> 63.6, Euler 1000 x
 // 700 26.6 -> 20.9; by latency on small grids (64^2 13.7 -> 8.1).

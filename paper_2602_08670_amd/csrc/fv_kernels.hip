@@ -312,6 +312,9 @@ static hipError_t stage_t(const StageDesc &d, const void *qs, const void *q0, vo
     constexpr bool ALL = sizeof(T) == 4 && FLUX == HLLE && RECON == MINMOD;
     int shape = stage_shape((int64_t)d.nx * d.ny, d.prec);
     if (!ALL) shape = shape < 2 ? 0 : 2;
+    // a cell's offset from its tile's first is 32 bits of bytes: fewer rows in
+    // a tile of very long ones
+    if ((uint64_t)(shape_rows(shape) + 4) * d.nx * sizeof(T) >> 32) shape = 0;
     const int tiles_x = (d.nx + TILE_X - 1) / TILE_X, ntiles = (int)stage_tiles(d.nx, d.ny, shape);
     const dim3 grid(xcd_grid(ntiles));
 #define FV_GO(S)                                                                                       \

@@ -51,3 +51,39 @@ def test_periodic_copies_follow_the_network(scheme, flux, ny):
     err = state_rel(big, np.tile(small, (1, 2, 2)))
     assert err <= min(1e-2 * worth, 1e-6), (err, worth)
     assert st2 == (4 * st[0], st[1])
+
+
+@pytest.mark.parametrize("scheme", ["learned", "direct", "blend"])
+@pytest.mark.parametrize("ny", [96, 104])
+def test_redone_steps_on_both_sides(scheme, ny):
+    """A shallow state and a large random head, so that steps fail and are
+    redone with the plain scheme: the same decisions, counts and states two by
+    two as alone (the redone step is the plain FP32 one: 1e-6)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from oracle import learned as L
+    from paper_2602_08670_amd import fv
+    from paper_2602_08670_amd import inputs as I
+
+    nx, steps = 128, 3
+    p = L.init_params(2, scale_last=10.0)
+    vec = fv.params_to_vector([w.numpy() for w in p["w"]], [b.numpy() for b in p["b"]])
+    q = I.random_smooth_swe(nx, seed=2)[:, :ny].astype(np.float32)
+    q[0] *= 0.1
+
+    def run(q):
+        print(f"[learned split] redo {scheme} {q.shape}", flush=True)
+        m = fv.Model(vec, fv.make_model_desc(mean=tuple(p["mean"].tolist()), inv_std=tuple(p["inv_std"].tolist())))
+        s = fv.Solver(q, prec=fv.FV_F32, dt_fixed=2.5e-4, learned=1, h_ref=0.1, lx=q.shape[2] / nx, ly=q.shape[1] / nx)
+        stats = {"learned": s.learned_step, "direct": s.direct_step, "blend": s.blend_step}[scheme](m, steps)
+        out, t = s.state(), s.time()
+        s.close()
+        m.close()
+        return out, stats, t
+
+    small, st, t = run(np.ascontiguousarray(q))
+    big, st2, t2 = run(np.tile(q, (1, 2, 2)))
+    assert st[1] >= 1 and np.isfinite(small).all()
+    assert st2 == (4 * st[0], st[1]) and t2 == t
+    assert state_rel(big, np.tile(small, (1, 2, 2))) <= 1e-6

@@ -97,7 +97,7 @@ struct fv_sphere {
 
 namespace {
 
-template <typename T> hipError_t stage(fv_sphere *s, const T *qs, T *out, double a0, double a1, int last, int ri,
+template <typename T> hipError_t stage(fv_sphere *s, const T *qs, T *out, double a0, double a1, int own, int ri,
                                        int ro, int rc)
 {
     const fv_sphere_config &c = s->cfg;
@@ -118,7 +118,8 @@ template <typename T> hipError_t stage(fv_sphere *s, const T *qs, T *out, double
     a.rate_in = ri;
     a.rate_out = ro;
     a.rate_clear = rc;
-    a.last = last;
+    a.last = own != 0;
+    a.own = own;
     return sph::stage<T>(c.flux, c.recon, a, s->stream);
 }
 
@@ -131,16 +132,24 @@ template <typename T> hipError_t step(fv_sphere *s)
     hipError_t e;
     switch (s->cfg.rk_stages) {
     case 1:
-        e = stage<T>(s, q, q, 0.0, 1.0, 1, ri, ro, rc);
+        e = stage<T>(s, q, S1, 0.0, 1.0, fvk::BAD_EVEN, ri, ro, rc);
+        if (e == hipSuccess) {
+            fvk::StageDesc d{};
+            d.prec = s->cfg.prec;
+            d.eqn = 1;  // four variables
+            d.nx = 2 * s->cfg.n;
+            d.ny = s->cfg.n;
+            e = fvk::launch_step_copy(d, S1, q, s->ctl(), s->stream);
+        }
         break;
     case 2:
         e = stage<T>(s, q, S1, 0.0, 1.0, 0, ri, -1, -1);
-        if (e == hipSuccess) e = stage<T>(s, S1, q, 0.5, 0.5, 1, ri, ro, rc);
+        if (e == hipSuccess) e = stage<T>(s, S1, q, 0.5, 0.5, fvk::BAD_STEP, ri, ro, rc);
         break;
     default:
         e = stage<T>(s, q, S1, 0.0, 1.0, 0, ri, -1, -1);
         if (e == hipSuccess) e = stage<T>(s, S1, S2, 0.75, 0.25, 0, ri, -1, -1);
-        if (e == hipSuccess) e = stage<T>(s, S2, q, 1.0 / 3.0, 2.0 / 3.0, 1, ri, ro, rc);
+        if (e == hipSuccess) e = stage<T>(s, S2, q, 1.0 / 3.0, 2.0 / 3.0, fvk::BAD_STEP, ri, ro, rc);
         break;
     }
     if (e == hipSuccess) s->enq++;

@@ -30,10 +30,12 @@ template <typename T> struct CellArgs {
     fvk::Ctl *ctl;
     unsigned long long *rates;
     int rate_in, rate_out, rate_clear, last;
+    int own;  // the fvk::Bad bit that this launch raises (0: it does not end a step)
 };
 
 template <typename T> hipError_t geometry(const Geometry<T> &G, int n, hipStream_t st);
-// One Runge-Kutta stage (a.qs -> a.out) in one launch over tiles of cells.
+// One Runge-Kutta stage (a.qs -> a.out, another array: neighbouring tiles read
+// each other's cells) in one launch over tiles of cells.
 template <typename T> hipError_t stage(int flux, int recon, const CellArgs<T> &a, hipStream_t st);
 template <typename T>
 hipError_t rate(const T *q, const Geometry<T> &G, int n, double g, fvk::Ctl *ctl, unsigned long long *rates, int slot,

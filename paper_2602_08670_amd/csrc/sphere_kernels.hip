@@ -335,7 +335,7 @@ __global__ __launch_bounds__(NT) void tile_kernel(CellArgs<T> a, int tiles_x)
     const int ty = w / tiles_x, tx = w - ty * tiles_x;
     const int x0 = tx * STX, y0 = ty * STY;
     const int tw = nx - x0 < STX ? nx - x0 : STX, th = ny - y0 < STY ? ny - y0 : STY;  // cells of this tile
-    const bool frozen = a.ctl->bad != 0;
+    const bool frozen = (a.ctl->bad & ~a.own) != 0;  // an earlier step failed
     // the state on the tile and its two-cell ring: x in [x0 - 2, x0 + tw + 2),
     // y in [y0 - 2, y0 + th + 2), each within one period or mirror of the
     // grid (a place past it loads the last one's)
@@ -466,8 +466,9 @@ __global__ __launch_bounds__(NT) void tile_kernel(CellArgs<T> a, int tiles_x)
             if (bad) rate = T(0);
         }
     }
+    if (frozen && blockIdx.x == 0 && tid == 0) atomicOr(&a.ctl->bad, fvk::BAD_SKIP);
     if (!a.last || frozen) return;
-    if (bad) atomicExch(&a.ctl->bad, 1);
+    if (bad) atomicOr(&a.ctl->bad, a.own);
     if (a.rate_out >= 0) {
         const T m = wave_max(rate);
         if ((tid & 63) == 0)
